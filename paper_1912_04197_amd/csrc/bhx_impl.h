@@ -154,6 +154,32 @@ __device__ inline double rsqrt_f64(double r2)
     return fma(0.5 * y, e, y);
 }
 
+// r2^(-3/2) for a positive normal r2 in one third-order step from the hardware
+// estimate y (e = 1 - r2 y^2, at most about 2^-23): y^3 (1 - e)^(-3/2) =
+// y^3 (1 + 3/2 e + 15/8 e^2) up to 35/16 e^3 < 2^-67, so only the roundings of
+// the last products count (under three of them, as in cubing rsqrt_f64, at four
+// instructions fewer). With RI also ri = r2^(-1/2) = y (1 + e / 2 + 3/8 e^2).
+// The constants that an instruction cannot hold, kept in registers by the
+// caller (the compiler would reload them for every term).
+struct CubeConsts {
+    double c1, c2, h2;
+};
+__device__ inline CubeConsts cube_consts()
+{
+    CubeConsts k{1.5, 1.875, 0.375};
+    asm("" : "+v"(k.c1), "+v"(k.c2), "+v"(k.h2));
+    return k;
+}
+template <bool RI>
+__device__ inline double inv_cube_f64(double r2, double &ri, const CubeConsts &k)
+{
+    const double y = __builtin_amdgcn_rsq(r2), y2 = y * y;
+    const double e = fma(-r2, y2, 1.0);
+    if (RI) ri = fma(y * e, fma(e, k.h2, 0.5), y);
+    const double y3 = y * y2;
+    return fma(y3 * e, fma(e, k.c2, k.c1), y3);
+}
+
 // A pair term counts only when its squared softened distance is a positive
 // normal number in the precision it is computed in: r^2 = 0 (coincident
 // unsoftened bodies) and subnormal r^2 (the same coincidence below the
@@ -208,10 +234,11 @@ struct Workspace {
     int32_t *prefix_mark = nullptr;
 };
 
-// The direct sum splits its sources over up to kDirectSplits block rows when
-// the targets alone give fewer than kDirectBlocks blocks; each row's partial
-// sums (4 doubles per target) go to a workspace buffer of kDirectPart doubles
-// and are added in row order.
+// The direct sum and its VJP split their sources over block rows when the
+// targets alone give too few blocks; each row's partial sums (4 doubles per
+// target) go to a workspace buffer of kDirectPart doubles and are added in row
+// order. Up to kDirectSmall bodies the direct sum needs no rows.
+constexpr int64_t kDirectSmall = 4096;
 constexpr int kDirectBlocks = 1024;
 constexpr int kDirectSplits = 64;
 constexpr int64_t kDirectPart = (int64_t)kDirectBlocks * 256 * 4;

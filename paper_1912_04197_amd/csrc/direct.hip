@@ -1,13 +1,19 @@
 // Direct N^2 sum, eq. (Newton) with every term softened as in
 // eq. (Force_rComp): a_i = G sum_{j != i} m_j d_ij / (|d_ij|^2 + eps_ij^2)^(3/2).
 //
-// One thread per target, 256 targets per block; sources stream through LDS in
-// tiles of 256 (positions in FP64 so that d_ij is formed in FP64 even in FP32C
-// mode, where only the pair arithmetic after the difference is FP32 and FP32
-// partial sums over at most 32 sources are added into FP64 accumulators).
-// When the targets give too few blocks to fill the GPU, block row y sums only
-// the y-th range of source tiles into a partial buffer, and a second kernel
-// adds the rows in order (so the result does not depend on scheduling).
+// Sources are summed in groups of 32, staged in LDS; positions stay FP64, so
+// that d_ij is formed in FP64 even in FP32C mode, where only the pair
+// arithmetic after the difference is FP32 and the FP32 partial sums of one
+// group are added into FP64 accumulators. Two kernels sweep the groups:
+//   k_direct        a block's four waves share 128 targets (two per lane) and
+//                   take the groups of a 256-source tile in turn; where the
+//                   targets give too few blocks to fill the GPU, block row y
+//                   sums the y-th range of tiles into a partial buffer, and a
+//                   second kernel adds the rows in order;
+//   k_direct_small  up to kDirectSmall bodies: a block serves 8 or 16
+//                   targets and all sources, its lanes sharing the groups, so
+//                   that one launch fills the GPU and nothing is added later.
+// Every sum has a fixed order, so results do not depend on scheduling.
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -17,169 +23,442 @@
 namespace bhx {
 namespace {
 
-constexpr int kTile = 256;
+constexpr int kGroup = 32;  // sources of one FP32C partial sum
+constexpr int kTile = 256;  // sources staged at a time by k_direct
+constexpr int kTargets = 2;              // targets per lane of k_direct
+constexpr int kBlockTargets = 64 * kTargets;
 
-// One source as a tile holds it in LDS: one record per source, so a sweep
-// reads it from a single address with immediate offsets.
-struct alignas(16) SrcD {  // FP64: position, mass, half the squared softening
+// One source as LDS holds it, read from one address with immediate offsets.
+template <bool PEPS>
+struct alignas(16) SrcD {  // FP64: position, mass
+    double x, y, z, m;
+};
+template <>
+struct alignas(16) SrcD<true> {  // and half the squared softening
     double x, y, z, m, eh, pad;
 };
 struct alignas(16) SrcF {  // FP32C: FP64 position; FP32 mass and half squared softening
     double x, y, z;
     float m, eh;
 };
+template <int PREC, bool PEPS>
+using Src = typename std::conditional<PREC == BH_FP64, SrcD<PEPS>, SrcF>::type;
+
+template <int PREC, bool PEPS>
+__device__ inline Src<PREC, PEPS> load_source(const double *__restrict__ pos,
+                                              const double *__restrict__ mass,
+                                              const double *__restrict__ eps, int64_t j)
+{
+    double eh = 0.0;
+    if (PEPS) {
+        const double e = eps[j];
+        eh = 0.5 * (e * e);
+    }
+    Src<PREC, PEPS> q;
+    q.x = pos[3 * j];
+    q.y = pos[3 * j + 1];
+    q.z = pos[3 * j + 2];
+    if constexpr (PREC == BH_FP64) {
+        q.m = mass[j];
+        if constexpr (PEPS) q.eh = eh;
+    } else {  // the FP32 operands, rounded once per source
+        q.m = (float)mass[j];
+        q.eh = (float)eh;
+    }
+    return q;
+}
+
+struct Target {
+    double x, y, z;
+    double eh;  // half the squared softening: (eps_i^2 + eps_j^2) / 2 = eh_i + eh_j exactly
+    float ehf;
+    double ax, ay, az, ph;  // sums
+};
+
+// Whether a pair has to be looked at before it is added. A group in which no
+// target meets itself needs no index test. In FP32C, where every pair's FP32
+// softening is a positive normal number, so is its r^2, and the r^2 test is
+// dropped too; other FP32C pairs are tested one by one. In FP64 the pairs of a
+// group are tested together: only a group with a dead pair takes them singly.
+enum { kPlain = 0, kTest = 1, kSkip = 2 };
+
+// Adds the terms of `cnt` sources at q to the T targets of this lane. skip[t]
+// (kSkip only): target t's own place in the group, or outside 0..cnt-1.
+//
+// Bound by VALU issue (a wave64 FP32 or FP64 operation takes about four cycles
+// of its SIMD). An FP32C pair takes 16 instructions softened and 18 unsoftened,
+// where testing every pair's index and r^2 took 19; an FP64 pair 18, where two
+// Newton steps, the cube and m d r^-3 per axis took 27. Two targets per lane
+// halve the LDS reads (two ds_read_b128 per source), which kept the LDS pipe
+// 62 % busy with one. 65536 bodies, one sum, before and after: FP32C 2.19 ->
+// 1.77 ms (per-body softening), 2.14 -> 1.68 ms (one softening), FP64 4.43 ->
+// 2.75 ms.
+template <int PREC, bool PEPS, bool PHI, int T, int MODE, bool FULL>
+__device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Target (&tg)[T],
+                                          double eps0sq, float eps0f, const int (&skip)[T])
+{
+    if (FULL) cnt = kGroup;
+    if constexpr (PREC == BH_FP64) {
+        const CubeConsts k = cube_consts();
+        auto one = [&](const Src<PREC, PEPS> &s, Target &g, int jj, int own) {
+            const double dx = s.x - g.x, dy = s.y - g.y, dz = s.z - g.z;
+            double e2 = eps0sq;
+            if constexpr (PEPS) e2 = g.eh + s.eh;
+            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
+            if (positive_normal(r2) && (MODE != kSkip || jj != own)) {
+                double ri;
+                const double c = s.m * inv_cube_f64<PHI>(r2, ri, k);
+                g.ax = fma(c, dx, g.ax);
+                g.ay = fma(c, dy, g.ay);
+                g.az = fma(c, dz, g.az);
+                if (PHI) g.ph -= s.m * ri;
+            }
+        };
+        if constexpr (FULL) {
+            // every pair live but a target's own: the group's sums, kept if so
+            double sx[T], sy[T], sz[T], sp[T];
+#pragma unroll
+            for (int t = 0; t < T; t++) sx[t] = sy[t] = sz[t] = sp[t] = 0.0;
+            bool live = true;
+#pragma unroll 2
+            for (int jj = 0; jj < kGroup; jj++) {
+                const Src<PREC, PEPS> s = q[jj];
+#pragma unroll
+                for (int t = 0; t < T; t++) {
+                    const bool own = MODE == kSkip && jj == skip[t];  // d = 0 there
+                    const double dx = s.x - tg[t].x, dy = s.y - tg[t].y, dz = s.z - tg[t].z;
+                    double e2 = eps0sq;
+                    if constexpr (PEPS) e2 = tg[t].eh + s.eh;
+                    const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
+                    live = live && (own || positive_normal(r2));
+                    double ri;
+                    double c = s.m * inv_cube_f64<PHI>(r2, ri, k);
+                    if (own) c = ri = 0.0;
+                    sx[t] = fma(c, dx, sx[t]);
+                    sy[t] = fma(c, dy, sy[t]);
+                    sz[t] = fma(c, dz, sz[t]);
+                    if (PHI) sp[t] -= s.m * ri;
+                }
+            }
+            if (__ballot(!live) == 0) {
+#pragma unroll
+                for (int t = 0; t < T; t++) {
+                    tg[t].ax += sx[t];
+                    tg[t].ay += sy[t];
+                    tg[t].az += sz[t];
+                    if (PHI) tg[t].ph += sp[t];
+                }
+                return;
+            }
+        }
+#pragma unroll 1
+        for (int jj = 0; jj < cnt; jj++) {
+            const Src<PREC, PEPS> s = q[jj];
+#pragma unroll
+            for (int t = 0; t < T; t++) one(s, tg[t], jj, MODE == kSkip ? skip[t] : -1);
+        }
+    } else {
+        float fx[T], fy[T], fz[T], fp[T];
+#pragma unroll
+        for (int t = 0; t < T; t++) fx[t] = fy[t] = fz[t] = fp[t] = 0.f;
+#pragma unroll(FULL ? 4 : 1)
+        for (int jj = 0; jj < cnt; jj++) {
+            const SrcF s = q[jj];
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                const float dx = (float)(s.x - tg[t].x), dy = (float)(s.y - tg[t].y),
+                            dz = (float)(s.z - tg[t].z);
+                const float e2 = PEPS ? s.eh + tg[t].ehf : eps0f;
+                const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, e2)));
+                float rinv = __builtin_amdgcn_rsqf(r2);
+                if (MODE != kPlain)
+                    rinv = positive_normal_f(r2) && (MODE != kSkip || jj != skip[t]) ? rinv : 0.f;
+                const float mr = s.m * rinv;
+                const float mr3 = mr * rinv * rinv;
+                fx[t] = fmaf(mr3, dx, fx[t]);
+                fy[t] = fmaf(mr3, dy, fy[t]);
+                fz[t] = fmaf(mr3, dz, fz[t]);
+                if (PHI) fp[t] -= mr;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < T; t++) {
+            tg[t].ax += (double)fx[t];
+            tg[t].ay += (double)fy[t];
+            tg[t].az += (double)fz[t];
+            if (PHI) tg[t].ph += (double)fp[t];
+        }
+    }
+}
+
+// The same, choosing the form: `own` (the same on every active lane) where a
+// target may be among the sources, `soft` (the same on every active lane) where
+// every pair of the group is softened as kPlain asks.
+template <int PREC, bool PEPS, bool PHI, int T>
+__device__ __forceinline__ void add_group(const Src<PREC, PEPS> *q, int cnt, bool full,
+                                          Target (&tg)[T], double eps0sq, float eps0f,
+                                          const int (&skip)[T], bool own, bool soft)
+{
+    if (!full)
+        sum_group<PREC, PEPS, PHI, T, kSkip, false>(q, cnt, tg, eps0sq, eps0f, skip);
+    else if (own)
+        sum_group<PREC, PEPS, PHI, T, kSkip, true>(q, cnt, tg, eps0sq, eps0f, skip);
+    else if (PREC == BH_FP64 || soft)
+        sum_group<PREC, PEPS, PHI, T, kPlain, true>(q, cnt, tg, eps0sq, eps0f, skip);
+    else
+        sum_group<PREC, PEPS, PHI, T, kTest, true>(q, cnt, tg, eps0sq, eps0f, skip);
+}
+
+template <bool PEPS>
+__device__ inline Target load_target(const double *__restrict__ pos,
+                                     const double *__restrict__ eps, int64_t i)
+{
+    Target g;
+    g.x = pos[3 * i];
+    g.y = pos[3 * i + 1];
+    g.z = pos[3 * i + 2];
+    g.eh = 0.0;
+    if (PEPS) {
+        const double e = eps[i];
+        g.eh = 0.5 * (e * e);
+    }
+    g.ehf = (float)g.eh;
+    g.ax = g.ay = g.az = g.ph = 0.0;
+    return g;
+}
+
+// A softening that makes every r^2 of its target a positive normal FP32
+// number, given that the other half is a number (not NaN).
+__device__ inline bool softened(bool peps, float ehf, float eps0f)
+{
+    return positive_normal_f(peps ? ehf : eps0f);
+}
 
 template <int PREC, bool PEPS, bool PHI>
-__global__ __launch_bounds__(kTile) void k_direct(const double *__restrict__ pos,
-                                                  const double *__restrict__ mass,
-                                                  const double *__restrict__ eps, int64_t n,
-                                                  double eps0sq, double G,
-                                                  double *__restrict__ acc,
-                                                  double *__restrict__ phi, int64_t chunk,
-                                                  double *__restrict__ part)
+__global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
+                                                const double *__restrict__ mass,
+                                                const double *__restrict__ eps, int64_t n,
+                                                double eps0sq, double G,
+                                                double *__restrict__ acc,
+                                                double *__restrict__ phi, int64_t chunk,
+                                                double *__restrict__ part)
 {
-    using Src = typename std::conditional<PREC == BH_FP64, SrcD, SrcF>::type;
-    __shared__ Src src[kTile];
-    const int tid = threadIdx.x;
-    const int64_t i = (int64_t)blockIdx.x * kTile + tid;
-    const bool valid = i < n;
-    const double xi = valid ? pos[3 * i] : 0.0, yi = valid ? pos[3 * i + 1] : 0.0,
-                 zi = valid ? pos[3 * i + 2] : 0.0;
-    double ei2 = 0.0;
-    if (PEPS && valid) {
-        const double e = eps[i];
-        ei2 = e * e;
-    }
-    const double ehi = 0.5 * ei2;  // (eps_i^2 + eps_j^2) / 2 = ehi + eps_j^2 / 2 exactly
-    const float e2hB = (float)ehi;
+    using S = Src<PREC, PEPS>;
+    __shared__ S src[kTile];
+    __shared__ double red[3][4][kBlockTargets];  // the other waves' sums
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t b0 = (int64_t)blockIdx.x * kBlockTargets;
+    Target tg[kTargets];
+    int64_t ti[kTargets];
     const float eps0f = (float)eps0sq;
-    double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
-
+    bool soft = true;
+#pragma unroll
+    for (int t = 0; t < kTargets; t++) {
+        ti[t] = b0 + 64 * t + lane;
+        // lanes past the end repeat the last target; nothing of theirs is stored
+        tg[t] = load_target<PEPS>(pos, eps, ti[t] < n ? ti[t] : n - 1);
+        soft = soft && softened(PEPS, tg[t].ehf, eps0f);
+    }
+    soft = __ballot(!soft) == 0;
     // this block row's sources: [s_lo, s_hi)
     const int64_t s_lo = (int64_t)blockIdx.y * chunk;
     const int64_t s_hi = s_lo + chunk < n ? s_lo + chunk : n;
     for (int64_t base = s_lo; base < s_hi; base += kTile) {
         const int64_t j = base + tid;
+        bool number = true;  // no NaN among the tile's FP32 softenings
         if (j < s_hi) {
-            double eh = 0.0;
-            if (PEPS) {
-                const double e = eps[j];
-                eh = 0.5 * (e * e);
-            }
-            if constexpr (PREC == BH_FP64)
-                src[tid] = SrcD{pos[3 * j], pos[3 * j + 1], pos[3 * j + 2], mass[j], eh, 0.0};
-            else  // the FP32 operands, rounded once per source
-                src[tid] = SrcF{pos[3 * j], pos[3 * j + 1], pos[3 * j + 2], (float)mass[j],
-                                (float)eh};
+            src[tid] = load_source<PREC, PEPS>(pos, mass, eps, j);
+            if constexpr (PREC != BH_FP64 && PEPS) number = src[tid].eh >= 0.f;
         }
-        __syncthreads();
+        const bool tile_ok = __syncthreads_and(number);
         const int cnt = (int)((s_hi - base) < kTile ? (s_hi - base) : kTile);
-        const int skip = (valid && i >= base && i < base + cnt) ? (int)(i - base) : -1;
-        if constexpr (PREC == BH_FP64) {
-#pragma unroll 4
-            for (int jj = 0; jj < cnt; jj++) {
-                const SrcD q = src[jj];
-                const double dx = q.x - xi, dy = q.y - yi, dz = q.z - zi;
-                const double e2 = PEPS ? ehi + q.eh : eps0sq;
-                const double r2 = dx * dx + dy * dy + dz * dz + e2;
-                if (jj != skip && positive_normal(r2)) {
-                    const double rinv = rsqrt_f64(r2);
-                    const double inv3 = rinv * rinv * rinv;
-                    ax += q.m * dx * inv3;
-                    ay += q.m * dy * inv3;
-                    az += q.m * dz * inv3;
-                    if (PHI) ph -= q.m * rinv;
-                }
+        const bool own = base < b0 + kBlockTargets && base + cnt > b0;
+#pragma unroll 1
+        for (int g = wave; g * kGroup < cnt; g += 4) {
+            const int gc = cnt - g * kGroup < kGroup ? cnt - g * kGroup : kGroup;
+            int skip[kTargets];
+#pragma unroll
+            for (int t = 0; t < kTargets; t++) {
+                const int64_t at = ti[t] - base - g * kGroup;
+                skip[t] = own && at >= 0 && at < gc ? (int)at : -1;
             }
-        } else {
-            for (int j0 = 0; j0 < cnt; j0 += 32) {
-                const int jn = j0 + 32 < cnt ? j0 + 32 : cnt;
-                float fx = 0.f, fy = 0.f, fz = 0.f, fp = 0.f;
-#pragma unroll 4
-                for (int jj = j0; jj < jn; jj++) {
-                    const SrcF q = src[jj];
-                    const float dx = (float)(q.x - xi), dy = (float)(q.y - yi),
-                                dz = (float)(q.z - zi);
-                    const float e2 = PEPS ? q.eh + e2hB : eps0f;
-                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, e2)));
-                    const float rinv =
-                        (jj != skip && positive_normal_f(r2)) ? __builtin_amdgcn_rsqf(r2) : 0.f;
-                    const float mr = q.m * rinv;
-                    const float mr3 = mr * rinv * rinv;
-                    fx = fmaf(mr3, dx, fx);
-                    fy = fmaf(mr3, dy, fy);
-                    fz = fmaf(mr3, dz, fz);
-                    if (PHI) fp -= mr;
-                }
-                ax += (double)fx;
-                ay += (double)fy;
-                az += (double)fz;
-                if (PHI) ph += (double)fp;
-            }
+            add_group<PREC, PEPS, PHI, kTargets>(src + g * kGroup, gc, gc == kGroup, tg, eps0sq,
+                                                 eps0f, skip, own, soft && tile_ok);
         }
         __syncthreads();
     }
-    if (valid && gridDim.y == 1) {
-        acc[3 * i] = G * ax;
-        acc[3 * i + 1] = G * ay;
-        acc[3 * i + 2] = G * az;
-        if (PHI) phi[i] = G * ph;
-    } else if (valid) {
-        double *q = part + 4 * ((int64_t)blockIdx.y * n + i);
-        q[0] = ax;
-        q[1] = ay;
-        q[2] = az;
-        q[3] = ph;
+    // the waves' sums in wave order
+    if (wave > 0)
+#pragma unroll
+        for (int t = 0; t < kTargets; t++) {
+            double(*r)[kBlockTargets] = red[wave - 1];
+            r[0][64 * t + lane] = tg[t].ax;
+            r[1][64 * t + lane] = tg[t].ay;
+            r[2][64 * t + lane] = tg[t].az;
+            if (PHI) r[3][64 * t + lane] = tg[t].ph;
+        }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int t = 0; t < kTargets; t++) {
+        const int64_t i = ti[t];
+        if (i >= n) continue;
+        double ax = tg[t].ax, ay = tg[t].ay, az = tg[t].az, ph = tg[t].ph;
+#pragma unroll
+        for (int w = 0; w < 3; w++) {
+            ax += red[w][0][64 * t + lane];
+            ay += red[w][1][64 * t + lane];
+            az += red[w][2][64 * t + lane];
+            if (PHI) ph += red[w][3][64 * t + lane];
+        }
+        if (gridDim.y == 1) {
+            acc[3 * i] = G * ax;
+            acc[3 * i + 1] = G * ay;
+            acc[3 * i + 2] = G * az;
+            if (PHI) phi[i] = G * ph;
+        } else {
+            double *q = part + 4 * ((int64_t)blockIdx.y * n + i);
+            q[0] = ax;
+            q[1] = ay;
+            q[2] = az;
+            q[3] = ph;
+        }
     }
 }
 
-// acc_i = G * sum over the block rows of their partial sums, in row order.
+// acc_i = G * sum over the block rows of their partial sums, in row order;
+// one thread per target and component, so that a wave reads whole lines.
 __global__ __launch_bounds__(256) void k_direct_reduce(const double *__restrict__ part,
                                                        int64_t n, int rows, double G,
                                                        double *__restrict__ acc,
                                                        double *__restrict__ phi)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
-    for (int r = 0; r < rows; r++) {
-        const double *q = part + 4 * ((int64_t)r * n + i);
-        ax += q[0];
-        ay += q[1];
-        az += q[2];
-        ph += q[3];
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = t >> 2;
+    const int c = (int)(t & 3);
+    if (i >= n || (c == 3 && !phi)) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int r = 0; r < rows; r++) s += part[4 * (int64_t)r * n + t];
+    if (c == 3)
+        phi[i] = G * s;
+    else
+        acc[3 * i + c] = G * s;
+}
+
+// Up to kDirectSmall bodies: 512 threads serve TG targets; lane l of wave w is
+// share w (64 / TG) + l / TG of target l % TG and sums every S-th group of
+// sources, S = 512 / TG shares, the S groups of a step staged in LDS (each
+// group 16 bytes past a multiple of 256, so that the shares of a wave read
+// from distinct banks).
+constexpr int kSmallThreads = 512;
+template <int PREC, bool PEPS, bool PHI, int TG>
+__global__ __launch_bounds__(kSmallThreads) void k_direct_small(
+    const double *__restrict__ pos, const double *__restrict__ mass,
+    const double *__restrict__ eps, int n, double eps0sq, double G, double *__restrict__ acc,
+    double *__restrict__ phi)
+{
+    using S = Src<PREC, PEPS>;
+    constexpr int kShares = kSmallThreads / TG, kWaveShares = 64 / TG, W = kSmallThreads / 64;
+    constexpr int kStride = kGroup * (int)sizeof(S) + 16;
+    static_assert((kGroup * sizeof(S)) % 256 == 0, "group stride");
+    __shared__ alignas(16) char tile[kShares * kStride];
+    __shared__ double red[W][4][TG];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tl = lane % TG, share = wave * kWaveShares + lane / TG;
+    const int b0 = (int)blockIdx.x * TG, i = b0 + tl;
+    const float eps0f = (float)eps0sq;
+    Target tg[1] = {load_target<PEPS>(pos, eps, i < n ? i : n - 1)};
+    const bool soft = __ballot(!softened(PEPS, tg[0].ehf, eps0f)) == 0;
+    for (int base = 0; base < n; base += kShares * kGroup) {
+        bool number = true;
+        const int in = n - base < kShares * kGroup ? n - base : kShares * kGroup;
+        for (int k = tid; k < in; k += kSmallThreads) {
+            const S s = load_source<PREC, PEPS>(pos, mass, eps, base + k);
+            *(S *)(tile + (k / kGroup) * kStride + (k % kGroup) * (int)sizeof(S)) = s;
+            if constexpr (PREC != BH_FP64 && PEPS) number = number && s.eh >= 0.f;
+        }
+        const bool tile_ok = __syncthreads_and(number);
+        const int left = in - share * kGroup;
+        const int cnt = left < 0 ? 0 : left < kGroup ? left : kGroup;
+        const int at = i - base - share * kGroup;
+        const int skip[1] = {at >= 0 && at < cnt ? at : -1};
+        // uniform over the wave: whether any of its shares holds one of the
+        // block's targets, and whether all its groups are whole
+        const int g0 = base + share * kGroup;
+        const bool own = __ballot(g0 < b0 + TG && g0 + cnt > b0) != 0;
+        const bool full = __ballot(cnt != kGroup) == 0;
+        if (__ballot(cnt > 0) != 0)
+            add_group<PREC, PEPS, PHI, 1>((const S *)(tile + share * kStride), cnt, full, tg,
+                                          eps0sq, eps0f, skip, own, soft && tile_ok);
+        __syncthreads();
     }
-    acc[3 * i] = G * ax;
-    acc[3 * i + 1] = G * ay;
-    acc[3 * i + 2] = G * az;
-    if (phi) phi[i] = G * ph;
+    // the shares in a fixed order: over the wave, then over the waves
+    double v[4] = {tg[0].ax, tg[0].ay, tg[0].az, tg[0].ph};
+#pragma unroll
+    for (int o = TG; o < 64; o <<= 1)
+#pragma unroll
+        for (int c = 0; c < (PHI ? 4 : 3); c++) v[c] += __shfl_xor(v[c], o);
+    if (lane < TG)
+#pragma unroll
+        for (int c = 0; c < (PHI ? 4 : 3); c++) red[wave][c][lane] = v[c];
+    __syncthreads();
+    const int c = tid / TG;  // one thread per target and component
+    if (c >= (PHI ? 4 : 3) || b0 + tid % TG >= n) return;
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; w++) s += red[w][c][tid % TG];
+    const int64_t o = b0 + tid % TG;
+    if (c == 3)
+        phi[o] = G * s;
+    else
+        acc[3 * o + c] = G * s;
+}
+
+template <int PREC, bool PEPS, bool PHI>
+hipError_t launch_t(hipStream_t s, const double *pos, const double *mass, const double *eps,
+                    int64_t n, double eps0sq, double G, double *acc, double *phi, double *part)
+{
+    if (n <= kDirectSmall) {
+        // the fewest targets per block that keep the blocks near one per CU:
+        // one sum of 2048 bodies 41 -> 12 us in FP64 (64 blocks of 256 targets
+        // and the row sums' launch before), 21 -> 11 us in FP32C; 4096 bodies
+        // 43 -> 21 and 23 -> 16 us. Above, k_direct's rows fill the GPU and its
+        // two targets per lane win (6000 bodies in FP64: 37 us against 50 here
+        // with 32 targets per block)
+        if (n <= 2048)
+            k_direct_small<PREC, PEPS, PHI, 8><<<(unsigned)((n + 7) / 8), kSmallThreads, 0, s>>>(
+                pos, mass, eps, (int)n, eps0sq, G, acc, phi);
+        else
+            k_direct_small<PREC, PEPS, PHI, 16>
+                <<<(unsigned)((n + 15) / 16), kSmallThreads, 0, s>>>(pos, mass, eps, (int)n,
+                                                                     eps0sq, G, acc, phi);
+        return hipGetLastError();
+    }
+    // rows of source ranges (whole tiles): as many as the partial buffer
+    // holds, which makes 2048 blocks (eight a CU) for any smaller n
+    const int64_t tb = (n + kBlockTargets - 1) / kBlockTargets;
+    const int64_t all = (n + kTile - 1) / kTile;
+    int64_t rows = part ? kDirectPart / (4 * n) : 1;
+    if (rows < 1) rows = 1;
+    if (rows > all) rows = all;  // at least one source tile per row
+    const int64_t tiles = (all + rows - 1) / rows;
+    rows = (all + tiles - 1) / tiles;
+    const dim3 grid((unsigned)tb, (unsigned)rows);
+    k_direct<PREC, PEPS, PHI><<<grid, 256, 0, s>>>(pos, mass, eps, n, eps0sq, G, acc, phi,
+                                                   rows == 1 ? n : tiles * kTile, part);
+    if (rows > 1)
+        k_direct_reduce<<<(unsigned)((4 * n + 255) / 256), 256, 0, s>>>(part, n, (int)rows, G, acc,
+                                                                        phi);
+    return hipGetLastError();
 }
 
 template <int PREC, bool PEPS>
 hipError_t launch_p(hipStream_t s, const double *pos, const double *mass, const double *eps,
                     int64_t n, double eps0sq, double G, double *acc, double *phi, double *part)
 {
-    // rows of source ranges (whole tiles) so that targets x rows reaches
-    // kDirectBlocks; rows * n <= kDirectBlocks * kTile fits the partial buffer
-    const int64_t tb = (n + kTile - 1) / kTile;
-    int64_t rows = tb >= kDirectBlocks ? 1 : kDirectBlocks / tb;
-    if (rows > kDirectSplits) rows = kDirectSplits;
-    if (rows > tb) rows = tb;  // at least one source tile per row
-    const int64_t tiles = (tb + rows - 1) / rows;
-    const int64_t chunk = tiles * kTile;
-    rows = (tb + tiles - 1) / tiles;
-    if (!part) rows = 1;
-    const dim3 grid((unsigned)tb, (unsigned)rows);
-    const int64_t ch = rows == 1 ? n : chunk;
-    if (phi)
-        k_direct<PREC, PEPS, true>
-            <<<grid, kTile, 0, s>>>(pos, mass, eps, n, eps0sq, G, acc, phi, ch, part);
-    else
-        k_direct<PREC, PEPS, false>
-            <<<grid, kTile, 0, s>>>(pos, mass, eps, n, eps0sq, G, acc, phi, ch, part);
-    if (rows > 1)
-        k_direct_reduce<<<(unsigned)tb, 256, 0, s>>>(part, n, (int)rows, G, acc, phi);
-    return hipGetLastError();
+    return phi ? launch_t<PREC, PEPS, true>(s, pos, mass, eps, n, eps0sq, G, acc, phi, part)
+               : launch_t<PREC, PEPS, false>(s, pos, mass, eps, n, eps0sq, G, acc, phi, part);
 }
 
 }  // namespace
