@@ -180,6 +180,16 @@ __device__ inline double inv_cube_f64(double r2, double &ri, const CubeConsts &k
     return fma(y3 * e, fma(e, k.c2, k.c1), y3);
 }
 
+// The same, with i2 = 1 / r2 = y^2 (1 + e + e^2) up to e^3.
+__device__ inline double inv_cube_sq_f64(double r2, double &i2, const CubeConsts &k)
+{
+    const double y = __builtin_amdgcn_rsq(r2), y2 = y * y;
+    const double e = fma(-r2, y2, 1.0);
+    i2 = fma(y2, fma(e, e, e), y2);
+    const double y3 = y * y2;
+    return fma(y3 * e, fma(e, k.c2, k.c1), y3);
+}
+
 // A pair term counts only when its squared softened distance is a positive
 // normal number in the precision it is computed in: r^2 = 0 (coincident
 // unsoftened bodies) and subnormal r^2 (the same coincidence below the
@@ -240,7 +250,6 @@ struct Workspace {
 // order. Up to kDirectSmall bodies the direct sum needs no rows.
 constexpr int64_t kDirectSmall = 4096;
 constexpr int kDirectBlocks = 1024;
-constexpr int kDirectSplits = 64;
 constexpr int64_t kDirectPart = (int64_t)kDirectBlocks * 256 * 4;
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;

@@ -55,3 +55,26 @@ def test_direct_dead_pairs(n, precision):
     eps[::7] = 0.0
     eps[[3, n // 2]] = 0.0
     _run(pos, s.mass, 0.0, eps, precision)
+
+
+@pytest.mark.parametrize("per_body", [False, True])
+@pytest.mark.parametrize("n", [2, 33, 64, 65, 257, 700, 4097])
+def test_direct_vjp_sizes(n, per_body):
+    """The direct VJP at the edges of its groups, tiles and blocks, and with
+    unsoftened coincident bodies, at the VJPs' bar (1e-10 of the largest
+    component: sums of n terms in another order)."""
+    from paper_1912_04197_amd.api import Context
+
+    s = ics.rubble_pile(n, seed=900 + n)
+    pos, eps = s.pos.copy(), s.eps.copy()
+    if n > 2:  # coincident and unsoftened: no contribution
+        pos[n // 2] = pos[1]
+        eps[[1, n // 2]] = 0.0
+    lam = np.random.default_rng(n).standard_normal((n, 3))
+    up = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    e = eps if per_body else None
+    ctx = Context(n, precision="fp64", adjoint=True, G=0.9)
+    got = ctx.accel_vjp(up(pos), up(s.mass), up(lam), theta=-1.0, softening=0.0, eps=up(e))
+    ref = oracle.direct_vjp(pos, s.mass, lam, softening=0.0, eps=e, G=0.9)
+    for a, r in zip(got, ref):
+        assert np.abs(a.cpu().numpy() - r).max() <= 1e-10 * np.abs(r).max()
