@@ -205,8 +205,10 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
 }
 
 // Root cube: side = largest extent (1 if all bodies coincide), centred on the
-// bounding box; the quantisation scale and the squared cell side per level.
-__device__ inline void root_cube(SceneBox &b, const double lo[3], const double hi[3])
+// bounding box; the quantisation scale and the squared cell side per level
+// (those of levels l_first, l_first + l_step, ...).
+__device__ inline void root_cube(SceneBox &b, const double lo[3], const double hi[3],
+                                 int l_first = 0, int l_step = 1)
 {
 #pragma clang fp contract(off)
     double L = 0.0;
@@ -222,7 +224,7 @@ __device__ inline void root_cube(SceneBox &b, const double lo[3], const double h
     }
     b.L = L;
     b.S = 2097152.0 / L;
-    for (int l = 0; l < kLevels; l++) {
+    for (int l = l_first; l < kLevels; l += l_step) {
         double sd = ldexp(L, -l);
         b.s2[l] = sd * sd;
     }
@@ -1310,9 +1312,81 @@ __global__ __launch_bounds__(1024) void k_prefix_levels(int32_t *__restrict__ ma
 
 // ------------------------------------------------------------ 6. moments
 
-// Mass, centre of mass and mass-weighted softening of every node of `level`,
-// by eq. (COMinternal): from the children of an internal node, from the
-// bodies of a leaf. Products and sums are rounded as written.
+// The sums of a node's mass, centre of mass and mass-weighted softening over
+// its bodies or its children, in member order, by eq. (COMinternal). Products
+// and sums are rounded as written; each group's loads are all issued before its
+// first addition.
+struct MomentSum {
+    double ms = 0.0, mx = 0.0, my = 0.0, mz = 0.0, me = 0.0;
+
+    __device__ inline void add(double x, double y, double z, double m, double e, bool use_eps)
+    {
+#pragma clang fp contract(off)
+        ms += m;
+        mx += x * m;
+        my += y * m;
+        mz += z * m;
+        if (use_eps) me += e * m;
+    }
+    __device__ inline void leaf(const Body *__restrict__ body, const double *__restrict__ beps2,
+                                const NodeInfo &info, bool use_eps)
+    {
+        const int32_t end = info.first + info.count;
+        for (int32_t s0 = info.first; s0 < end; s0 += 4) {
+            Body b[4];
+            double e[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int32_t s = s0 + u < end ? s0 + u : s0;
+                b[u] = body[s];
+                e[u] = use_eps ? beps2[s] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (s0 + u >= end) break;
+                add(b[u].x, b[u].y, b[u].z, b[u].m, e[u], use_eps);
+            }
+        }
+    }
+    __device__ inline void children(const NodeMom *nmom, const double *neps2, const NodeInfo &info,
+                                    bool use_eps)
+    {
+        const int nch = node_nchild(info);
+        NodeMom cm[8];
+        double e[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int32_t c = info.child0 + (u < nch ? u : 0);
+            cm[u] = nmom[c];
+            e[u] = use_eps ? neps2[c] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            if (u >= nch) break;
+            add(cm[u].x, cm[u].y, cm[u].z, cm[u].m, e[u], use_eps);
+        }
+    }
+    // The node's moments and mean eps^2; a massless cell has its centre.
+    __device__ inline NodeMom moments(int level, int32_t first, const uint64_t *__restrict__ keys,
+                                      const SceneBox &b, bool use_eps, double &e2) const
+    {
+#pragma clang fp contract(off)
+        e2 = 0.0;
+        if (ms > 0.0) {
+            if (use_eps) e2 = me / ms;
+            return NodeMom{mx / ms, my / ms, mz / ms, ms};
+        }
+        const uint64_t key = keys[first];
+        const int sh = kMaxLevel - level;
+        const double s = ldexp(b.L, -level);
+        return NodeMom{b.x0[0] + ((double)(compact3(key >> 2) >> sh) + 0.5) * s,
+                       b.x0[1] + ((double)(compact3(key >> 1) >> sh) + 0.5) * s,
+                       b.x0[2] + ((double)(compact3(key) >> sh) + 0.5) * s, 0.0};
+    }
+};
+
+// The moments of every node of `level`: of an internal node from its
+// children, of a leaf from its bodies.
 __device__ inline void moments_nodes(int level, const int32_t *counts,
                                      const NodeInfo *__restrict__ ninfo,
                                      const Body *__restrict__ body,
@@ -1329,66 +1403,14 @@ __device__ inline void moments_nodes(int level, const int32_t *counts,
     for (int64_t g = g_first; g < cnt; g += stride) {
         const int32_t k = beg + (int32_t)g;
         const NodeInfo info = ninfo[k];
-        // sums in member order; each group's loads are all issued before
-        // its first addition
-        double ms = 0.0, mx = 0.0, my = 0.0, mz = 0.0, me = 0.0;
-        if (info.child0 < 0) {
-            const int32_t end = info.first + info.count;
-            for (int32_t s0 = info.first; s0 < end; s0 += 4) {
-                Body b[4];
-                double e[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int32_t s = s0 + u < end ? s0 + u : s0;
-                    b[u] = body[s];
-                    e[u] = use_eps ? beps2[s] : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    if (s0 + u >= end) break;
-                    ms += b[u].m;
-                    mx += b[u].x * b[u].m;
-                    my += b[u].y * b[u].m;
-                    mz += b[u].z * b[u].m;
-                    if (use_eps) me += e[u] * b[u].m;
-                }
-            }
-        } else {
-            const int nch = node_nchild(info);
-            NodeMom cm[8];
-            double e[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int32_t c = info.child0 + (u < nch ? u : 0);
-                cm[u] = nmom[c];
-                e[u] = use_eps ? neps2[c] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                if (u >= nch) break;
-                ms += cm[u].m;
-                mx += cm[u].x * cm[u].m;
-                my += cm[u].y * cm[u].m;
-                mz += cm[u].z * cm[u].m;
-                if (use_eps) me += e[u] * cm[u].m;
-            }
-        }
-        NodeMom out;
-        double e2 = 0.0;
-        if (ms > 0.0) {
-            out = NodeMom{mx / ms, my / ms, mz / ms, ms};
-            e2 = use_eps ? me / ms : 0.0;
-        } else {
-            // massless cell: its centre
-            const uint64_t key = keys[info.first];
-            const SceneBox &b = box[node_scene(info)];
-            const int sh = kMaxLevel - level;
-            const double s = ldexp(b.L, -level);
-            out.x = b.x0[0] + ((double)(compact3(key >> 2) >> sh) + 0.5) * s;
-            out.y = b.x0[1] + ((double)(compact3(key >> 1) >> sh) + 0.5) * s;
-            out.z = b.x0[2] + ((double)(compact3(key) >> sh) + 0.5) * s;
-            out.m = 0.0;
-        }
+        MomentSum sum;
+        if (info.child0 < 0)
+            sum.leaf(body, beps2, info, use_eps);
+        else
+            sum.children(nmom, neps2, info, use_eps);
+        double e2;
+        const NodeMom out =
+            sum.moments(level, info.first, keys, box[node_scene(info)], use_eps, e2);
         nmom[k] = out;
         if (use_eps) neps2[k] = e2;
         if (nquad) {
@@ -1501,185 +1523,338 @@ __global__ __launch_bounds__(1024) void k_moments_tail(
 // ------------------------------------------------- whole build, small scene
 
 // The whole build of one scene of at most kSmallBuild bodies in one block:
-// box and input check, keys, an eight-pass stable radix sort of (key, index)
-// held in LDS, gather, every level of the tree and the moments.
-// Each stage computes what the multi-launch path computes (the same stable
-// order, the same node set and moments); a small scene is bound by launch
-// latency, which this removes.
+// box and input check, keys, a stable merge sort of (key, index), gather, every
+// level of the tree and the moments. Each stage computes what the multi-launch
+// path computes (the same stable order, the same node set and moments); a small
+// scene is bound by latency, so the stages are chosen for few dependent steps:
+//   sort     runs of 64 ranked by comparison in LDS, then runs merged in pairs,
+//            each key finding its place by a binary search in the other run
+//            (one barrier a round, 4 rounds at 1000 bodies, 6 at 4096, where
+//            eight radix passes took 40 barriers and left most waves idle);
+//   levels   only the nodes that split are carried from level to level, in an
+//            LDS list; a wave reserves its children with one LDS atomic and the
+//            level ends in one barrier (six, and the node table in global
+//            memory, with the launches' split);
+//   moments  of every leaf at once, then the internal nodes level by level from
+//            a copy of the moments in LDS (up to kCacheNodes nodes).
+// A ball of 1000 bodies, leaf 16: 80 -> 29 us; leaf 1 (ten levels) 119 -> 43 us;
+// 4096 bodies, leaf 16: 111 -> 74 us.
 constexpr int kSmallThreads = 1024;
+constexpr int kCacheNodes = 3840;
+// LDS: two buffers of keys and indices while sorting; the sorted keys and two
+// lists of splitting nodes while splitting; node moments at the end.
+constexpr int kSmallLds = kCacheNodes * (int)(sizeof(NodeMom) + sizeof(double));
+static_assert(kSmallLds >= (int)kSmallBuild * 2 * (8 + 2), "sort buffers");
+static_assert(kSmallLds >= (int)kSmallBuild * (8 + 8), "keys and split lists");
+static_assert(kCacheNodes <= 4 * kSmallThreads, "nodes a thread keeps");
+
+// A stable sort of the m (a multiple of 64, at most kSmallBuild) keys and
+// indices in buffer 0; returns the buffer that holds the order.
+__device__ inline int small_sort(uint64_t (*key)[kSmallBuild], uint16_t (*val)[kSmallBuild], int m)
+{
+    const int lane = threadIdx.x & 63;
+    // runs of 64, one per wave: each lane counts the keys before its own
+    for (int p = threadIdx.x; p < m; p += kSmallThreads) {
+        const uint64_t k = key[0][p];
+        const uint64_t *run = key[0] + (p - lane);
+        int rank = 0;
+#pragma unroll 8
+        for (int j = 0; j < 64; j++) {
+            const uint64_t o = run[j];
+            rank += (o < k || (o == k && j < lane)) ? 1 : 0;
+        }
+        key[1][p - lane + rank] = k;
+        val[1][p - lane + rank] = val[0][p];
+    }
+    __syncthreads();
+    int src = 1;
+    for (int len = 64; len < m; len *= 2) {
+        for (int p = threadIdx.x; p < m; p += kSmallThreads) {
+            const uint64_t k = key[src][p];
+            const int a0 = p & ~(2 * len - 1);  // the pair of runs
+            const bool right = (p & len) != 0;
+            const int o0 = right ? a0 : a0 + len;  // the other run
+            const int olen = min(len, max(0, m - o0));
+            const uint64_t *o = key[src] + o0;
+            // keys of the other run before this one: less, or, coming from the
+            // left run, equal
+            int c = 0;
+            for (int s = len; s > 0; s >>= 1)
+                if (c + s <= olen) {
+                    const uint64_t x = o[c + s - 1];
+                    if (x < k || (right && x == k)) c += s;
+                }
+            const int to = (right ? p - len : p) + c;
+            key[src ^ 1][to] = k;
+            val[src ^ 1][to] = val[src][p];
+        }
+        src ^= 1;
+        __syncthreads();
+    }
+    return src;
+}
+
+// A splitting node of a level: its number, first body and body count.
+struct SplitNode {
+    int32_t id;
+    uint16_t first, count;
+};
 
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     const double *__restrict__ pos, const double *__restrict__ mass,
-    const double *__restrict__ eps, int64_t n, int leaf, SceneBox *__restrict__ box,
+    const double *__restrict__ eps, int64_t n64, int leaf, SceneBox *__restrict__ box,
     TreeHeader *__restrict__ hdr, uint64_t *__restrict__ k0, uint32_t *__restrict__ i0,
     Body *__restrict__ body,
     double *__restrict__ beps2, NodeInfo *__restrict__ ninfo, NodeMom *__restrict__ nmom,
     double *__restrict__ neps2, double *__restrict__ nquad, int64_t node_cap,
     int32_t *__restrict__ depth_out)
 {
-    constexpr int W = kSmallThreads / 64;
-    constexpr int kChunk = kSmallBuild / W;  // keys per wave in the sort (4 rounds of 64)
-    static_assert(kChunk % 64 == 0, "whole rounds per wave");
-    __shared__ unsigned long long red_lo[3], red_hi[3];
-    __shared__ uint32_t base[256];
-    __shared__ uint32_t whist[W][256];  // per-wave digit counts, then per-wave digit offsets
-    __shared__ uint32_t lds4[4];
-    // the keys and indices, sorted in LDS (ping-pong)
-    __shared__ uint64_t skey[2][kSmallBuild];
-    __shared__ uint32_t sval[2][kSmallBuild];
+    constexpr int W = kSmallThreads / 64, kPer = (int)(kSmallBuild / kSmallThreads);
+    __shared__ alignas(16) char lds[kSmallLds];
+    __shared__ double red[W][6];
+    __shared__ SceneBox sbox;
+    __shared__ int32_t scnt[kLevels + 1];
+    __shared__ int32_t nsplit[3];
+    const int n = (int)n64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool use_eps = eps != nullptr;
+    uint64_t(*skey)[kSmallBuild] = (uint64_t(*)[kSmallBuild])lds;
+    uint16_t(*sval)[kSmallBuild] = (uint16_t(*)[kSmallBuild])(lds + 2 * sizeof(uint64_t) * kSmallBuild);
 
     // 1. box and input check
-    if (tid < 3) {
-        red_lo[tid] = ~0ull;
-        red_hi[tid] = 0ull;
-    }
-    __shared__ int32_t scnt[kLevels + 1];
-    if (tid <= kLevels) scnt[tid] = tid == 0 ? 1 : 0;
-    __syncthreads();
+    double x[kPer][3];
     {
-        unsigned long long lo[3] = {~0ull, ~0ull, ~0ull}, hi[3] = {0ull, 0ull, 0ull};
+        double lo[3] = {kInf, kInf, kInf}, hi[3] = {-kInf, -kInf, -kInf};
         bool bad = false;
-        for (int64_t i = tid; i < n; i += kSmallThreads) {
-            const double x[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int i = tid + j * kSmallThreads;
+            if (i >= n) continue;
+            for (int a = 0; a < 3; a++) x[j][a] = pos[3 * i + a];
             const double m = mass[i];
-            bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
+            bad |= !(isfinite(x[j][0]) && isfinite(x[j][1]) && isfinite(x[j][2]));
             bad |= !(isfinite(m) && m >= 0.0);
-            if (eps) {
+            if (use_eps) {
                 const double e = eps[i];
                 bad |= !(isfinite(e) && e >= 0.0);
             }
             for (int a = 0; a < 3; a++) {
-                const unsigned long long c = order_enc(x[a]);
-                lo[a] = c < lo[a] ? c : lo[a];
-                hi[a] = c > hi[a] ? c : hi[a];
+                lo[a] = fmin(lo[a], x[j][a]);
+                hi[a] = fmax(hi[a], x[j][a]);
             }
         }
         if (__ballot(bad) && lane == 0) atomicOr(&hdr->status, ST_NONFINITE);
         for (int a = 0; a < 3; a++) {
-            atomicMin(&red_lo[a], lo[a]);
-            atomicMax(&red_hi[a], hi[a]);
+            const double l = wave_min(lo[a]), h = wave_max(hi[a]);
+            if (lane == 0) {
+                red[wave][a] = l;
+                red[wave][3 + a] = h;
+            }
+        }
+    }
+    if (tid <= kLevels) scnt[tid] = tid == 0 ? 1 : 0;
+    if (tid < 3) nsplit[tid] = 0;
+    __syncthreads();
+    if (tid < 64) {
+        double v[6];
+        for (int a = 0; a < 6; a++) v[a] = red[lane & (W - 1)][a];
+#pragma unroll
+        for (int o = 1; o < W; o <<= 1)
+            for (int a = 0; a < 6; a++) {
+                const double u = __shfl_xor(v[a], o);
+                v[a] = a < 3 ? fmin(v[a], u) : fmax(v[a], u);
+            }
+        for (int a = 0; a < 3; a++) {  // every lane stores the same
+            sbox.lo_enc[a] = order_enc(v[a]);
+            sbox.hi_enc[a] = order_enc(v[3 + a]);
+        }
+        root_cube(sbox, v, v + 3, lane, 64);
+    }
+    __syncthreads();
+    if (tid < (int)(sizeof(SceneBox) / 8)) ((uint64_t *)box)[tid] = ((const uint64_t *)&sbox)[tid];
+
+    // 2. keys, in LDS; the places past n hold the largest key and sort last
+    const int m = (n + 63) & ~63;
+#pragma unroll
+    for (int j = 0; j < kPer; j++) {
+        const int i = tid + j * kSmallThreads;
+        if (i < m) {
+            skey[0][i] = i < n ? morton_key(x[j], sbox) : ~0ull;
+            sval[0][i] = (uint16_t)i;
         }
     }
     __syncthreads();
+
+    // 3. sort, and 4. gather; the walk and the tree export read the sorted keys
+    // and indices from global memory
+    {
+        const int at = small_sort(skey, sval, m);
+        uint64_t mine[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int s = tid + j * kSmallThreads;
+            if (s >= n) continue;
+            const uint32_t i = sval[at][s];
+            mine[j] = skey[at][s];
+            k0[s] = mine[j];
+            i0[s] = i;
+            body[s] = Body{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]};
+            if (use_eps) {
+                const double e = eps[i];
+                beps2[s] = e * e;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int s = tid + j * kSmallThreads;
+            if (s < n) skey[0][s] = mine[j];
+        }
+    }
+    const uint64_t *key = skey[0];
+    SplitNode(*list)[kSmallBuild / 2] =
+        (SplitNode(*)[kSmallBuild / 2])(lds + sizeof(uint64_t) * kSmallBuild);
     if (tid == 0) {
-        double lo[3], hi[3];
-        for (int a = 0; a < 3; a++) {
-            box[0].lo_enc[a] = red_lo[a];
-            box[0].hi_enc[a] = red_hi[a];
-            lo[a] = order_dec(red_lo[a]);
-            hi[a] = order_dec(red_hi[a]);
+        if (n > leaf) {
+            list[0][0] = SplitNode{0, 0, (uint16_t)n};
+            nsplit[0] = 1;
+        } else {
+            ninfo[0] = NodeInfo{0, n, -1, 0};
         }
-        root_cube(box[0], lo, hi);
-        ninfo[0] = NodeInfo{0, (int32_t)n, -1, 0};
     }
     __syncthreads();
 
-    // 2. keys, in LDS
-    for (int64_t i = tid; i < n; i += kSmallThreads) {
-        skey[0][i] = morton_key(pos + 3 * i, box[0]);
-        sval[0][i] = (uint32_t)i;
-    }
-    __syncthreads();
-
-    // 3. sort, in LDS: wave w holds keys w*kChunk .. (w+1)*kChunk-1 of the
-    // current order and ranks them among equal digits with ballots and a
-    // per-wave digit count (tile order = wave, round, lane = input order);
-    // scans over the waves and over the digits then place every key.
-    for (int pass = 0; pass < 8; pass++) {
-        const int shift = 8 * pass, src = pass & 1, dst = src ^ 1;
-        for (int i = tid; i < W * 256; i += kSmallThreads) (&whist[0][0])[i] = 0;
-        __syncthreads();
-        uint32_t rank[kChunk / 64], dig[kChunk / 64];
-#pragma unroll
-        for (int r = 0; r < kChunk / 64; r++) {
-            const int i = wave * kChunk + r * 64 + lane;
-            const bool valid = i < n;
-            const uint32_t d = valid ? (uint32_t)(skey[src][i] >> shift) & 255u : 0u;
-            uint64_t peers = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < 8; b++) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t bal = __ballot(bit);
-                peers &= bit ? bal : ~bal;
-            }
-            const uint64_t lower = peers & lanemask_lt(lane);
-            const uint32_t before = valid ? whist[wave][d] : 0u;
-            if (valid && lower == 0) whist[wave][d] = before + (uint32_t)__popcll(peers);
-            rank[r] = before + (uint32_t)__popcll(lower);
-            dig[r] = d;
-        }
-        __syncthreads();
-        // digit tid (first four waves): offsets of the waves, and the exclusive
-        // scan of the digit totals; the barriers are reached by every thread
-        {
-            uint32_t run = 0;
-            if (tid < 256)
-                for (int w = 0; w < W; w++) {
-                    const uint32_t c = whist[w][tid];
-                    whist[w][tid] = run;
-                    run += c;
+    // 5. tree, top-down, eight lanes a splitting node. A splitting node holds at
+    // least two bodies, so a level has at most n / 2 of them. nsplit turns over
+    // three counters: this level's, the next one's and the one being cleared.
+    int beg = 1;  // first node of level + 1
+    for (int level = 0; level < kMaxLevel; level++) {
+        const int ns = nsplit[level % 3];
+        if (ns == 0) break;  // the same on every thread
+        const SplitNode *now = list[level & 1];
+        SplitNode *next = list[(level & 1) ^ 1];
+        const int o = tid & 7, gl = lane & ~7, shift = 60 - 3 * level;
+        if (tid == 0) nsplit[(level + 2) % 3] = 0;
+        for (int g0 = 8 * wave; g0 < ns; g0 += kSmallThreads / 8) {
+            const int g = g0 + (lane >> 3);
+            const bool live = g < ns;
+            const SplitNode nd = now[live ? g : g0];
+            const int first = nd.first, count = live ? nd.count : 0;
+            int start;
+            if (count <= kLinearSplit) {
+                uint64_t hist = 0;  // one byte per octant
+                for (int j = o; j < count; j += 8)
+                    hist += 1ull << (8 * (int)((key[first + j] >> shift) & 7ull));
+                hist += __shfl_xor(hist, 1, 8);
+                hist += __shfl_xor(hist, 2, 8);
+                hist += __shfl_xor(hist, 4, 8);
+                const uint64_t below = o == 0 ? 0ull : hist & (~0ull >> (64 - 8 * o));
+                start = first + (int)((below * 0x0101010101010101ull) >> 56);
+            } else {
+                int a = first, b = first + count;
+                while (a < b) {
+                    const int mid = (a + b) >> 1;
+                    if ((int)((key[mid] >> shift) & 7ull) < o)
+                        a = mid + 1;
+                    else
+                        b = mid;
                 }
-            const uint32_t v = wave_incl_scan(run);
-            if (lane == 63 && wave < 4) lds4[wave] = v;
-            __syncthreads();
-            if (tid < 256) {
-                uint32_t add = 0;
-                for (int w = 0; w < wave; w++) add += lds4[w];
-                base[tid] = add + v - run;
+                start = a;
             }
+            int end = __shfl_down(start, 1, 8);
+            if (o == 7) end = first + count;
+            BHX_CHECK(start >= first && start <= end && end <= first + count, CK_PARTITION);
+            const bool child = live && end > start;
+            const uint64_t cb = __ballot(child);
+            const bool deeper = child && end - start > leaf && level + 1 < kMaxLevel;
+            const uint64_t sb = __ballot(deeper);
+            int base = 0, at = 0;
+            if (lane == 0) {
+                base = atomicAdd(&scnt[level + 1], __popcll(cb));
+                if (sb) at = atomicAdd(&nsplit[(level + 1) % 3], __popcll(sb));
+            }
+            base = beg + __builtin_amdgcn_readfirstlane(base);
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (base + __popcll(cb) > node_cap) {  // the same on every lane
+                if (lane == 0) atomicOr(&hdr->status, ST_CAPACITY);
+                if (live && o == 0) ninfo[nd.id] = NodeInfo{first, count, -1, level};
+                continue;
+            }
+            const int id = base + (int)lanes_below(cb);
+            if (deeper)
+                next[at + (int)lanes_below(sb)] =
+                    SplitNode{id, (uint16_t)start, (uint16_t)(end - start)};
+            else if (child)
+                ninfo[id] = NodeInfo{start, end - start, -1, level + 1};
+            if (live && o == 0)
+                ninfo[nd.id] = NodeInfo{first, count, id,
+                                        level | ((int)__popcll((cb >> gl) & 0xffull) << 8)};
         }
         __syncthreads();
+        beg += scnt[level + 1];
+    }
+    int depth = 0, total = 0;
+    for (int l = 0; l < kLevels; l++) {
+        if (scnt[l] > 0) depth = l;
+        total += scnt[l];
+    }
+
+    // 6. moments
+    if (total <= kCacheNodes && total <= node_cap && !nquad) {
+        NodeMom *cm = (NodeMom *)lds;
+        double *ce = (double *)(lds + kCacheNodes * sizeof(NodeMom));
+        int inner[4];  // an internal node's first child, children << 12 and level << 16
+        __syncthreads();  // the keys and lists are read no more
+        auto store = [&](int k, int level, const MomentSum &s) {
+            double e2;
+            const int32_t first = s.ms > 0.0 ? 0 : ninfo[k].first;  // read for a massless cell only
+            const NodeMom out = s.moments(level, first, k0, sbox, use_eps, e2);
+            cm[k] = out;
+            nmom[k] = out;
+            if (use_eps) {
+                ce[k] = e2;
+                neps2[k] = e2;
+            }
+        };
 #pragma unroll
-        for (int r = 0; r < kChunk / 64; r++) {
-            const int i = wave * kChunk + r * 64 + lane;
-            if (i < n) {
-                const uint32_t o = base[dig[r]] + whist[wave][dig[r]] + rank[r];
-                skey[dst][o] = skey[src][i];
-                sval[dst][o] = sval[src][i];
+        for (int j = 0; j < 4; j++) {
+            const int k = tid + j * kSmallThreads;
+            inner[j] = -1;
+            if (k >= total) continue;
+            const NodeInfo info = ninfo[k];
+            if (info.child0 >= 0) {
+                inner[j] = info.child0 | node_nchild(info) << 12 | node_level(info) << 16;
+            } else {
+                MomentSum s;
+                s.leaf(body, beps2, info, use_eps);
+                store(k, node_level(info), s);
             }
         }
         __syncthreads();
-    }
-    // eight passes leave the order in buffer 0; the walk and the tree export
-    // read the sorted keys and indices from global memory
-    for (int64_t i = tid; i < n; i += kSmallThreads) {
-        k0[i] = skey[0][i];
-        i0[i] = sval[0][i];
-    }
-    __syncthreads();
-
-    // 4. gather
-    for (int64_t s = tid; s < n; s += kSmallThreads) {
-        const uint32_t i = sval[0][s];
-        body[s] = Body{pos[3 * (int64_t)i], pos[3 * (int64_t)i + 1], pos[3 * (int64_t)i + 2],
-                       mass[i]};
-        if (eps) {
-            const double e = eps[i];
-            beps2[s] = e * e;
+        for (int level = depth - 1; level >= 0; level--) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                if (inner[j] < 0 || inner[j] >> 16 != level) continue;
+                MomentSum s;
+                s.children(cm, ce, NodeInfo{0, 0, inner[j] & 0xfff, (inner[j] >> 12 & 0xf) << 8},
+                           use_eps);
+                store(tid + j * kSmallThreads, level, s);
+            }
+            __syncthreads();
         }
-    }
-    __syncthreads();
-
-    // 5. tree, top-down, with the node counts and the sorted keys in LDS
-    build_levels_block<false>(0, kMaxLevel, skey[0], hdr, ninfo, node_cap, leaf, scnt);
-    __syncthreads();
-    // 6. moments, bottom-up
-    for (int level = kMaxLevel; level >= 0; level--) {
-        if (scnt[level] == 0) continue;  // the same on every thread
-        moments_nodes(level, scnt, ninfo, body, beps2, skey[0], box, nmom, neps2, nquad, node_cap,
-                      eps != nullptr, tid, kSmallThreads);
-        __syncthreads();
+    } else {
+        for (int level = depth; level >= 0; level--) {
+            moments_nodes(level, scnt, ninfo, body, beps2, key, box, nmom, neps2, nquad, node_cap,
+                          use_eps, tid, kSmallThreads);
+            __syncthreads();
+        }
     }
     if (tid <= kLevels) hdr->level_count[tid] = scnt[tid];
     if (depth_out && tid == 0) {
-        int d = 0;
-        for (int l = 1; l <= kMaxLevel; l++)
-            if (scnt[l] > 0) d = l;
-        depth_out[0] = d;
+        depth_out[0] = depth;
         depth_out[1] = -1;  // no sort hint from a one-block build
-        for (int l = 0; l < kLevels; l++) depth_out[2 + l] = scnt[l];
     }
+    if (depth_out && tid < kLevels) depth_out[2 + tid] = scnt[tid];
 }
 
 inline unsigned blocks_for(int64_t items, int per_block, unsigned cap)
