@@ -14,9 +14,9 @@
 // Tree VJP, on the GPU:
 //   1. the same build as the forward evaluation (deterministic, so the same
 //      tree and decisions);
-//   2. a walk with the forward walk's traversal and decisions (one wave per
-//      64 Morton-consecutive targets, per-lane masks, batched rounds, staged
-//      items split into dense items and pairs); each target's terms are
+//   2. a walk with the forward walk's traversal and decisions (one block per
+//      group of Morton-consecutive targets, one wave traversing and the others
+//      evaluating, staged items split into dense items and pairs); each target's terms are
 //      summed in registers and LDS, each source's terms are summed over the
 //      group and added with FP64 atomics into the body or node adjoints;
 //   3. node adjoints become per-node coefficients (A = gX / m_N,
@@ -33,12 +33,9 @@
 namespace bhx {
 namespace {
 
-using walkx::kPop;
-using walkx::PopCom;
-using walkx::PopData;
+using walkx::kBatch;
+using walkx::kEvals;
 constexpr int kStack = 320;
-constexpr int kRing = 128;
-constexpr int kBatch = 64;
 
 struct alignas(16) ItemV {  // staged source
     double x, y, z, m;
@@ -69,6 +66,15 @@ __device__ inline float dpp(float v)
 
 constexpr int kPairCap = 448;  // pairs per batch
 
+// What one evaluating wave works in.
+template <int GB>
+struct EvalLds {
+    ItemV items[kBatch];        // dense items first, then the sparse ones
+    double sacc[5 * kBatch];    // pair source-side sums per staged item
+    double tacc[3 * GB];        // pair target-side sums per body; at the end the wave's sums
+    uint16_t rec[kPairCap];     // pair: item slot << 6 | body
+};
+
 // badj: per sorted body {gX x, y, z, gm}; nadj: per node {gX x, y, z, gm, ge2}.
 //
 // The traversal and the opening decisions are those of the forward walk. A
@@ -83,7 +89,7 @@ constexpr int kPairCap = 448;  // pairs per batch
 // target-side terms go to per-body and whose source-side terms go to per-item
 // FP64 sums in LDS, flushed to the adjoints once per batch.
 template <bool PEPS, int GB, bool F32>
-__global__ __launch_bounds__(64) void k_vjp_walk(
+__global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const NodeInfo *__restrict__ ninfo, const NodeMom *__restrict__ nmom,
     const double *__restrict__ neps2, const uint32_t *__restrict__ idx,
@@ -99,40 +105,39 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
     // FP32C: every term in FP32 from the FP64 offset rounded once, the terms
     // of a step summed in FP32 and added into FP64 sums and adjoints
     using VT = typename std::conditional<F32, float, double>::type;
-    __shared__ walkx::Lds<kStack, kRing> L;
-    int32_t *const dq_a = L.dq_a;
-    int32_t *const dq_n = L.dq_n;
-    uint32_t *const dq_at = L.dq_at;
-    uint64_t *const dq_mask = L.dq_mask;
-    union Shared {
-        struct {
-            PopCom pc[kPop];
-            PopData pd[kPop];
-        } pop;
-        struct {
-            ItemV items[kBatch];     // dense items first, then the sparse ones
-            uint16_t rec[kPairCap];  // pair: item slot << 6 | body
-        } ev;
-    };
-    __shared__ Shared sh;
-    __shared__ double tacc[3 * GB];      // pair target-side sums per body
-    __shared__ double sacc[5 * kBatch];  // pair source-side sums per staged item
-    PopCom *const pc = sh.pop.pc;
-    PopData *const pd = sh.pop.pd;
-    ItemV *const items = sh.ev.items;
-    uint16_t *const rec = sh.ev.rec;
+    __shared__ walkx::Lds<kStack> L;
+    __shared__ EvalLds<GB> eval_lds[kEvals];
 
     const int grp = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
     if (grp >= ngroups) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int bq = GB == 64 ? lane : lane % GB;  // body of this lane within the group
     const int sub = GB == 64 ? 0 : lane / GB;    // which share of the items it takes
     const int64_t g0 = (int64_t)grp * GB;
     const int64_t s = g0 + bq;
     const bool valid = s < n;
     const Body me = body[valid ? s : g0];
+
+    if (threadIdx.x == 0) L.published = 0;
+    if (threadIdx.x < kEvals) L.head[threadIdx.x] = 0;
+    __syncthreads();
+
+    if (wave == 0) {
+        double glo[3], ghi[3];  // the group's bounding box
+        walkx::group_box<GB>(valid, me.x, me.y, me.z, glo, ghi);
+        const uint64_t active = __ballot(valid) & kBodyMask;
+        walkx::traverse<GB>(L, 0, active, ninfo, nmom, walkx::SideSq(box[0]), glo, ghi, me.x, me.y,
+                            me.z, th2);
+    } else {
+    EvalLds<GB> &sh = eval_lds[wave - 1];
+    ItemV *const items = sh.items;
+    uint16_t *const rec = sh.rec;
+    double *const tacc = sh.tacc;
+    double *const sacc = sh.sacc;
     const double eb2 = PEPS ? beps2[valid ? s : g0] : 0.0;
     const float ebhf = (float)(0.5 * eb2);  // FP32C: half the target's squared softening
+    const CubeConsts cc = cube_consts();
     double lx = 0.0, ly = 0.0, lz = 0.0;
     if (valid) {
         const int64_t o = idx[s];
@@ -140,25 +145,13 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
         ly = lambda[3 * o + 1];
         lz = lambda[3 * o + 2];
     }
-    const uint64_t active = __ballot(valid) & kBodyMask;
-    if (lane < kLevels) L.s2tab[lane] = box[0].s2[lane];
-    double glo[3], ghi[3];  // the group's bounding box
-    walkx::group_box<GB>(valid, me.x, me.y, me.z, glo, ghi);
     // This lane's order of its share's eight items of a dense step: slot bits
     // 2 and 1 follow lane bits 0 and 1, slot bit 0 lane bit 5 (GB = 64) or 3.
     const int perm = ((lane & 1) << 2) | (lane & 2) | (GB == 64 ? lane >> 5 : (lane >> 3) & 1);
 
     double gx = 0.0, gy = 0.0, gz = 0.0;  // target-side gradient of this lane's body
     const VT lxv = (VT)lx, lyv = (VT)ly, lzv = (VT)lz;
-    int sp = 1, dq_head = 0, dq_tail = 0;
-    uint32_t queued = 0, consumed = 0;
-    if (lane == 0) {
-        L.st_c0[0] = 0;
-        L.st_n[0] = 1;
-        L.st_mask[0] = active;
-    }
     for (int i = lane; i < 3 * GB; i += 64) tacc[i] = 0.0;
-    __syncthreads();
 
     // One softened term of source (x, y, z, m, e2) on a target at (bx, by, bz)
     // with softening eb and upstream (ux, uy, uz): the target-side gradient is
@@ -190,19 +183,19 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
         } else {
             const double dx = it.x - bx, dy = it.y - by, dz = it.z - bz;
             const double e2 = PEPS ? 0.5 * (eb + it.e2) : eps0sq;
-            const double r2 = dx * dx + dy * dy + dz * dz + e2;
-            if (on && positive_normal(r2)) {
-                const double rinv = rsqrt_f64(r2), inv2 = rinv * rinv;
-                const double inv3 = inv2 * rinv;
-                const double inv5 = inv3 * inv2;
-                const double ld = ux * dx + uy * dy + uz * dz;
-                const double gms = G * it.m;
-                out[0] = gms * (ux * inv3 - 3.0 * dx * ld * inv5);
-                out[1] = gms * (uy * inv3 - 3.0 * dy * ld * inv5);
-                out[2] = gms * (uz * inv3 - 3.0 * dz * ld * inv5);
-                out[3] = G * ld * inv3;
-                out[4] = -1.5 * gms * ld * inv5;
-            }
+            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
+            const bool live = on && positive_normal(r2);
+            const double ld = ux * dx + uy * dy + uz * dz;
+            double i2;
+            double i3 = inv_cube_sq_f64(r2, i2, cc);
+            i3 = live ? i3 : 0.0;
+            const double li = live ? ld * i2 : 0.0;
+            const double g3 = G * it.m * i3, k3 = 3.0 * li;
+            out[0] = g3 * fma(-k3, dx, ux);
+            out[1] = g3 * fma(-k3, dy, uy);
+            out[2] = g3 * fma(-k3, dz, uz);
+            out[3] = G * ld * i3;
+            out[4] = -1.5 * g3 * li;
         }
     };
     // adds a source-side sum to the item's adjoints (e2 = (eps_B^2 + <eps^2>_N) / 2)
@@ -223,33 +216,14 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
         }
     };
 
-    auto evaluate = [&](int c) {
-        uint64_t mk = 0;
+    auto evaluate = [&](walkx::Batch &bt) {
+        const int c = bt.count;
+        uint64_t mk;
+        int32_t src;
+        walkx::take_batch(L, wave - 1, bt, src, mk);
         ItemV ld_it{0.0, 0.0, 0.0, 0.0, 0.0, 0ull, 0, 0.f, 0.f, 0};
-        // The descriptor of item consumed + lane: each descriptor that starts
-        // inside the batch flags its first item (only the head descriptor can
-        // start at item 0, and it may also start before the batch), so item
-        // L belongs to the head plus as many descriptors as start in 1..L.
-        // The flags use the pair list's space, free until the items are split.
-        uint16_t *const flag = rec;
-        flag[lane] = 0;
-#pragma unroll
-        for (int h = 0; h < kRing; h += 64) {
-            if (h + lane < dq_tail - dq_head) {
-                const uint32_t rel = dq_at[(dq_head + h + lane) & (kRing - 1)] - consumed;
-                if (rel < (uint32_t)c) flag[rel] = 1;
-            }
-        }
-        __syncthreads();
-        const uint64_t starts = __ballot(flag[lane] != 0) & ~1ull;
-        const int dsel = (int)lanes_below(starts) + (int)((starts >> lane) & 1ull);
         if (lane < c) {
-            const uint32_t q = consumed + (uint32_t)lane;
-            const int d = (dq_head + dsel) & (kRing - 1);
-            const int32_t a = dq_a[d];
-            mk = dq_mask[d];
-            if (a >= 0) {
-                int32_t src = a + (int32_t)(q - dq_at[d]);
+            if (src >= 0) {
                 if (!check_ok(src < n, CK_INDEX)) src = 0;
                 const int64_t rel = (int64_t)src - g0;
                 if (rel >= 0 && rel < GB) mk &= ~(1ull << rel);
@@ -258,9 +232,9 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
                 ld_it = ItemV{b.x,  b.y, b.z, b.m, e2, mk, src, (float)(G * b.m),
                               (float)(0.5 * e2), 0};
             } else {
-                const NodeMom nm = nmom[~a];
-                const double e2 = PEPS ? neps2[~a] : 0.0;
-                ld_it = ItemV{nm.x, nm.y, nm.z, nm.m, e2, mk, a, (float)(G * nm.m),
+                const NodeMom nm = nmom[~src];
+                const double e2 = PEPS ? neps2[~src] : 0.0;
+                ld_it = ItemV{nm.x, nm.y, nm.z, nm.m, e2, mk, src, (float)(G * nm.m),
                               (float)(0.5 * e2), 0};
             }
         }
@@ -290,7 +264,7 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
                 }
             }
         }
-        __syncthreads();
+        walkx::wave_sync();
 
         // dense items, eight per share of lanes per step
 #pragma unroll 1
@@ -381,7 +355,7 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
-        __syncthreads();
+        walkx::wave_sync();
         if (lane < ns) {
             const int k = nd + lane;
             double o[5];
@@ -389,29 +363,12 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
             for (int q = 0; q < 5; q++) o[q] = sacc[5 * k + q];
             flush(items[k].src, o);
         }
-
-        consumed += (uint32_t)c;
-        // retire the fully evaluated descriptors: they form a prefix of the
-        // queue, and one batch completes at most 64 of them
-        {
-            const int da = dq_head + lane;
-            bool done = false;
-            if (da < dq_tail) {
-                const int d = da & (kRing - 1);
-                done = dq_at[d] + (uint32_t)dq_n[d] <= consumed;
-            }
-            dq_head += __popcll(__ballot(done));
-        }
-        __syncthreads();
+        walkx::wave_sync();
     };
 
-    while (sp > 0) {
-        walkx::traverse_round<GB>(L, pc, pd, sp, dq_tail, queued, ninfo, nmom, glo, ghi, me.x, me.y,
-                                  me.z, th2);
-        BHX_CHECK(dq_tail - dq_head <= kRing, CK_RING);
-        while (queued - consumed >= (uint32_t)kBatch) evaluate(kBatch);
-    }
-    while (queued != consumed) evaluate((int)min(queued - consumed, (uint32_t)kBatch));
+    walkx::Batch bt;
+    bt.start = (uint32_t)(kBatch * (wave - 1));
+    while (walkx::next_batch(L, wave - 1, bt)) evaluate(bt);
 
     // the lanes' shares of each body, in a fixed order, then its pair sums
 #pragma unroll
@@ -420,10 +377,19 @@ __global__ __launch_bounds__(64) void k_vjp_walk(
         gy += __shfl_xor(gy, o);
         gz += __shfl_xor(gz, o);
     }
-    if (valid && sub == 0) {
-        gt[3 * s] = gx + tacc[3 * bq];
-        gt[3 * s + 1] = gy + tacc[3 * bq + 1];
-        gt[3 * s + 2] = gz + tacc[3 * bq + 2];
+    if (sub == 0) {
+        tacc[3 * bq] += gx;
+        tacc[3 * bq + 1] += gy;
+        tacc[3 * bq + 2] += gz;
+    }
+    }
+    __syncthreads();
+    // the waves' sums in wave order
+    if (wave != 1 || !valid || sub != 0) return;
+    for (int a = 0; a < 3; a++) {
+        double v = 0.0;
+        for (int e = 0; e < kEvals; e++) v += eval_lds[e].tacc[3 * bq + a];
+        gt[3 * s + a] = v;
     }
 }
 
@@ -738,12 +704,12 @@ hipError_t launch_tree_vjp(const Workspace &w, const AdjointWork &aw, hipStream_
     auto walk = [&](auto peps, auto gbc) {
         if (p.precision == BH_FP32C)
             k_vjp_walk<decltype(peps)::value, decltype(gbc)::value, true>
-                <<<8 * per_xcd, 64, 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
+                <<<8 * per_xcd, 64 * (1 + kEvals), 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
                                             w.box, p.n, ngroups, per_xcd, p.th2, p.eps0sq, p.G,
                                             lambda, aw.gt, aw.badj, aw.nadj);
         else
             k_vjp_walk<decltype(peps)::value, decltype(gbc)::value, false>
-                <<<8 * per_xcd, 64, 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
+                <<<8 * per_xcd, 64 * (1 + kEvals), 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
                                             w.box, p.n, ngroups, per_xcd, p.th2, p.eps0sq, p.G,
                                             lambda, aw.gt, aw.badj, aw.nadj);
     };
