@@ -75,7 +75,8 @@ struct EvalLds {
     uint16_t rec[kPairCap];     // pair: item slot << 6 | body
 };
 
-// badj: per sorted body {gX x, y, z, gm}; nadj: per node {gX x, y, z, gm, ge2}.
+// badj: per sorted body {gX x, y, z, gm}; nadj: per node the same; nadj_e: per
+// node ge2.
 //
 // The traversal and the opening decisions are those of the forward walk. A
 // staged batch is split like the forward walk's: a dense item (reaching
@@ -84,10 +85,14 @@ struct EvalLds {
 // its lane bits so that three halving exchanges (lane ^ 1, ^ 2, ^ 32) leave
 // lane L with one item's source-side terms summed over eight lanes, and three
 // more (rotations by 4 and 8 inside a row, lane ^ 16) complete the sum over
-// the group; then eight lanes add the eight sums to the item's adjoints with
-// FP64 atomics. A sparse item becomes (item, body) pairs, one per lane, whose
-// target-side terms go to per-body and whose source-side terms go to per-item
-// FP64 sums in LDS, flushed to the adjoints once per batch.
+// the group. Then one lane permute puts the four components of each item on
+// four neighbouring lanes, and one FP64 atomic per lane adds them to the item's
+// adjoints, which lie together: a request for each item instead of one for each
+// component (the atomics bound this kernel: with a component per instruction and
+// eight lanes active, 40,000 bodies took 458 us, now 215). A sparse item
+// becomes (item, body) pairs, one per lane, whose target-side terms go to
+// per-body and whose source-side terms go to per-item FP64 sums in LDS, flushed
+// to the adjoints once per batch, four lanes an item.
 template <bool PEPS, int GB, bool F32>
 __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
     const Body *__restrict__ body, const double *__restrict__ beps2,
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
     const double *__restrict__ neps2, const uint32_t *__restrict__ idx,
     const SceneBox *__restrict__ box, int64_t n, int ngroups, int per_xcd, double th2,
     double eps0sq, double G, const double *__restrict__ lambda, double *__restrict__ gt,
-    double *__restrict__ badj, double *__restrict__ nadj)
+    double *__restrict__ badj, double *__restrict__ nadj, double *__restrict__ nadj_e)
 {
     static_assert(GB == 64 || GB == 32 || GB == 16, "group size");
     constexpr int NC = PEPS ? 5 : 4;  // source-side components: gX (3), gm, g<eps^2>
@@ -198,23 +203,26 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
             out[4] = -1.5 * g3 * li;
         }
     };
-    // adds a source-side sum to the item's adjoints (e2 = (eps_B^2 + <eps^2>_N) / 2)
-    auto flush = [&](int32_t src, const double v[5]) {
-        if (src >= 0) {
-            double *b = badj + 4 * (int64_t)src;
-            unsafeAtomicAdd(b, v[0]);
-            unsafeAtomicAdd(b + 1, v[1]);
-            unsafeAtomicAdd(b + 2, v[2]);
-            unsafeAtomicAdd(b + 3, v[3]);
-        } else {
-            double *b = nadj + 5 * (int64_t)(~src);
-            unsafeAtomicAdd(b, v[0]);
-            unsafeAtomicAdd(b + 1, v[1]);
-            unsafeAtomicAdd(b + 2, v[2]);
-            unsafeAtomicAdd(b + 3, v[3]);
-            if (PEPS) unsafeAtomicAdd(b + 4, 0.5 * v[4]);
-        }
+    // where component q (0..3) of an item's source-side sum is added, and its
+    // fifth, of a node (e2 = (eps_B^2 + <eps^2>_N) / 2)
+    auto adj = [&](int32_t src, int q) {
+        return src >= 0 ? badj + 4 * (int64_t)src + q : nadj + 4 * (int64_t)(~src) + q;
     };
+    auto add_e2 = [&](int32_t src, double v) {
+        if (src < 0) unsafeAtomicAdd(nadj_e + ~src, 0.5 * v);
+    };
+    // After the exchanges of a dense step the lanes that agree in the bits of
+    // `perm` and `sub` hold the same item's sums. Lane t of the flush adds
+    // component t & 3 of the step's item t / 4 (16 items a flush for GB = 16 and
+    // 32, all 8 for GB = 64): it reads them from the lane that holds that item
+    // and has the component in the remaining lane bits.
+    constexpr int kFlushes = GB == 16 ? 2 : 1, kFlushItems = GB == 64 ? 8 : 16;
+    const int fq = lane & 3, fi = lane >> 2;
+    int from = ((fi >> 2) & 1) | (fi & 2);  // the lane bits of the item's place in its share
+    from |= GB == 64 ? (fi & 1) << 5 : (fi & 1) << 3;
+    if (GB == 64) from |= fq << 2;                                    // component: bits 2, 3
+    if (GB == 32) from |= (fq & 1) << 2 | (fq >> 1) << 4 | (fi >> 3) << 5;  // bits 2, 4
+    if (GB == 16) from |= (fq & 1) << 2 | (fi >> 3) << 4;             // bit 2 (and two values)
 
     auto evaluate = [&](walkx::Batch &bt) {
         const int c = bt.count;
@@ -318,15 +326,29 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
                 }
                 v[0][q] = w;
             }
-            // each share's sums of items j0 + 8 sub + perm sit in its lanes with
-            // lane bits 2 and 3, 4 (GB = 64) or 2 (and 4 for GB = 32) clear
-            const int j = j0 + 8 * sub + perm;
-            const bool lead = GB == 64 ? (lane & 28) == 0 : GB == 32 ? (lane & 20) == 0 : (lane & 4) == 0;
-            if (lead && j < nd) {
-                double o[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            if constexpr (GB == 16) {
+                // two of the four components per source lane, picked by the reader
+                const VT va = (lane & 4) ? v[0][1] : v[0][0], vb = (lane & 4) ? v[0][3] : v[0][2];
 #pragma unroll
-                for (int q = 0; q < NC; q++) o[q] = (double)v[0][q];
-                flush(items[j].src, o);
+                for (int f = 0; f < kFlushes; f++) {
+                    const VT wa = __shfl(va, from | f << 5), wb = __shfl(vb, from | f << 5);
+                    const int j = j0 + kFlushItems * f + fi;
+                    if (j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)(fq >> 1 ? wb : wa));
+                }
+            } else {
+                const int c = GB == 64 ? (lane >> 2) & 3 : ((lane >> 2) & 1) | ((lane >> 4) & 1) << 1;
+                const VT lo = c & 1 ? v[0][1] : v[0][0], hi = c & 1 ? v[0][3] : v[0][2];
+                const VT w = __shfl(c >> 1 ? hi : lo, from);
+                const int j = j0 + fi;
+                if (fi < kFlushItems && j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)w);
+            }
+            if constexpr (PEPS) {
+                // each share's sums of items j0 + 8 sub + perm sit in its lanes with
+                // lane bits 2 and 3, 4 (GB = 64) or 2 (and 4 for GB = 32) clear
+                const int j = j0 + 8 * sub + perm;
+                const bool lead =
+                    GB == 64 ? (lane & 28) == 0 : GB == 32 ? (lane & 20) == 0 : (lane & 4) == 0;
+                if (lead && j < nd) add_e2(items[j].src, (double)v[0][4]);
             }
         }
 
@@ -356,13 +378,11 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
             }
         }
         walkx::wave_sync();
-        if (lane < ns) {
-            const int k = nd + lane;
-            double o[5];
-#pragma unroll
-            for (int q = 0; q < 5; q++) o[q] = sacc[5 * k + q];
-            flush(items[k].src, o);
+        for (int i = lane; i < 4 * ns; i += 64) {
+            const int k = nd + (i >> 2);
+            unsafeAtomicAdd(adj(items[k].src, i & 3), sacc[5 * k + (i & 3)]);
         }
+        if (PEPS && lane < ns) add_e2(items[nd + lane].src, sacc[5 * (nd + lane) + 4]);
         walkx::wave_sync();
     };
 
@@ -393,10 +413,11 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
     }
 }
 
-// Zeroes body adjoints (4 per body) and node adjoints (5 per node that
+// Zeroes body adjoints (4 per body) and node adjoints (4 and 1 per node that
 // exists), and writes each node's parent (-1 for the root).
 __global__ __launch_bounds__(256) void k_vjp_clear(double *__restrict__ badj, int64_t n,
                                                    double *__restrict__ nadj,
+                                                   double *__restrict__ nadj_e,
                                                    int32_t *__restrict__ nparent,
                                                    const NodeInfo *__restrict__ ninfo,
                                                    const TreeHeader *__restrict__ hdr,
@@ -408,7 +429,8 @@ __global__ __launch_bounds__(256) void k_vjp_clear(double *__restrict__ badj, in
     const int64_t stride = (int64_t)gridDim.x * 256;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     for (int64_t i = t; i < 4 * n; i += stride) badj[i] = 0.0;
-    for (int64_t i = t; i < 5 * nn; i += stride) nadj[i] = 0.0;
+    for (int64_t i = t; i < 4 * nn; i += stride) nadj[i] = 0.0;
+    for (int64_t i = t; i < nn; i += stride) nadj_e[i] = 0.0;
     if (t == 0 && nn > 0) nparent[0] = -1;
     for (int64_t k = t; k < nn; k += stride) {
         const NodeInfo info = ninfo[k];
@@ -420,16 +442,17 @@ __global__ __launch_bounds__(256) void k_vjp_clear(double *__restrict__ badj, in
 }
 
 // Per-node coefficients of the member update, from the node's adjoints.
-__device__ inline void node_coeffs(const double *__restrict__ nadj, const NodeMom &nm, double e2,
+__device__ inline void node_coeffs(const double *__restrict__ nadj,
+                                   const double *__restrict__ nadj_e, const NodeMom &nm, double e2,
                                    int64_t k, double out[5])
 {
-    const double *a = nadj + 5 * k;
+    const double *a = nadj + 4 * k;
     if (nm.m > 0.0) {
         const double inv = 1.0 / nm.m;
         out[0] = a[0] * inv;
         out[1] = a[1] * inv;
         out[2] = a[2] * inv;
-        out[4] = a[4] * inv;
+        out[4] = nadj_e[k] * inv;
         out[3] = a[3] - (nm.x * out[0] + nm.y * out[1] + nm.z * out[2]) - e2 * out[4];
     } else {
         out[0] = out[1] = out[2] = out[4] = 0.0;
@@ -446,6 +469,7 @@ __global__ __launch_bounds__(256) void k_vjp_finish(
     const TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const NodeMom *__restrict__ nmom, const double *__restrict__ neps2,
     const int32_t *__restrict__ nparent, const double *__restrict__ nadj,
+    const double *__restrict__ nadj_e,
     const Body *__restrict__ body, const double *__restrict__ beps2, int use_eps,
     const uint32_t *__restrict__ idx, const double *__restrict__ gt,
     const double *__restrict__ badj, double *__restrict__ g_pos, double *__restrict__ g_mass,
@@ -471,7 +495,7 @@ __global__ __launch_bounds__(256) void k_vjp_finish(
             const int32_t c = chain[d];
             if (c < 0) continue;
             double cf[5];
-            node_coeffs(nadj, nmom[c], use_eps ? neps2[c] : 0.0, c, cf);
+            node_coeffs(nadj, nadj_e, nmom[c], use_eps ? neps2[c] : 0.0, c, cf);
             for (int q = 0; q < 5; q++) p[q] = p[q] + cf[q];
         }
         for (int32_t s = info.first; s < info.first + info.count; s++) {
@@ -696,7 +720,9 @@ hipError_t launch_tree_vjp(const Workspace &w, const AdjointWork &aw, hipStream_
                            double *g_mass)
 {
     if (p.n <= 0) return hipSuccess;
-    k_vjp_clear<<<1024, 256, 0, s>>>(aw.badj, p.n, aw.nadj, aw.nparent, w.ninfo, w.hdr,
+    // the fifth component of every node follows the four of all
+    double *const nadj_e = aw.nadj + 4 * aw.node_cap;
+    k_vjp_clear<<<1024, 256, 0, s>>>(aw.badj, p.n, aw.nadj, nadj_e, aw.nparent, w.ninfo, w.hdr,
                                      w.node_cap);
     const int gb = p.group == 16 || p.group == 32 ? p.group : 64;
     const int ngroups = (int)((p.n + gb - 1) / gb);
@@ -706,12 +732,12 @@ hipError_t launch_tree_vjp(const Workspace &w, const AdjointWork &aw, hipStream_
             k_vjp_walk<decltype(peps)::value, decltype(gbc)::value, true>
                 <<<8 * per_xcd, 64 * (1 + kEvals), 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
                                             w.box, p.n, ngroups, per_xcd, p.th2, p.eps0sq, p.G,
-                                            lambda, aw.gt, aw.badj, aw.nadj);
+                                            lambda, aw.gt, aw.badj, aw.nadj, nadj_e);
         else
             k_vjp_walk<decltype(peps)::value, decltype(gbc)::value, false>
                 <<<8 * per_xcd, 64 * (1 + kEvals), 0, s>>>(w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.idx[0],
                                             w.box, p.n, ngroups, per_xcd, p.th2, p.eps0sq, p.G,
-                                            lambda, aw.gt, aw.badj, aw.nadj);
+                                            lambda, aw.gt, aw.badj, aw.nadj, nadj_e);
     };
     using T = std::true_type;
     using F = std::false_type;
@@ -729,7 +755,7 @@ hipError_t launch_tree_vjp(const Workspace &w, const AdjointWork &aw, hipStream_
     }
     const int use_eps = p.per_body_eps ? 1 : 0;
     k_vjp_finish<<<blocks(p.n, 4096), 256, 0, s>>>(w.hdr, w.ninfo, w.nmom, w.neps2, aw.nparent,
-                                                   aw.nadj, w.body, w.beps2, use_eps, w.idx[0],
+                                                   aw.nadj, nadj_e, w.body, w.beps2, use_eps, w.idx[0],
                                                    aw.gt, aw.badj, g_pos, g_mass, w.node_cap);
     return hipGetLastError();
 }

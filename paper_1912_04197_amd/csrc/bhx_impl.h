@@ -346,7 +346,8 @@ struct AdjointWork {
     TreeSlots trees;         // allocated by the first segment VJP that fits in memory
     double *gt = nullptr;    // [n_cap][3] target-side gradients, sorted order
     double *badj = nullptr;  // [n_cap][4] source-side body adjoints, sorted order
-    double *nadj = nullptr;  // [node_cap][5] node adjoints: gX, gm, g<eps^2>
+    int64_t node_cap = 0;    // of the context's node table
+    double *nadj = nullptr;  // [node_cap][4] node adjoints gX, gm, then [node_cap] g<eps^2>
     int32_t *nparent = nullptr;  // [node_cap] parent of each node (-1: the root)
     double *vwork = nullptr; // [n_cap][3] velocity while a segment is recomputed
     double *awork = nullptr; // [n_cap][3] acceleration while a segment is recomputed

@@ -719,6 +719,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     if (cfg->flags & BH_FLAG_ADJOINT) {
         A(dalloc(&c->aw.gt, 3 * n));
         A(dalloc(&c->aw.badj, 4 * n));
+        c->aw.node_cap = node_cap;
         A(dalloc(&c->aw.nadj, 5 * node_cap));
         A(dalloc(&c->aw.nparent, node_cap));
         A(dalloc(&c->aw.vwork, 3 * n));
