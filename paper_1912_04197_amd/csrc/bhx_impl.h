@@ -16,8 +16,15 @@ constexpr int kMaxLevel = 21;           // cells on a 2^21 grid per axis
 constexpr int kLevels = kMaxLevel + 1;  // levels 0..21
 constexpr uint32_t kQMax = 2097151u;    // 2^21 - 1
 
-// Device status bits, latched until bh_sync().
-enum : uint32_t { ST_NONFINITE = 1u, ST_CAPACITY = 2u, ST_STACK = 4u };
+// Device errors, latched until bh_sync(): words of pinned host memory, one an
+// error, so that a synchronisation reads them without a copy from the device (a
+// 4-byte copy to pageable memory cost each synchronising call 15 us). A kernel
+// that finds an error stores 1 (atomics on host memory are not needed for that).
+enum : int { ST_NONFINITE = 0, ST_CAPACITY = 1, ST_WORDS = 2 };
+__device__ inline void flag_status(uint32_t *status, int error)
+{
+    __hip_atomic_store(status + error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // One body in Morton order: position and mass (32 B, one aligned load pair).
 struct alignas(32) Body {
@@ -58,12 +65,14 @@ struct SceneBox {
 // so a whole force evaluation runs without host round trips.
 struct TreeHeader {
     int32_t level_count[kLevels + 1];  // nodes created per level (all scenes)
-    uint32_t status;                   // ST_* bits
+    uint32_t *status;                  // ST_* words, set at creation
     int32_t cell_max;                  // most bodies in one node of level kHintLevel
 };
 // The level whose largest node the build reports for the choice of sort.
 constexpr int kHintLevel = 5;
 constexpr int kHintWords = 2 + kLevels;  // pinned launch-hint words of a workspace
+constexpr int kStatusAt = 64;  // the status words follow, on a line of their own
+static_assert(kHintWords <= kStatusAt, "pinned words");
 // The levels 1..kPrefixLevels of a single scene's tree are read off the
 // sorted keys: a level-kPrefixLevels cell is the key's top 3 kPrefixLevels
 // bits, and the first body of each such cell gives every cell range above it.
@@ -238,6 +247,8 @@ struct Workspace {
     // (which picks how level l is split), kHintWords words in all.
     int32_t *depth_host = nullptr;
     int32_t *depth_dev = nullptr;  // the same memory as the device sees it
+    // the ST_* words, kStatusAt words into the same allocation
+    uint32_t *status_host = nullptr, *status_dev = nullptr;
     // [kPrefixCells] first sorted body of each level-kPrefixLevels cell, or
     // INT32_MAX ("none"): set at creation, written by one build and restored
     // to "none" by the same build once read.
@@ -339,8 +350,6 @@ struct TreeSlots {
 };
 // A workspace whose tree arrays are slot k's (scratch arrays shared with w).
 Workspace slot_view(const Workspace &w, const TreeSlots &t, int k);
-// ORs the slots' status words into *status and clears them.
-hipError_t launch_merge_status(hipStream_t s, TreeHeader *slot_hdr, int count, uint32_t *status);
 
 struct AdjointWork {
     TreeSlots trees;         // allocated by the first segment VJP that fits in memory

@@ -107,6 +107,15 @@ hipError_t dalloc(T **p, int64_t count)
     return hipMalloc((void **)p, (size_t)count * sizeof(T));
 }
 
+// Empty tree headers that report to the status words.
+hipError_t init_headers(bhx::TreeHeader *hdr, int count, uint32_t *status)
+{
+    bhx::TreeHeader h{};
+    h.status = status;
+    const std::vector<bhx::TreeHeader> all((size_t)count, h);
+    return hipMemcpy(hdr, all.data(), all.size() * sizeof(h), hipMemcpyHostToDevice);
+}
+
 void free_slots(bhx::TreeSlots &t)
 {
     void *ptrs[] = {t.body, t.beps2, t.idx, t.keys, t.ninfo, t.nmom, t.neps2, t.box, t.hdr};
@@ -479,7 +488,7 @@ bh_status run_steps(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
     const bool state = sorted_state(lay, theta, nsteps, graph);
     if (state)
         BHX_HIP(c, bhx::launch_state_pack(c->w, c->stream, pos, vel, acc, mass, eps, lay.n,
-                                          &c->w.hdr->status));
+                                          c->w.status_dev));
     if (!graph) {
         for (int32_t k = 0; k < nsteps; k++) {
             bh_status s = any_step(c, state, lay, pos, vel, mass, softening, eps, theta, dt, acc);
@@ -615,7 +624,7 @@ bool ensure_tree_slots(bh_ctx *c, int32_t nsteps, int64_t n)
     A(dalloc(&t.neps2, k * node_cap));
     A(dalloc(&t.box, k));
     A(dalloc(&t.hdr, k));
-    if (r == hipSuccess) r = hipMemset(t.hdr, 0, (size_t)k * sizeof(bhx::TreeHeader));
+    if (r == hipSuccess) r = init_headers(t.hdr, nsteps, c->w.status_dev);
     if (r != hipSuccess) {
         (void)hipGetLastError();
         free_slots(t);
@@ -710,11 +719,16 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     A(dalloc(&w.red_part, (int64_t)bhx::kRedBlocks * 16));
     A(dalloc(&w.dpart, bhx::kDirectPart));
     A(dalloc(&c->diag_out, 8));
-    A(hipHostMalloc((void **)&w.depth_host, bhx::kHintWords * sizeof(int32_t),
+    A(hipHostMalloc((void **)&w.depth_host, (bhx::kStatusAt + bhx::ST_WORDS) * sizeof(int32_t),
                     hipHostMallocMapped));
     if (r == hipSuccess) {
         for (int i = 0; i < bhx::kHintWords; i++) w.depth_host[i] = -1;
         r = hipHostGetDevicePointer((void **)&w.depth_dev, w.depth_host, 0);
+    }
+    if (r == hipSuccess) {
+        w.status_host = (uint32_t *)(w.depth_host + bhx::kStatusAt);
+        w.status_dev = (uint32_t *)(w.depth_dev + bhx::kStatusAt);
+        for (int k = 0; k < bhx::ST_WORDS; k++) w.status_host[k] = 0;
     }
     if (cfg->flags & BH_FLAG_ADJOINT) {
         A(dalloc(&c->aw.gt, 3 * n));
@@ -730,7 +744,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
         for (auto &ev : c->ev_pool)
             if (r == hipSuccess) r = hipEventCreate(&ev);
     }
-    if (r == hipSuccess) r = hipMemset(w.hdr, 0, sizeof(bhx::TreeHeader));
+    if (r == hipSuccess) r = init_headers(w.hdr, 1, w.status_dev);
     if (r == hipSuccess) r = hipDeviceSynchronize();
     if (r != hipSuccess) {
         bh_status st = (r == hipErrorOutOfMemory) ? BH_E_OOM : BH_E_HIP;
@@ -767,9 +781,6 @@ const char *bh_last_error(const bh_ctx *c) { return c ? c->err.c_str() : "NULL c
 bh_status bh_sync(bh_ctx *c)
 {
     if (!c) return BH_E_INVALID;
-    uint32_t st = 0;
-    BHX_HIP(c, hipMemcpyAsync(&st, &c->w.hdr->status, sizeof(st), hipMemcpyDeviceToHost,
-                              c->stream));
     BHX_HIP(c, hipStreamSynchronize(c->stream));
     uint32_t ck = 0;  // device checks (checked build only)
     BHX_HIP(c, bhx::walk_take_checks(&ck));
@@ -784,15 +795,16 @@ bh_status bh_sync(bh_ctx *c)
             if (ck & (1u << b)) msg += std::string(" ") + names[b];
         return fail(c, BH_E_CHECK, msg);
     }
-    if (st == 0) return BH_OK;
-    const uint32_t zero = 0;
-    BHX_HIP(c, hipMemcpyAsync(&c->w.hdr->status, &zero, sizeof(zero), hipMemcpyHostToDevice,
-                              c->stream));
-    BHX_HIP(c, hipStreamSynchronize(c->stream));
-    if (st & bhx::ST_NONFINITE)
+    volatile uint32_t *status = c->w.status_host;
+    bool found[bhx::ST_WORDS];
+    for (int k = 0; k < bhx::ST_WORDS; k++) {
+        found[k] = status[k] != 0;
+        status[k] = 0;
+    }
+    if (found[bhx::ST_NONFINITE])
         return fail(c, BH_E_NONFINITE, "non-finite position, mass or softening, or negative mass");
-    if (st & bhx::ST_CAPACITY) return fail(c, BH_E_CAPACITY, "node table overflow");
-    return fail(c, BH_E_STACK, "unknown device status");
+    if (found[bhx::ST_CAPACITY]) return fail(c, BH_E_CAPACITY, "node table overflow");
+    return BH_OK;
 }
 
 bh_status bh_build_tree(bh_ctx *c, const double *pos, const double *mass, const double *eps,
@@ -986,9 +998,6 @@ bh_status bh_leapfrog_vjp(bh_ctx *c, const double *pos, const double *vel, const
     s = reverse_sweep(c, traj, mass, softening, eps, theta, dt, nsteps, xbar, vbar, abar, g_mass,
                       n, keep);
     if (s) return s;
-    // bad input found by the slot builds is reported like the context's own
-    if (keep)
-        BHX_HIP(c, bhx::launch_merge_status(c->stream, aw.trees.hdr, nsteps, &c->w.hdr->status));
     return BH_OK;
 }
 
@@ -1106,7 +1115,7 @@ bh_status bh_gravity_dt_bound(bh_ctx *c, const double *mass, const double *radiu
     auto *work = (long long *)c->diag_out;
     double *out = c->diag_out + 1;
     BHX_HIP(c, bhx::launch_dt_bound(c->stream, mass, radius, n, c->cfg.G, work, out,
-                                    &c->w.hdr->status));
+                                    c->w.status_dev));
     double dt = 0.0;
     BHX_HIP(c, hipMemcpyAsync(&dt, out, sizeof(dt), hipMemcpyDeviceToHost, c->stream));
     bh_status st = bh_sync(c);

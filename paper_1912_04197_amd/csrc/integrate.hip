@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void k_state_pack(
         }
         idx[i] = (uint32_t)i;
     }
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(status, ST_NONFINITE);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(status, ST_NONFINITE);
 }
 
 // The end of a multi-step call: the state back to the caller's arrays.
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void k_rho_max(const double *__restrict__ mass
     if ((threadIdx.x & 63) == 0) {
         if (best >= 0.0) atomicMax(&work[0], __double_as_longlong(best));
     }
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(status, ST_NONFINITE);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(status, ST_NONFINITE);
 }
 
 __global__ __launch_bounds__(64) void k_dt_from_rho(const long long *__restrict__ work, double G,

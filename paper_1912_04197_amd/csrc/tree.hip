@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_box_chunk(const double *__restr
             hi[a] = fmax(hi[a], x[a]);
         }
     }
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&hdr->status, ST_NONFINITE);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(hdr->status, ST_NONFINITE);
     __shared__ double red[kBoxThreads / 64][6];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int a = 0; a < 3; a++) {
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
             hi[a] = fmax(hi[a], x[a]);
         }
     }
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&hdr->status, ST_NONFINITE);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(hdr->status, ST_NONFINITE);
     __shared__ double red[kBoxThreads / 64][6];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int a = 0; a < 3; a++) {
@@ -1058,7 +1058,7 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
             if (!split) continue;
             const int64_t cfirst = (int64_t)next_beg + slot;
             if (cfirst + nch > node_cap) {
-                if (o == 0) atomicOr(status, ST_CAPACITY);
+                if (o == 0) flag_status(status, ST_CAPACITY);
                 continue;
             }
             const int32_t scene_bits = info.lvl_nch & (int32_t)0xffff0000;
@@ -1087,7 +1087,7 @@ __global__ __launch_bounds__(1024) void k_build_level(int level, const uint64_t 
                                                       int64_t node_cap, int leaf)
 {
     const int64_t per_step = compact ? blockDim.x : blockDim.x >> 3;  // nodes per block step
-    build_nodes<compact>(level, keys, hdr->level_count, &hdr->status, &hdr->cell_max, ninfo,
+    build_nodes<compact>(level, keys, hdr->level_count, hdr->status, &hdr->cell_max, ninfo,
                          node_cap, leaf, (int64_t)blockIdx.x * per_step,
                          (int64_t)gridDim.x * per_step);
 }
@@ -1102,7 +1102,7 @@ __device__ inline void build_levels_block(int from, int upto, const uint64_t *__
 {
     for (int level = from; level < upto; level++) {
         if (scnt[level] == 0) break;
-        build_nodes<compact>(level, keys, scnt, &hdr->status, &hdr->cell_max, ninfo, node_cap, leaf,
+        build_nodes<compact>(level, keys, scnt, hdr->status, &hdr->cell_max, ninfo, node_cap, leaf,
                              0, compact ? blockDim.x : blockDim.x >> 3);
         __syncthreads();
     }
@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(1024) void k_prefix_levels(int32_t *__restrict__ ma
     const int64_t beg1 = 1, beg2 = beg1 + tot[0], beg3 = beg2 + tot[1], beg4 = beg3 + tot[2],
                   beg5 = beg4 + tot[3];
     if (beg5 + tot[4] > node_cap) {
-        if (t == 0) atomicOr(&hdr->status, ST_CAPACITY);
+        if (t == 0) flag_status(hdr->status, ST_CAPACITY);
         return;  // the same on every thread
     }
     auto nonempty8 = [&](int l, int c) {  // non-empty children of level-l cell c, l <= 4
@@ -1643,7 +1643,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
                 hi[a] = fmax(hi[a], x[j][a]);
             }
         }
-        if (__ballot(bad) && lane == 0) atomicOr(&hdr->status, ST_NONFINITE);
+        if (__ballot(bad) && lane == 0) flag_status(hdr->status, ST_NONFINITE);
         for (int a = 0; a < 3; a++) {
             const double l = wave_min(lo[a]), h = wave_max(hi[a]);
             if (lane == 0) {
@@ -1776,7 +1776,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
             base = beg + __builtin_amdgcn_readfirstlane(base);
             at = __builtin_amdgcn_readfirstlane(at);
             if (base + __popcll(cb) > node_cap) {  // the same on every lane
-                if (lane == 0) atomicOr(&hdr->status, ST_CAPACITY);
+                if (lane == 0) flag_status(hdr->status, ST_CAPACITY);
                 if (live && o == 0) ninfo[nd.id] = NodeInfo{first, count, -1, level};
                 continue;
             }
@@ -2042,18 +2042,6 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
                                           w.nmom, w.neps2, w.nquad, w.node_cap, ue, w.depth_dev);
 }
 
-__global__ __launch_bounds__(64) void k_merge_status(TreeHeader *__restrict__ slot_hdr, int count,
-                                                     uint32_t *__restrict__ status)
-{
-    for (int k = threadIdx.x; k < count; k += 64) {
-        const uint32_t st = slot_hdr[k].status;
-        if (st) {
-            atomicOr(status, st);
-            slot_hdr[k].status = 0u;
-        }
-    }
-}
-
 }  // namespace
 
 BHX_DEFINE_TAKE_CHECKS(tree_take_checks)
@@ -2073,13 +2061,6 @@ Workspace slot_view(const Workspace &w, const TreeSlots &t, int k)
     v.hdr = t.hdr + k;
     v.max_scenes = 1;
     return v;
-}
-
-hipError_t launch_merge_status(hipStream_t s, TreeHeader *slot_hdr, int count, uint32_t *status)
-{
-    if (count <= 0) return hipSuccess;
-    k_merge_status<<<1, 64, 0, s>>>(slot_hdr, count, status);
-    return hipGetLastError();
 }
 
 bool bucket_sort_hint(const Workspace &w, const Layout &lay)
