@@ -39,6 +39,33 @@ __device__ inline T wave_max(T v)
     return v;
 }
 
+// The smallest and largest of a row's 16 lanes' values, on every lane of the row,
+// by DPP lane moves (a lane permute goes through the LDS unit, which the 16
+// waves of a block share).
+template <int CTRL>
+__device__ inline double dpp_f64(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppRor4 = 0x124, kDppRor8 = 0x128;
+__device__ inline double row_min(double v)
+{
+    v = fmin(v, dpp_f64<kDppXor1>(v));
+    v = fmin(v, dpp_f64<kDppXor2>(v));
+    v = fmin(v, dpp_f64<kDppRor4>(v));
+    return fmin(v, dpp_f64<kDppRor8>(v));
+}
+__device__ inline double row_max(double v)
+{
+    v = fmax(v, dpp_f64<kDppXor1>(v));
+    v = fmax(v, dpp_f64<kDppXor2>(v));
+    v = fmax(v, dpp_f64<kDppRor4>(v));
+    return fmax(v, dpp_f64<kDppRor8>(v));
+}
+
 // Inclusive scan over a 256-thread block (4 waves).
 __device__ inline uint32_t block_incl_scan_256(uint32_t v, uint32_t *lds4, uint32_t *total)
 {
@@ -1348,22 +1375,29 @@ struct MomentSum {
             }
         }
     }
+    // G children are loaded at a time (8 from global memory, whose latency
+    // counts; fewer from LDS, where registers do)
+    template <int G = 8>
     __device__ inline void children(const NodeMom *nmom, const double *neps2, const NodeInfo &info,
                                     bool use_eps)
     {
         const int nch = node_nchild(info);
-        NodeMom cm[8];
-        double e[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) {
-            const int32_t c = info.child0 + (u < nch ? u : 0);
-            cm[u] = nmom[c];
-            e[u] = use_eps ? neps2[c] : 0.0;
-        }
+        for (int u0 = 0; u0 < 8; u0 += G) {
+            if (u0 >= nch) break;
+            NodeMom cm[G];
+            double e[G];
 #pragma unroll
-        for (int u = 0; u < 8; u++) {
-            if (u >= nch) break;
-            add(cm[u].x, cm[u].y, cm[u].z, cm[u].m, e[u], use_eps);
+            for (int u = 0; u < G; u++) {
+                const int32_t c = info.child0 + (u0 + u < nch ? u0 + u : 0);
+                cm[u] = nmom[c];
+                e[u] = use_eps ? neps2[c] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < G; u++) {
+                if (u0 + u >= nch) break;
+                add(cm[u].x, cm[u].y, cm[u].z, cm[u].m, e[u], use_eps);
+            }
         }
     }
     // The node's moments and mean eps^2; a massless cell has its centre.
@@ -1537,56 +1571,115 @@ __global__ __launch_bounds__(1024) void k_moments_tail(
 //            memory, with the launches' split);
 //   moments  of every leaf at once, then the internal nodes level by level from
 //            a copy of the moments in LDS (up to kCacheNodes nodes).
-// A ball of 1000 bodies, leaf 16: 80 -> 29 us; leaf 1 (ten levels) 119 -> 43 us;
-// 4096 bodies, leaf 16: 111 -> 74 us.
+// A ball of 1000 bodies, leaf 16: 80 -> 20 us; leaf 1 (ten levels) 119 -> 32 us;
+// 4096 bodies, leaf 16: 111 -> 47 us.
 constexpr int kSmallThreads = 1024;
 constexpr int kCacheNodes = 3840;
 // LDS: two buffers of keys and indices while sorting; the sorted keys and two
-// lists of splitting nodes while splitting; node moments at the end.
+// lists of splitting nodes while splitting; node moments at the end; above all of
+// these, for at most kCacheBodies bodies, the sorted bodies that the leaves sum.
+constexpr int kCacheBodies = 1024;
 constexpr int kSmallLds = kCacheNodes * (int)(sizeof(NodeMom) + sizeof(double));
-static_assert(kSmallLds >= (int)kSmallBuild * 2 * (8 + 2), "sort buffers");
 static_assert(kSmallLds >= (int)kSmallBuild * (8 + 8), "keys and split lists");
 static_assert(kCacheNodes <= 4 * kSmallThreads, "nodes a thread keeps");
+constexpr int kNodeLds = (int)(sizeof(NodeMom) + sizeof(double));
+constexpr int kBodyLds = kCacheBodies * (int)(sizeof(Body) + sizeof(double));
+static_assert(kSmallLds - kBodyLds >= (int)kSmallBuild * (2 * (8 + 2) + 4), "bodies beside the sort");
 
-// A stable sort of the m (a multiple of 64, at most kSmallBuild) keys and
-// indices in buffer 0; returns the buffer that holds the order.
-__device__ inline int small_sort(uint64_t (*key)[kSmallBuild], uint16_t (*val)[kSmallBuild], int m)
+// One round of merges: runs of LEN keys in pairs, from buffer src to dst, E keys a
+// thread. A key goes to its place in its own run plus the number of keys of the
+// other run before it: less, or, coming from the left run, equal (so that the
+// order is stable). The searches are unrolled, three instructions and one LDS read
+// at a constant offset a step, and a thread's E searches run side by side: with a
+// loop over a run-time length and one search at a time the sort of 4096 bodies took
+// 33 us, now 16.
+template <int LEN, int E>
+__device__ inline void merge_runs(const uint64_t *__restrict__ ksrc,
+                                  const uint16_t *__restrict__ vsrc, uint64_t *__restrict__ kdst,
+                                  uint16_t *__restrict__ vdst, int m)
+{
+    if (E == 1 && (int)threadIdx.x >= m) return;
+    uint64_t k[E], lim[E];
+    int o[E], c[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int p = threadIdx.x + e * kSmallThreads;
+        k[e] = ksrc[p];
+        const bool right = (p & LEN) != 0;
+        o[e] = (p & ~(2 * LEN - 1)) + (right ? 0 : LEN);  // the other run
+        lim[e] = k[e] + (right ? 1 : 0);                  // its keys below this come first
+        c[e] = 0;
+    }
+#pragma unroll
+    for (int s = LEN / 2; s > 0; s >>= 1)
+#pragma unroll
+        for (int e = 0; e < E; e++) c[e] += ksrc[o[e] + c[e] + s - 1] < lim[e] ? s : 0;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int p = threadIdx.x + e * kSmallThreads;
+        c[e] += ksrc[o[e] + c[e]] < lim[e] ? 1 : 0;
+        const int to = (p & LEN ? p - LEN : p) + c[e];
+        kdst[to] = k[e];
+        vdst[to] = vsrc[p];
+    }
+}
+
+// A stable sort of the m (1024 E, or 64 times a power of two below) keys and
+// indices in buffer 0; returns the buffer that holds the order. Keys are below
+// 2^64 - 1; high: their high words.
+template <int E>
+__device__ inline int small_sort(uint64_t (*key)[kSmallBuild], uint16_t (*val)[kSmallBuild],
+                                 const uint32_t *high, int m)
 {
     const int lane = threadIdx.x & 63;
-    // runs of 64, one per wave: each lane counts the keys before its own
+    // runs of 64, one per wave: each lane counts the keys before its own, by the
+    // high words (levels 1 to 10) where no two of the run are equal, else by
+    // whole keys
     for (int p = threadIdx.x; p < m; p += kSmallThreads) {
         const uint64_t k = key[0][p];
-        const uint64_t *run = key[0] + (p - lane);
+        const int r0 = p - lane;
+        const uint64_t *run = key[0] + r0;
+        const uint4 *hrun = (const uint4 *)(high + r0);
+        const uint32_t kh = (uint32_t)(k >> 32);
         int rank = 0;
-#pragma unroll 8
-        for (int j = 0; j < 64; j++) {
-            const uint64_t o = run[j];
-            rank += (o < k || (o == k && j < lane)) ? 1 : 0;
+#pragma unroll 4
+        for (int j = 0; j < 16; j++) {
+            const uint4 h = hrun[j];
+            rank += (h.x < kh ? 1 : 0) + (h.y < kh ? 1 : 0) + (h.z < kh ? 1 : 0) + (h.w < kh ? 1 : 0);
         }
-        key[1][p - lane + rank] = k;
-        val[1][p - lane + rank] = val[0][p];
+        // a place that two lanes claim: equal high words somewhere in the run
+        val[1][r0 + rank] = (uint16_t)lane;
+        __builtin_amdgcn_wave_barrier();
+        if (__ballot(val[1][r0 + rank] != lane)) {
+            rank = 0;
+#pragma unroll 1
+            for (int j = 0; j < 64; j++) {
+                const uint64_t o = run[j];
+                rank += (o < k || (o == k && j < lane)) ? 1 : 0;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        key[1][r0 + rank] = k;
+        val[1][r0 + rank] = val[0][p];
     }
     __syncthreads();
     int src = 1;
     for (int len = 64; len < m; len *= 2) {
-        for (int p = threadIdx.x; p < m; p += kSmallThreads) {
-            const uint64_t k = key[src][p];
-            const int a0 = p & ~(2 * len - 1);  // the pair of runs
-            const bool right = (p & len) != 0;
-            const int o0 = right ? a0 : a0 + len;  // the other run
-            const int olen = min(len, max(0, m - o0));
-            const uint64_t *o = key[src] + o0;
-            // keys of the other run before this one: less, or, coming from the
-            // left run, equal
-            int c = 0;
-            for (int s = len; s > 0; s >>= 1)
-                if (c + s <= olen) {
-                    const uint64_t x = o[c + s - 1];
-                    if (x < k || (right && x == k)) c += s;
-                }
-            const int to = (right ? p - len : p) + c;
-            key[src ^ 1][to] = k;
-            val[src ^ 1][to] = val[src][p];
+        const uint64_t *ks = key[src];
+        const uint16_t *vs = val[src];
+        uint64_t *kd = key[src ^ 1];
+        uint16_t *vd = val[src ^ 1];
+        switch (len) {
+            case 64: merge_runs<64, E>(ks, vs, kd, vd, m); break;
+            case 128: merge_runs<128, E>(ks, vs, kd, vd, m); break;
+            case 256: merge_runs<256, E>(ks, vs, kd, vd, m); break;
+            case 512: merge_runs<512, E>(ks, vs, kd, vd, m); break;
+            case 1024:
+                if constexpr (E > 1) merge_runs<1024, E>(ks, vs, kd, vd, m);
+                break;
+            default:
+                if constexpr (E > 2) merge_runs<2048, E>(ks, vs, kd, vd, m);
+                break;
         }
         src ^= 1;
         __syncthreads();
@@ -1609,9 +1702,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     double *__restrict__ neps2, double *__restrict__ nquad, int64_t node_cap,
     int32_t *__restrict__ depth_out)
 {
-    constexpr int W = kSmallThreads / 64, kPer = (int)(kSmallBuild / kSmallThreads);
+    constexpr int kPer = (int)(kSmallBuild / kSmallThreads);
     __shared__ alignas(16) char lds[kSmallLds];
-    __shared__ double red[W][6];
+    static_assert(kSmallThreads / 16 == 64, "one row of 16 lanes a lane");
+    __shared__ double red[64][6];
     __shared__ SceneBox sbox;
     __shared__ int32_t scnt[kLevels + 1];
     __shared__ int32_t nsplit[3];
@@ -1645,10 +1739,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         }
         if (__ballot(bad) && lane == 0) flag_status(hdr->status, ST_NONFINITE);
         for (int a = 0; a < 3; a++) {
-            const double l = wave_min(lo[a]), h = wave_max(hi[a]);
-            if (lane == 0) {
-                red[wave][a] = l;
-                red[wave][3 + a] = h;
+            const double l = row_min(lo[a]), h = row_max(hi[a]);
+            if ((lane & 15) == 0) {
+                red[tid >> 4][a] = l;
+                red[tid >> 4][3 + a] = h;
             }
         }
     }
@@ -1657,9 +1751,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     __syncthreads();
     if (tid < 64) {
         double v[6];
-        for (int a = 0; a < 6; a++) v[a] = red[lane & (W - 1)][a];
+        for (int a = 0; a < 6; a++) v[a] = a < 3 ? row_min(red[lane][a]) : row_max(red[lane][a]);
 #pragma unroll
-        for (int o = 1; o < W; o <<= 1)
+        for (int o = 16; o < 64; o <<= 1)
             for (int a = 0; a < 6; a++) {
                 const double u = __shfl_xor(v[a], o);
                 v[a] = a < 3 ? fmin(v[a], u) : fmax(v[a], u);
@@ -1673,13 +1767,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     __syncthreads();
     if (tid < (int)(sizeof(SceneBox) / 8)) ((uint64_t *)box)[tid] = ((const uint64_t *)&sbox)[tid];
 
-    // 2. keys, in LDS; the places past n hold the largest key and sort last
-    const int m = (n + 63) & ~63;
+    const bool few = n <= kCacheBodies;
+    Body *const lbody = (Body *)(lds + kSmallLds - kBodyLds);
+    double *const leps2 = (double *)(lds + kSmallLds - kCacheBodies * (int)sizeof(double));
+
+    // 2. keys, in LDS; the places past n hold keys above any body's
+    uint32_t *const high = (uint32_t *)(lds + 2 * (sizeof(uint64_t) + sizeof(uint16_t)) * kSmallBuild);
+    int m = 64;
+    while (m < n) m *= 2;
 #pragma unroll
     for (int j = 0; j < kPer; j++) {
         const int i = tid + j * kSmallThreads;
         if (i < m) {
-            skey[0][i] = i < n ? morton_key(x[j], sbox) : ~0ull;
+            const uint64_t k =
+                i < n ? morton_key(x[j], sbox) : (0xffffffc0ull | (uint64_t)(i & 63)) << 32;
+            skey[0][i] = k;
+            high[i] = (uint32_t)(k >> 32);
             sval[0][i] = (uint16_t)i;
         }
     }
@@ -1688,7 +1791,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     // 3. sort, and 4. gather; the walk and the tree export read the sorted keys
     // and indices from global memory
     {
-        const int at = small_sort(skey, sval, m);
+        static_assert(kSmallBuild == 4 * kSmallThreads, "keys a thread");
+        const int at = m > 2 * kSmallThreads ? small_sort<4>(skey, sval, high, m)
+                       : m > kSmallThreads   ? small_sort<2>(skey, sval, high, m)
+                                             : small_sort<1>(skey, sval, high, m);
         uint64_t mine[kPer];
 #pragma unroll
         for (int j = 0; j < kPer; j++) {
@@ -1698,10 +1804,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
             mine[j] = skey[at][s];
             k0[s] = mine[j];
             i0[s] = i;
-            body[s] = Body{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]};
-            if (use_eps) {
-                const double e = eps[i];
-                beps2[s] = e * e;
+            const Body b{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]};
+            const double e = use_eps ? eps[i] : 0.0;
+            body[s] = b;
+            if (use_eps) beps2[s] = e * e;
+            if (few) {
+                lbody[s] = b;
+                leps2[s] = e * e;
             }
         }
         __syncthreads();
@@ -1800,9 +1909,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     }
 
     // 6. moments
-    if (total <= kCacheNodes && total <= node_cap && !nquad) {
+    const int cache = few ? (kSmallLds - kBodyLds) / kNodeLds : kCacheNodes;
+    if (total <= cache && total <= node_cap && !nquad) {
         NodeMom *cm = (NodeMom *)lds;
-        double *ce = (double *)(lds + kCacheNodes * sizeof(NodeMom));
+        double *ce = (double *)(lds + cache * sizeof(NodeMom));
         int inner[4];  // an internal node's first child, children << 12 and level << 16
         __syncthreads();  // the keys and lists are read no more
         auto store = [&](int k, int level, const MomentSum &s) {
@@ -1826,18 +1936,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
                 inner[j] = info.child0 | node_nchild(info) << 12 | node_level(info) << 16;
             } else {
                 MomentSum s;
-                s.leaf(body, beps2, info, use_eps);
+                if (few)
+                    s.leaf(lbody, leps2, info, use_eps);
+                else
+                    s.leaf(body, beps2, info, use_eps);
                 store(k, node_level(info), s);
             }
         }
         __syncthreads();
         for (int level = depth - 1; level >= 0; level--) {
-#pragma unroll
+            // the level's nodes are consecutive, so a thread seldom has two of them
+#pragma unroll 1
             for (int j = 0; j < 4; j++) {
-                if (inner[j] < 0 || inner[j] >> 16 != level) continue;
+                const int in = j == 0 ? inner[0] : j == 1 ? inner[1] : j == 2 ? inner[2] : inner[3];
+                if (in < 0 || in >> 16 != level) continue;
                 MomentSum s;
-                s.children(cm, ce, NodeInfo{0, 0, inner[j] & 0xfff, (inner[j] >> 12 & 0xf) << 8},
-                           use_eps);
+                s.children<4>(cm, ce, NodeInfo{0, 0, in & 0xfff, (in >> 12 & 0xf) << 8}, use_eps);
                 store(tid + j * kSmallThreads, level, s);
             }
             __syncthreads();
