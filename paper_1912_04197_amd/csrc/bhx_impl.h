@@ -285,8 +285,21 @@ inline int64_t node_capacity(int64_t n, int leaf, int scenes = 1)
 // previous build reported (a host read of pinned memory, frozen in a
 // captured graph) and handles deeper levels in one block: any depth is
 // built correctly, a deeper one more slowly.
+// With `adv`, only for a layout that one block builds (one_block_build): the
+// bodies are moved first, in the same launch.
+struct Advance {
+    double *pos = nullptr, *vel = nullptr;  // caller order; pos: the build's
+    const double *acc = nullptr;
+    double dt = 0.0;
+    int substeps = 0;  // > 0: as launch_euler_substeps; 0: as launch_kick_drift
+};
 hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
-                        const double *mass, const double *eps, int leaf, bool *bucket = nullptr);
+                        const double *mass, const double *eps, int leaf, bool *bucket = nullptr,
+                        const Advance *adv = nullptr);
+inline bool one_block_build(const Layout &lay)
+{
+    return lay.n_scenes == 1 && lay.n >= 1 && lay.n <= kSmallBuild;
+}
 // The same build for one step on the sorted state (multi-step calls, more
 // than kSmallBuild bodies or several scenes): the step's first kick and its
 // drift (v = v + dt/2 a, x = x + dt v) run in the bounding-box pass over the
@@ -319,6 +332,10 @@ struct WalkParams {
     int precision;
     int group;  // target bodies per wavefront: 64, 32 or 16
     const double *nquad = nullptr;  // node quadrupoles: add their terms (or nullptr)
+    // velocities (in the order of acc) that the walk kicks by kick_h times the
+    // acceleration it writes, as launch_kick does (or nullptr)
+    double *kick_vel = nullptr;
+    double kick_h = 0.0;
 };
 constexpr int kDefaultWalkGroup = 64;
 constexpr int64_t kSmallWalk = 131072;  // below this many bodies the default group is 16

@@ -242,9 +242,17 @@ bhx::Layout single(int64_t n)
     return L;
 }
 
+// A second kick that the walk makes: velocities in the order of its
+// accelerations, and the time by which they are kicked.
+struct Kick {
+    double *vel = nullptr;
+    double h = 0.0;
+};
+
 // The walk of the tree just built, for the bodies of `lay`.
 bh_status walk(bh_ctx *c, const Workspace &w, const bhx::Layout &lay, double softening,
-               bool use_eps, double theta, double *acc, double *phi, bool acc_sorted)
+               bool use_eps, double theta, double *acc, double *phi, bool acc_sorted,
+               const Kick &kick)
 {
     const int64_t n = lay.n;
     c->tree_n = n;
@@ -264,6 +272,8 @@ bh_status walk(bh_ctx *c, const Workspace &w, const bhx::Layout &lay, double sof
     p.nquad = w.nquad;
     p.groups = lay.groups;
     p.n_groups = lay.n_groups;
+    p.kick_vel = kick.vel;
+    p.kick_h = kick.h;
     {
         Marker m(c, "bhx walk");
         BHX_HIP(c, bhx::launch_walk(w, c->stream, p));
@@ -276,7 +286,8 @@ bh_status walk(bh_ctx *c, const Workspace &w, const bhx::Layout &lay, double sof
 // slot of the adjoint).
 bh_status force_tree(bh_ctx *c, const bhx::Layout &lay, const double *pos, const double *mass,
                      double softening, const double *eps, double theta, double *acc, double *phi,
-                     const Workspace *w = nullptr)
+                     const Workspace *w = nullptr, const Kick &kick = Kick{},
+                     const bhx::Advance *adv = nullptr)
 {
     const Workspace &ws = w ? *w : c->w;
     bh_status st = record(c, 0);
@@ -284,11 +295,11 @@ bh_status force_tree(bh_ctx *c, const bhx::Layout &lay, const double *pos, const
     {
         Marker m(c, "bhx build");
         BHX_HIP(c, bhx::launch_build(ws, c->stream, lay, pos, mass, eps, c->cfg.leaf_size,
-                                     &c->bucket));
+                                     &c->bucket, adv));
     }
     st = record(c, 1);
     if (st) return st;
-    st = walk(c, ws, lay, softening, eps != nullptr, theta, acc, phi, false);
+    st = walk(c, ws, lay, softening, eps != nullptr, theta, acc, phi, false, kick);
     if (st) return st;
     return record(c, 2);
 }
@@ -422,11 +433,14 @@ bh_status kdk_step(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
                    double dt, double *acc)
 {
     Marker m(c, "bhx step");
-    BHX_HIP(c, bhx::launch_kick_drift(c->stream, pos, vel, acc, lay.n, dt));
-    bh_status s = theta >= 0.0
-                      ? force_tree(c, lay, pos, mass, softening, eps, theta, acc, nullptr)
-                      : force_direct(c, pos, mass, softening, eps, acc, nullptr, lay.n,
-                                     c->cfg.precision);
+    // a scene that one block builds is kicked and drifted there
+    const bool moved = theta >= 0.0 && bhx::one_block_build(lay);
+    const bhx::Advance adv{pos, vel, acc, dt, 0};
+    if (!moved) BHX_HIP(c, bhx::launch_kick_drift(c->stream, pos, vel, acc, lay.n, dt));
+    if (theta >= 0.0)  // the walk makes the second kick
+        return force_tree(c, lay, pos, mass, softening, eps, theta, acc, nullptr, nullptr,
+                          Kick{vel, 0.5 * dt}, moved ? &adv : nullptr);
+    bh_status s = force_direct(c, pos, mass, softening, eps, acc, nullptr, lay.n, c->cfg.precision);
     if (s) return s;
     BHX_HIP(c, bhx::launch_kick(c->stream, vel, acc, lay.n, dt));
     return BH_OK;
@@ -444,7 +458,7 @@ bool sorted_state(const bhx::Layout &lay, double theta, int32_t nsteps, bool gra
 
 // One kick-drift-kick step on the sorted state: the first kick and the drift
 // run in the build's bounding-box pass, the walk writes the accelerations in
-// sorted order and the second kick uses them there.
+// sorted order and makes the second kick there.
 bh_status kdk_step_state(bh_ctx *c, const bhx::Layout &lay, double softening, bool use_eps,
                          double theta, double dt)
 {
@@ -459,12 +473,9 @@ bh_status kdk_step_state(bh_ctx *c, const bhx::Layout &lay, double softening, bo
     }
     st = record(c, 1);
     if (st) return st;
-    st = walk(c, w, lay, softening, use_eps, theta, w.tacc, nullptr, true);
+    st = walk(c, w, lay, softening, use_eps, theta, w.tacc, nullptr, true, Kick{w.tvel, 0.5 * dt});
     if (st) return st;
-    st = record(c, 2);
-    if (st) return st;
-    BHX_HIP(c, bhx::launch_kick(c->stream, w.tvel, w.tacc, lay.n, dt));
-    return BH_OK;
+    return record(c, 2);
 }
 
 // One step of either kind.
@@ -868,18 +879,22 @@ bh_status bh_step_euler(bh_ctx *c, double *pos, double *vel, const double *mass,
     if (every < 1) return fail(c, BH_E_INVALID, "every < 1");
     if (n > 0 && (!vel || !acc)) return fail(c, BH_E_INVALID, "NULL vel or acc");
     if (n == 0) return BH_OK;
-    // substeps in runs of `every` (one fused launch each), gravity after each
-    // full run
+    // substeps in runs of `every` (one launch each, or made by the build of the
+    // gravity that follows where one block builds), gravity after each full run
+    const bhx::Layout lay = single(n);
+    const bool fused = theta >= 0.0 && bhx::one_block_build(lay);
     for (int32_t done = 0; done < nsteps;) {
         const int32_t k = nsteps - done < every ? nsteps - done : every;
-        BHX_HIP(c, bhx::launch_euler_substeps(c->stream, pos, vel, acc, n, dt, k));
         done += k;
-        if (k == every) {
-            s = theta >= 0.0 ? force_tree(c, single(n), pos, mass, softening, eps, theta, acc, nullptr)
-                             : force_direct(c, pos, mass, softening, eps, acc, nullptr, n,
-                                            c->cfg.precision);
-            if (s) return s;
-        }
+        const bhx::Advance adv{pos, vel, acc, dt, k};
+        if (!fused || k < every)
+            BHX_HIP(c, bhx::launch_euler_substeps(c->stream, pos, vel, acc, n, dt, k));
+        if (k < every) break;
+        s = theta >= 0.0 ? force_tree(c, lay, pos, mass, softening, eps, theta, acc, nullptr,
+                                      nullptr, Kick{}, fused ? &adv : nullptr)
+                         : force_direct(c, pos, mass, softening, eps, acc, nullptr, n,
+                                        c->cfg.precision);
+        if (s) return s;
     }
     return BH_OK;
 }
@@ -988,10 +1003,13 @@ bh_status bh_leapfrog_vjp(bh_ctx *c, const double *pos, const double *vel, const
         double *x_out = traj + (int64_t)k * n3;
         BHX_HIP(c, bhx::launch_kick_drift_to(c->stream, x_in, aw.vwork, aw.awork, x_out, n, dt));
         const Workspace slot = keep ? bhx::slot_view(c->w, aw.trees, k) : c->w;
-        s = theta >= 0.0 ? force_tree(c, single(n), x_out, mass, softening, eps, theta, aw.awork,
-                                      nullptr, keep ? &slot : nullptr)
-                         : force_direct(c, x_out, mass, softening, eps, aw.awork, nullptr, n,
-                                        c->cfg.precision);
+        if (theta >= 0.0) {  // the walk makes the second kick
+            s = force_tree(c, single(n), x_out, mass, softening, eps, theta, aw.awork, nullptr,
+                           keep ? &slot : nullptr, Kick{aw.vwork, 0.5 * dt});
+            if (s) return s;
+            continue;
+        }
+        s = force_direct(c, x_out, mass, softening, eps, aw.awork, nullptr, n, c->cfg.precision);
         if (s) return s;
         BHX_HIP(c, bhx::launch_kick(c->stream, aw.vwork, aw.awork, n, dt));
     }

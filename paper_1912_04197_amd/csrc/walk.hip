@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
     const SceneBox *__restrict__ box, const int32_t *__restrict__ groups, int64_t n,
     int ngroups, int per_xcd, double th2, double eps0sq, double G,
     double *__restrict__ acc, double *__restrict__ phi, int32_t *__restrict__ counts,
-    bool acc_sorted)
+    bool acc_sorted, double *__restrict__ kick_vel, double kick_h)
 {
     static_assert(GB == 64 || GB == 32 || GB == 16, "group size");
     constexpr int LPB = 64 / GB;  // lanes per body
@@ -460,9 +460,10 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
     }
     const int64_t o = idx[s];
     const int64_t oa = acc_sorted ? s : o;  // where acc and phi go
-    acc[3 * oa] = G * ax;
-    acc[3 * oa + 1] = G * ay;
-    acc[3 * oa + 2] = G * az;
+    const double a[3] = {G * ax, G * ay, G * az};
+    for (int k = 0; k < 3; k++) acc[3 * oa + k] = a[k];
+    if (kick_vel)
+        for (int k = 0; k < 3; k++) kick_vel[3 * oa + k] = fma(kick_h, a[k], kick_vel[3 * oa + k]);
     if (PHI) phi[oa] = G * ph;
     if (CNT) {
         counts[2 * o] = cnode;
@@ -479,7 +480,8 @@ hipError_t launch_t(const Workspace &w, hipStream_t s, const WalkParams &p)
     k_walk<PREC, PEPS, PHI, CNT, GB, QUAD>
         <<<p.groups ? ngroups : 8 * per_xcd, 64 * (1 + kEvals), 0, s>>>(
             w.body, w.beps2, w.ninfo, w.nmom, w.neps2, p.nquad, w.idx[0], w.box, p.groups, p.n,
-            ngroups, per_xcd, p.th2, p.eps0sq, p.G, p.acc, p.phi, p.counts, p.acc_sorted);
+            ngroups, per_xcd, p.th2, p.eps0sq, p.G, p.acc, p.phi, p.counts, p.acc_sorted,
+            p.kick_vel, p.kick_h);
     return hipGetLastError();
 }
 
