@@ -61,16 +61,25 @@ struct SceneBox {
     double s2[kLevels];   // squared cell side per level
 };
 
+constexpr int kDeepSlots = 16;
 // Tree header, written on the device by the build and read by later kernels,
 // so a whole force evaluation runs without host round trips.
 struct TreeHeader {
     int32_t level_count[kLevels + 1];  // nodes created per level (all scenes)
     uint32_t *status;                  // ST_* words, set at creation
-    int32_t cell_max;                  // most bodies in one node of level kHintLevel
+    int32_t cell_max[kLevels];         // most bodies in one node per level (0: not looked at)
+    int32_t inner_top;                 // entries of Workspace::inner in use
+    alignas(128) int32_t deep_count;   // nodes k_build_subtrees has created
+    // and how many of them per level, spread over lines of their own (all blocks
+    // adding to one line took longer than the rest of that kernel); added to
+    // level_count, and cleared, by the kernel that reports the launch hints
+    struct alignas(128) {
+        int32_t level[kLevels];
+    } deep[kDeepSlots];
 };
 // The level whose largest node the build reports for the choice of sort.
 constexpr int kHintLevel = 5;
-constexpr int kHintWords = 2 + kLevels;  // pinned launch-hint words of a workspace
+constexpr int kHintWords = 2 + 2 * kLevels;  // pinned launch-hint words of a workspace
 constexpr int kStatusAt = 64;  // the status words follow, on a line of their own
 static_assert(kHintWords <= kStatusAt, "pinned words");
 // The levels 1..kPrefixLevels of a single scene's tree are read off the
@@ -230,6 +239,7 @@ struct Workspace {
     double *seps2 = nullptr;          // [n_cap]
     uint32_t *scidx = nullptr;        // [n_cap]
     NodeInfo *ninfo = nullptr;
+    int32_t *inner = nullptr;     // [node_cap] k_build_subtrees' lists beyond LDS
     NodeMom *nmom = nullptr;
     double *neps2 = nullptr;
     double *nquad = nullptr;      // [node_cap][6] quadrupoles, only with BH_FLAG_QUAD
@@ -244,7 +254,9 @@ struct Workspace {
     // next build launches the levels down to one below it one by one and the
     // rest in one block), [1] the most bodies in one node of level kHintLevel
     // (which picks the next build's sort), [2 + l] its node count on level l
-    // (which picks how level l is split), kHintWords words in all.
+    // (which picks how level l is split), [2 + kLevels + l] the most bodies in
+    // one node of level l (0 or less: not known; which picks the level below
+    // which subtrees are built whole), kHintWords words in all.
     int32_t *depth_host = nullptr;
     int32_t *depth_dev = nullptr;  // the same memory as the device sees it
     // the ST_* words, kStatusAt words into the same allocation
@@ -313,6 +325,9 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
 // the pinned hints, frozen in a captured graph. Either sort gives the same
 // order; the choice only affects speed.
 bool bucket_sort_hint(const Workspace &w, const Layout &lay);
+// The level from which the next build of `lay` builds whole subtrees in one
+// launch, or -1; a host read of the pinned hints like bucket_sort_hint.
+int subtree_hint(const Workspace &w, const Layout &lay);
 // scene_of[i] = scene of body i, from device offsets of n_scenes scenes
 hipError_t launch_scene_of(hipStream_t s, const int64_t *offsets, int n_scenes,
                            uint16_t *scene_of);

@@ -52,6 +52,7 @@ struct bh_ctx {
     bool capturing = false;
     int gdepth = -1;  // depth hint the captured step's build was launched with
     int gbucket = -1; // sort the captured step's build was launched with (bucket_sort_hint)
+    int gsub = -1;    // level of its subtrees (subtree_hint)
 };
 
 namespace {
@@ -138,7 +139,7 @@ void free_ws(Workspace &w)
     void *ptrs[] = {w.keys[0], w.keys[1], w.idx[0],  w.idx[1],      w.sort_counts,
                     w.sort_totals, w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.box,
                     w.hdr, w.counts, w.scratch, w.red_part, w.nquad, w.dpart,
-                    w.tvel, w.tacc, w.sbody, w.svel, w.seps2, w.scidx, w.prefix_mark};
+                    w.tvel, w.tacc, w.sbody, w.svel, w.seps2, w.scidx, w.prefix_mark, w.inner};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (w.depth_host) (void)hipHostFree(w.depth_host);
@@ -528,7 +529,9 @@ bh_status run_steps(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
     const bool deeper = depth_now >= 0 && (c->gdepth < 0 || depth_now > c->gdepth + 1);
     // likewise when the hints now pick the other sort (same order, other speed)
     const int bucket_now = bhx::bucket_sort_hint(c->w, lay) ? 1 : 0;
-    if (!c->gexec || key != c->gkey || deeper || bucket_now != c->gbucket) {
+    // or another level for the subtrees that are built whole
+    const int sub_now = bhx::subtree_hint(c->w, lay);
+    if (!c->gexec || key != c->gkey || deeper || bucket_now != c->gbucket || sub_now != c->gsub) {
         if (c->gexec) {
             (void)hipGraphExecDestroy(c->gexec);
             c->gexec = nullptr;
@@ -542,6 +545,7 @@ bh_status run_steps(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
         c->capturing = true;
         c->gdepth = depth_now;
         c->gbucket = bucket_now;
+        c->gsub = sub_now;
         bh_status s = any_step(c, state, lay, pos, vel, mass, softening, eps, theta, dt, acc);
         c->capturing = false;
         c->stream = caller;
@@ -704,6 +708,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     A(dalloc(&w.seps2, n));
     A(dalloc(&w.scidx, n));
     A(dalloc(&w.ninfo, node_cap));
+    A(dalloc(&w.inner, node_cap));
     A(dalloc(&w.prefix_mark, bhx::kPrefixCells));
     if (r == hipSuccess)
         r = hipMemsetD32((hipDeviceptr_t)w.prefix_mark, INT32_MAX, bhx::kPrefixCells);

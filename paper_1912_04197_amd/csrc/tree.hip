@@ -257,6 +257,15 @@ __device__ inline void root_cube(SceneBox &b, const double lo[3], const double h
     }
 }
 
+// A header for a build about to create `roots` root nodes.
+__device__ inline void reset_header(TreeHeader *__restrict__ hdr, int32_t roots)
+{
+    for (int l = 0; l <= kLevels; l++) hdr->level_count[l] = l == 0 ? roots : 0;
+    for (int l = 0; l < kLevels; l++) hdr->cell_max[l] = 0;
+    hdr->deep_count = 0;
+    hdr->inner_top = 0;
+}
+
 // Root cube of a scene into `out` from the reduced box encodings of `in`
 // (the same SceneBox or a copy); a scene without bodies gets the cube at 0.
 __device__ inline void scene_root_cube(SceneBox &out, const SceneBox &in, bool any)
@@ -280,9 +289,7 @@ __global__ __launch_bounds__(256) void k_box_final(SceneBox *__restrict__ box, i
 #pragma clang fp contract(off)
     const int sc = blockIdx.x * 256 + threadIdx.x;
     if (sc == 0) {
-        for (int l = 0; l <= kLevels; l++) hdr->level_count[l] = 0;
-        hdr->level_count[0] = n > 0 ? n_scenes : 0;
-        hdr->cell_max = 0;
+        reset_header(hdr, n > 0 ? n_scenes : 0);
     }
     if (sc >= n_scenes) return;
     const int64_t first = offsets ? offsets[sc] : 0, end = offsets ? offsets[sc + 1] : n;
@@ -411,9 +418,7 @@ __global__ __launch_bounds__(kSortThreads) void k_keys_hist(const double *__rest
         scene_root_cube(b, box[0], true);
         if (blockIdx.x == 0) {
             scene_root_cube(box[0], box[0], true);
-            for (int l = 0; l <= kLevels; l++) hdr->level_count[l] = 0;
-            hdr->level_count[0] = 1;
-            hdr->cell_max = 0;
+            reset_header(hdr, 1);
             ninfo[0] = NodeInfo{0, (int32_t)n, -1, 0};
         }
     }
@@ -989,9 +994,9 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     const int o = threadIdx.x & 7, gl = lane & ~7;
     const int shift = 60 - 3 * level;  // bits of the child octant at level + 1
-    // level kHintLevel: the block's largest node, merged into cell_max once
+    // the block's largest node, merged into cell_max once
     int32_t cmax = 0;
-    if (level == kHintLevel && threadIdx.x == 0) s_cmax = 0;
+    if (threadIdx.x == 0) s_cmax = 0;
     const uint32_t chunk = blockDim.x >> 3;
     for (int64_t b0 = b_first; b0 < cnt; b0 += stride) {
         uint32_t nlist;  // nodes of the step to give eight lanes each
@@ -1002,7 +1007,7 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
             if (g < cnt) {
                 const int32_t c = ninfo[beg + (int32_t)g].count;
                 splits = c > leaf && level < kMaxLevel;
-                if (level == kHintLevel) cmax = max(cmax, c);
+                cmax = max(cmax, c);
             }
             const uint64_t sb = __ballot(splits);
             if (lane == 0) s_wtot[wave] = (uint32_t)__popcll(sb);
@@ -1029,7 +1034,7 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
             else
                 k = beg + (int32_t)(b0 + gl_node);
             const NodeInfo info = ninfo[k];
-            if (!compact && level == kHintLevel && live) cmax = max(cmax, info.count);
+            if (!compact && live) cmax = max(cmax, info.count);
             const bool split = live && info.count > leaf && level < kMaxLevel;
             int32_t start;
             if (info.count <= kLinearSplit) {
@@ -1098,13 +1103,11 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
         }
         if constexpr (compact) __syncthreads();  // s_list is rewritten by the next step
     }
-    if (level == kHintLevel) {  // the same on every thread
-        for (int off = 32; off > 0; off >>= 1) cmax = max(cmax, __shfl_xor(cmax, off));
-        __syncthreads();
-        if (lane == 0 && cmax > 0) atomicMax(&s_cmax, cmax);
-        __syncthreads();
-        if (threadIdx.x == 0 && s_cmax > 0) atomicMax(cell_max, s_cmax);
-    }
+    for (int off = 32; off > 0; off >>= 1) cmax = max(cmax, __shfl_xor(cmax, off));
+    __syncthreads();
+    if (lane == 0 && cmax > 0) atomicMax(&s_cmax, cmax);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_cmax > 0) atomicMax(cell_max, s_cmax);
 }
 
 template <bool compact>
@@ -1114,7 +1117,7 @@ __global__ __launch_bounds__(1024) void k_build_level(int level, const uint64_t 
                                                       int64_t node_cap, int leaf)
 {
     const int64_t per_step = compact ? blockDim.x : blockDim.x >> 3;  // nodes per block step
-    build_nodes<compact>(level, keys, hdr->level_count, hdr->status, &hdr->cell_max, ninfo,
+    build_nodes<compact>(level, keys, hdr->level_count, hdr->status, &hdr->cell_max[level], ninfo,
                          node_cap, leaf, (int64_t)blockIdx.x * per_step,
                          (int64_t)gridDim.x * per_step);
 }
@@ -1129,7 +1132,7 @@ __device__ inline void build_levels_block(int from, int upto, const uint64_t *__
 {
     for (int level = from; level < upto; level++) {
         if (scnt[level] == 0) break;
-        build_nodes<compact>(level, keys, scnt, hdr->status, &hdr->cell_max, ninfo, node_cap, leaf,
+        build_nodes<compact>(level, keys, scnt, hdr->status, &hdr->cell_max[level], ninfo, node_cap, leaf,
                              0, compact ? blockDim.x : blockDim.x >> 3);
         __syncthreads();
     }
@@ -1419,8 +1422,56 @@ struct MomentSum {
     }
 };
 
-// The moments of every node of `level`: of an internal node from its
-// children, of a leaf from its bodies.
+// The moments of node k (on `level`): of an internal node from its children (G
+// loaded at a time), of a leaf from its bodies.
+template <int G = 8>
+__device__ inline void node_moments(int32_t k, const NodeInfo &info, int level,
+                                    const Body *__restrict__ body,
+                                    const double *__restrict__ beps2,
+                                    const uint64_t *__restrict__ keys,
+                                    const SceneBox *__restrict__ box, NodeMom *nmom, double *neps2,
+                                    double *nquad, int use_eps)
+{
+#pragma clang fp contract(off)
+    MomentSum sum;
+    if (info.child0 < 0)
+        sum.leaf(body, beps2, info, use_eps);
+    else
+        sum.children<G>(nmom, neps2, info, use_eps);
+    double e2;
+    const NodeMom out = sum.moments(level, info.first, keys, box[node_scene(info)], use_eps, e2);
+    nmom[k] = out;
+    if (use_eps) neps2[k] = e2;
+    if (!nquad) return;
+    // traceless quadrupole about the centre of mass: from the bodies of a leaf,
+    // from the children by the parallel-axis shift
+    double q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    auto add = [&](double dx, double dy, double dz, double m) {
+        const double d2 = dx * dx + dy * dy + dz * dz;
+        q[0] += m * (3.0 * dx * dx - d2);
+        q[1] += m * (3.0 * dy * dy - d2);
+        q[2] += m * (3.0 * dz * dz - d2);
+        q[3] += m * 3.0 * dx * dy;
+        q[4] += m * 3.0 * dx * dz;
+        q[5] += m * 3.0 * dy * dz;
+    };
+    if (info.child0 < 0) {
+        for (int32_t s = info.first; s < info.first + info.count; s++) {
+            const Body b = body[s];
+            add(b.x - out.x, b.y - out.y, b.z - out.z, b.m);
+        }
+    } else {
+        const int nch = node_nchild(info);
+        for (int32_t c = info.child0; c < info.child0 + nch; c++) {
+            const NodeMom cm = nmom[c];
+            for (int a = 0; a < 6; a++) q[a] += nquad[6 * (int64_t)c + a];
+            add(cm.x - out.x, cm.y - out.y, cm.z - out.z, cm.m);
+        }
+    }
+    for (int a = 0; a < 6; a++) nquad[6 * (int64_t)k + a] = q[a];
+}
+
+// The moments of every node of `level`.
 __device__ inline void moments_nodes(int level, const int32_t *counts,
                                      const NodeInfo *__restrict__ ninfo,
                                      const Body *__restrict__ body,
@@ -1431,68 +1482,237 @@ __device__ inline void moments_nodes(int level, const int32_t *counts,
                                      int64_t node_cap, int use_eps, int64_t g_first,
                                      int64_t stride)
 {
-#pragma clang fp contract(off)
     int32_t beg, cnt;
     level_range(counts, level, node_cap, &beg, &cnt);
     for (int64_t g = g_first; g < cnt; g += stride) {
         const int32_t k = beg + (int32_t)g;
-        const NodeInfo info = ninfo[k];
-        MomentSum sum;
-        if (info.child0 < 0)
-            sum.leaf(body, beps2, info, use_eps);
-        else
-            sum.children(nmom, neps2, info, use_eps);
-        double e2;
-        const NodeMom out =
-            sum.moments(level, info.first, keys, box[node_scene(info)], use_eps, e2);
-        nmom[k] = out;
-        if (use_eps) neps2[k] = e2;
-        if (nquad) {
-            // traceless quadrupole about the centre of mass: from the bodies
-            // of a leaf, from the children by the parallel-axis shift
-            double q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            auto add = [&](double dx, double dy, double dz, double m) {
-                const double d2 = dx * dx + dy * dy + dz * dz;
-                q[0] += m * (3.0 * dx * dx - d2);
-                q[1] += m * (3.0 * dy * dy - d2);
-                q[2] += m * (3.0 * dz * dz - d2);
-                q[3] += m * 3.0 * dx * dy;
-                q[4] += m * 3.0 * dx * dz;
-                q[5] += m * 3.0 * dy * dz;
-            };
-            if (info.child0 < 0) {
-                for (int32_t s = info.first; s < info.first + info.count; s++) {
-                    const Body b = body[s];
-                    add(b.x - out.x, b.y - out.y, b.z - out.z, b.m);
-                }
-            } else {
-                const int nch = node_nchild(info);
-                for (int32_t c = info.child0; c < info.child0 + nch; c++) {
-                    const NodeMom cm = nmom[c];
-                    for (int a = 0; a < 6; a++) q[a] += nquad[6 * (int64_t)c + a];
-                    add(cm.x - out.x, cm.y - out.y, cm.z - out.z, cm.m);
-                }
-            }
-            for (int a = 0; a < 6; a++) nquad[6 * (int64_t)k + a] = q[a];
-        }
+        node_moments(k, ninfo[k], level, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
     }
 }
 
-// The launch hints of the build just finished, into pinned host memory:
-// its deepest non-empty level, its largest level-kHintLevel node and its
-// node count per level.
-__device__ inline void report_hints(const TreeHeader *__restrict__ hdr, int32_t *out)
+// --------------------------------------------------------- 5 and 6, subtrees
+
+// max in place; most calls find a value that is already as large.
+__device__ inline void raise_max(int32_t *p, int32_t v)
 {
-    int d = 0;
-    for (int l = 1; l <= kMaxLevel; l++)
-        if (hdr->level_count[l] > 0) d = l;
-    out[0] = d;
-    out[1] = hdr->cell_max;
-    for (int l = 0; l < kLevels; l++) out[2 + l] = hdr->level_count[l];
+    if (v > *(const volatile int32_t *)p) atomicMax(p, v);
+}
+
+// Everything below level `level0`, whose nodes exist: each block takes
+// kSubNodes of them at a time, splits their subtrees level by level and forms
+// the moments of all their nodes bottom-up, so that the levels from level0 down
+// take one launch whatever their depth instead of two each. Bound by latency (a
+// block's dependent loads, two barriers a step and the atomic on the node count
+// that all blocks share): at 2^20 bodies and leaf 4 it takes 87 us where the
+// launches of those levels and their moments took 130, at 50,000 (leaf 8) 11
+// instead of 24; steps of 40,000 to 2^20 bodies are 1 to 5 % shorter. 256 threads
+// a block are 1 % slower at 2^20 (more atomics), 1024 the same. The
+// launches above stop at the first level whose nodes held at most kSubBodies
+// bodies in the previous build, which keeps a block's work even; any node is
+// handled, a larger one more slowly.
+//
+// A step splits 64 nodes, eight lanes each as in build_nodes, with one atomic for
+// the numbers of all their children: nodes below level0 are numbered as they
+// are made, level0's follow by level. A child that is a leaf gets its moments at
+// once; one that splits goes on the block's list, which holds the splitting
+// nodes in level order and is walked backwards for their moments. The list is in
+// LDS and, beyond kSubList entries, in `inner`, of which the block then reserves
+// what its subtrees can need (their levels times their bodies / (leaf + 1)).
+constexpr int kSubThreads = 512;
+constexpr int kSubNodes = kSubThreads / 8;
+constexpr int kSubBodies = 256;  // 1024: 64 uneven scenes take 15 % longer a step; 64: 4 % at 2^20
+constexpr int kSubList = 2048;
+__global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
+    int level0, const uint64_t *__restrict__ keys, TreeHeader *__restrict__ hdr, NodeInfo *ninfo,
+    int64_t node_cap, int leaf, const Body *__restrict__ body, const double *__restrict__ beps2,
+    const SceneBox *__restrict__ box, NodeMom *nmom, double *neps2, double *nquad, int use_eps,
+    int32_t *inner)
+{
+    static_assert(kSubNodes <= 64, "one wave lists the subtrees' roots");
+    constexpr int W = kSubThreads / 64;
+    __shared__ int32_t list[kSubList];
+    __shared__ int32_t lbeg[kLevels + 2];     // first list entry per level, from level0
+    __shared__ int32_t made[kLevels + 1];     // nodes made per level
+    __shared__ uint32_t s_wtot[2][W], s_wdeep[2][W];
+    __shared__ int32_t s_base[2], s_inner, s_need, s_hint;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int o = tid & 7, gl = lane & ~7;
+    int32_t beg, cnt;
+    level_range(hdr->level_count, level0, node_cap, &beg, &cnt);
+    const int32_t deep0 = beg + cnt;
+    if (tid <= kLevels) made[tid] = 0;
+    if (tid == 0) s_hint = 0;
+    auto entry = [&](int i) { return i < kSubList ? list[i] : inner[s_inner + i - kSubNodes]; };
+    for (int64_t g0 = (int64_t)blockIdx.x * kSubNodes; g0 < cnt;
+         g0 += (int64_t)gridDim.x * kSubNodes) {
+        __syncthreads();  // the previous chunk's list is read no more
+        if (wave == 0) {
+            const bool mine = lane < kSubNodes && g0 + lane < cnt;
+            const int32_t k = beg + (int32_t)g0 + lane;
+            NodeInfo info{0, 0, -1, 0};
+            if (mine) info = ninfo[k];
+            const bool split = info.count > leaf && level0 < kMaxLevel;
+            const uint64_t sb = __ballot(split);
+            if (split) list[lanes_below(sb)] = k;
+            int32_t bodies = split ? info.count : 0, most = info.count;
+            for (int off = 32; off > 0; off >>= 1) {
+                bodies += __shfl_xor(bodies, off);
+                most = max(most, __shfl_xor(most, off));
+            }
+            if (lane == 0) {
+                lbeg[0] = 0;
+                lbeg[1] = __popcll(sb);
+                s_inner = -1;
+                s_need = (kMaxLevel - level0) * (bodies / (leaf + 1));
+                raise_max(&hdr->cell_max[level0], most);
+            }
+            if (mine && !split)
+                node_moments<4>(k, info, level0, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
+        }
+        __syncthreads();
+        int d = 0, hi = lbeg[1], par = 0;
+        for (int lo = 0; lo < hi; d++) {  // the list entries of level level0 + d
+            const int level = level0 + d, shift = 60 - 3 * level;
+            int top = hi;        // end of the list
+            int32_t total = 0;   // children of this level's nodes
+            for (int f0 = lo; f0 < hi; f0 += kSubThreads / 8, par ^= 1) {
+                const int gi = f0 + (tid >> 3);
+                const bool live = gi < hi;
+                const int32_t id = entry(live ? gi : f0);
+                const NodeInfo info = ninfo[id];
+                const int32_t count = live ? info.count : 0;
+                int32_t start;
+                if (info.count <= kLinearSplit) {
+                    uint64_t hist = 0;  // one byte per octant
+                    for (int32_t j = o; j < count; j += 8)
+                        hist += 1ull << (8 * (int)((keys[info.first + j] >> shift) & 7ull));
+                    hist += __shfl_xor(hist, 1, 8);
+                    hist += __shfl_xor(hist, 2, 8);
+                    hist += __shfl_xor(hist, 4, 8);
+                    const uint64_t below = o == 0 ? 0ull : hist & (~0ull >> (64 - 8 * o));
+                    start = info.first + (int32_t)((below * 0x0101010101010101ull) >> 56);
+                } else {
+                    int32_t a = info.first, b = info.first + count;
+                    while (a < b) {
+                        const int32_t mid = (a + b) >> 1;
+                        if ((int)((keys[mid] >> shift) & 7ull) < o)
+                            a = mid + 1;
+                        else
+                            b = mid;
+                    }
+                    start = a;
+                }
+                int32_t end = __shfl_down(start, 1, 8);
+                if (o == 7) end = info.first + count;
+                BHX_CHECK(!live || (start >= info.first && start <= end &&
+                                    end <= info.first + info.count),
+                          CK_PARTITION);
+                const int32_t nb = end - start;
+                const bool child = live && nb > 0;
+                const bool deeper = child && nb > leaf && level + 1 < kMaxLevel;
+                const uint64_t cb = __ballot(child), sb = __ballot(deeper);
+                if (lane == 0) {
+                    s_wtot[par][wave] = (uint32_t)__popcll(cb);
+                    s_wdeep[par][wave] = (uint32_t)__popcll(sb);
+                }
+                __syncthreads();
+                uint32_t before = 0, btot = 0, dbefore = 0, dtot = 0;
+#pragma unroll
+                for (int w = 0; w < W; w++) {
+                    const uint32_t t = s_wtot[par][w], u = s_wdeep[par][w];
+                    if (w < wave) before += t, dbefore += u;
+                    btot += t;
+                    dtot += u;
+                }
+                if (tid == 0) {
+                    s_base[par] = atomicAdd(&hdr->deep_count, (int32_t)btot);
+                    if (top + (int)dtot > kSubList && s_inner < 0)
+                        s_inner = atomicAdd(&hdr->inner_top, s_need);
+                }
+                __syncthreads();
+                const int64_t base = (int64_t)deep0 + s_base[par];
+                total += (int32_t)btot;
+                if (base + btot > node_cap) {  // the same on every thread
+                    if (tid == 0) flag_status(hdr->status, ST_CAPACITY);
+                    continue;
+                }
+                const int32_t cid = (int32_t)base + (int32_t)(before + lanes_below(cb));
+                const int32_t scene_bits = info.lvl_nch & (int32_t)0xffff0000;
+                if (child) {
+                    const NodeInfo ci{start, nb, -1, (level + 1) | scene_bits};
+                    ninfo[cid] = ci;
+                    if (level + 1 == kHintLevel) atomicMax(&s_hint, nb);
+                    if (!deeper)
+                        node_moments<4>(cid, ci, level + 1, body, beps2, keys, box, nmom, neps2,
+                                     nquad, use_eps);
+                }
+                if (deeper) {
+                    const int at = top + (int)(dbefore + lanes_below(sb));
+                    if (at < kSubList)
+                        list[at] = cid;
+                    else
+                        inner[s_inner + at - kSubNodes] = cid;
+                }
+                if (live && o == 0) {
+                    ninfo[id].child0 = cid;
+                    ninfo[id].lvl_nch =
+                        level | ((int)__popcll((cb >> gl) & 0xffull) << 8) | scene_bits;
+                }
+                top += (int)dtot;
+            }
+            if (tid == 0) {
+                made[level + 1] += total;
+                lbeg[d + 2] = top;
+            }
+            __syncthreads();
+            lo = hi;
+            hi = top;
+        }
+        for (d--; d >= 0; d--) {
+            for (int i = lbeg[d] + tid; i < lbeg[d + 1]; i += kSubThreads) {
+                const int32_t id = entry(i);
+                node_moments<4>(id, ninfo[id], level0 + d, body, beps2, keys, box, nmom, neps2, nquad,
+                             use_eps);
+            }
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    if (tid < kLevels && made[tid] > 0)
+        atomicAdd(&hdr->deep[blockIdx.x % kDeepSlots].level[tid], made[tid]);
+    if (tid == 0) raise_max(&hdr->cell_max[kHintLevel], s_hint);
+}
+
+// The end of a build, by one wave: the nodes that k_build_subtrees made and
+// counted apart are added to their levels, and the launch hints go to pinned
+// host memory: the deepest non-empty level, the largest level-kHintLevel node, and
+// the node count and the largest node looked at per level.
+__device__ inline void report_hints(TreeHeader *__restrict__ hdr, int32_t *out)
+{
+    const int l = threadIdx.x & 63;
+    int32_t c = 0, most = 0;
+    if (l < kLevels) {
+        c = hdr->level_count[l];
+        most = hdr->cell_max[l];
+#pragma unroll
+        for (int k = 0; k < kDeepSlots; k++) {
+            c += hdr->deep[k].level[l];
+            hdr->deep[k].level[l] = 0;
+        }
+        hdr->level_count[l] = c;
+    }
+    const uint64_t some = __ballot(c > 0) & ~1ull;
+    if (!out) return;
+    if (l == 0) out[0] = some ? 63 - __builtin_clzll(some) : 0;
+    if (l == kHintLevel) out[1] = most;
+    if (l < kLevels) {
+        out[2 + l] = c;
+        out[2 + kLevels + l] = most;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_moments_level(
-    int level, const TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
+    int level, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const uint64_t *__restrict__ keys, const SceneBox *__restrict__ box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
@@ -1502,14 +1722,13 @@ __global__ __launch_bounds__(256) void k_moments_level(
                   node_cap, use_eps, (int64_t)blockIdx.x * 256 + threadIdx.x,
                   (int64_t)gridDim.x * 256);
     // the root level reports the launch hints for the next build
-    if (level == 0 && depth_out && blockIdx.x == 0 && threadIdx.x == 0)
-        report_hints(hdr, depth_out);
+    if (level == 0 && blockIdx.x == 0 && threadIdx.x < 64) report_hints(hdr, depth_out);
 }
 
 // Levels from-1 down to 0 of a single scene in one block, then the depth
 // report of k_moments_level at level 0.
 __global__ __launch_bounds__(1024) void k_moments_head(
-    int from, const TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
+    int from, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const uint64_t *__restrict__ keys, const SceneBox *__restrict__ box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
@@ -1524,7 +1743,7 @@ __global__ __launch_bounds__(1024) void k_moments_head(
                       threadIdx.x, 1024);
         __syncthreads();
     }
-    if (depth_out && threadIdx.x == 0) report_hints(hdr, depth_out);
+    if (threadIdx.x < 64) report_hints(hdr, depth_out);
 }
 
 // The deep levels in one block (they hold few nodes): with `split`, first
@@ -1994,7 +2213,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         depth_out[0] = depth;
         depth_out[1] = -1;  // no sort hint from a one-block build
     }
-    if (depth_out && tid < kLevels) depth_out[2 + tid] = scnt[tid];
+    if (depth_out && tid < kLevels) {
+        depth_out[2 + tid] = scnt[tid];
+        depth_out[2 + kLevels + tid] = -1;
+    }
 }
 
 inline unsigned blocks_for(int64_t items, int per_block, unsigned cap)
@@ -2112,8 +2334,11 @@ bool enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, con
 // levels 0..deep-1 get a launch each (the deeper ones share one block), and
 // with `prefix` a single scene's levels 1..kPrefixLevels are read off the
 // sorted keys instead (the gather writes the marks k_prefix_levels reads).
+// With sub >= 0 the levels below it, and its moments, are left to one launch
+// of k_build_subtrees: sub is the first level (from the first that is launched) whose
+// nodes held at most kSubBodies bodies in the previous build.
 struct LevelPlan {
-    int deep = kMaxLevel, prev = -1;
+    int deep = kMaxLevel, prev = -1, sub = -1;
     bool prefix = false;
 };
 
@@ -2125,6 +2350,15 @@ LevelPlan plan_levels(const Workspace &w, const Layout &lay)
         if (p.prev >= 0 && p.prev + 1 < p.deep) p.deep = p.prev + 1;
     }
     p.prefix = lay.n_scenes == 1 && p.deep > kPrefixLevels && w.prefix_mark != nullptr;
+    if (p.prev >= 0) {
+        const volatile int32_t *most = w.depth_host + 2 + kLevels;
+        // (not the root's: its moments launch reports the hints)
+        for (int l = p.prefix ? kPrefixLevels : 1; l < kMaxLevel && most[l] > 0; l++)
+            if (most[l] <= kSubBodies) {
+                p.sub = l;
+                break;
+            }
+    }
     return p;
 }
 
@@ -2141,7 +2375,7 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     // 0..head-1, at most 585 nodes) in one block too. (Splitting the top
     // levels in one block was measured slower: its binary searches over all
     // bodies run four passes deep there.) The split only affects speed.
-    const int deep = plan.deep, prev = plan.prev;
+    const int deep = plan.sub >= 0 ? plan.sub : plan.deep, prev = plan.prev;
     const volatile int32_t *hint = w.depth_host;
     const int head = ns == 1 ? (deep < 4 ? deep : 4) : 0;
     // one scene: levels 1..kPrefixLevels from the marks of the gather in one
@@ -2167,11 +2401,19 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
             k_build_level<false>
                 <<<g, bs, 0, s>>>(level, w.keys[0], w.hdr, w.ninfo, w.node_cap, leaf);
     }
-    // the levels from `deep` down: their split and their moments in one block
     const int ue = use_eps ? 1 : 0;
-    k_moments_tail<<<1, 1024, 0, s>>>(deep, deep < kMaxLevel ? 1 : 0, w.keys[0], w.hdr, w.ninfo,
-                                      w.body, w.beps2, w.box, w.nmom, w.neps2, w.nquad,
-                                      w.node_cap, leaf, ue);
+    if (plan.sub >= 0) {
+        // as many blocks as the level's nodes need, by the previous build's count
+        const int64_t nodes = hint[2 + deep] > 0 ? (int64_t)hint[2 + deep] : 1;
+        k_build_subtrees<<<blocks_for(nodes, kSubNodes, 1u << 16), kSubThreads, 0, s>>>(
+            deep, w.keys[0], w.hdr, w.ninfo, w.node_cap, leaf, w.body, w.beps2, w.box, w.nmom,
+            w.neps2, w.nquad, ue, w.inner);
+    } else {
+        // the levels from `deep` down: their split and their moments in one block
+        k_moments_tail<<<1, 1024, 0, s>>>(deep, deep < kMaxLevel ? 1 : 0, w.keys[0], w.hdr,
+                                          w.ninfo, w.body, w.beps2, w.box, w.nmom, w.neps2,
+                                          w.nquad, w.node_cap, leaf, ue);
+    }
     for (int level = deep - 1; level >= head; level--) {
         const unsigned g = blocks_for(level_bound(level, n, ns), 256, 4096);
         k_moments_level<<<g, 256, 0, s>>>(level, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0], w.box,
@@ -2211,6 +2453,8 @@ bool bucket_sort_hint(const Workspace &w, const Layout &lay)
     const int cell = ((const volatile int32_t *)w.depth_host)[1];
     return cell >= 0 && cell <= kBucketMax;
 }
+
+int subtree_hint(const Workspace &w, const Layout &lay) { return plan_levels(w, lay).sub; }
 
 hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
                         const double *mass, const double *eps, int leaf, bool *bucket,
