@@ -708,7 +708,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     A(dalloc(&w.seps2, n));
     A(dalloc(&w.scidx, n));
     A(dalloc(&w.ninfo, node_cap));
-    A(dalloc(&w.inner, node_cap));
+    A(dalloc(&w.inner, node_cap + 1));  // the contact search's cell table: two words at least
     A(dalloc(&w.prefix_mark, bhx::kPrefixCells));
     if (r == hipSuccess)
         r = hipMemsetD32((hipDeviceptr_t)w.prefix_mark, INT32_MAX, bhx::kPrefixCells);
