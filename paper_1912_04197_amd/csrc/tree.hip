@@ -1422,30 +1422,28 @@ struct MomentSum {
     }
 };
 
-// The moments of node k (on `level`): of an internal node from its children (G
-// loaded at a time), of a leaf from its bodies.
-template <int G = 8>
-__device__ inline void node_moments(int32_t k, const NodeInfo &info, int level,
-                                    const Body *__restrict__ body,
+// A node's moments, mean eps^2 and (QUAD) quadrupole: of an internal node
+// from its children in cmom (G loaded at a time), ceps2 and cquad, of a leaf from its
+// bodies.
+template <bool QUAD, int G = 8>
+__device__ inline NodeMom node_sums(const NodeInfo &info, int level, const Body *__restrict__ body,
                                     const double *__restrict__ beps2,
                                     const uint64_t *__restrict__ keys,
-                                    const SceneBox *__restrict__ box, NodeMom *nmom, double *neps2,
-                                    double *nquad, int use_eps)
+                                    const SceneBox *__restrict__ box, const NodeMom *cmom,
+                                    const double *ceps2, const double *cquad, int use_eps,
+                                    double &e2, double *q)
 {
 #pragma clang fp contract(off)
     MomentSum sum;
     if (info.child0 < 0)
         sum.leaf(body, beps2, info, use_eps);
     else
-        sum.children<G>(nmom, neps2, info, use_eps);
-    double e2;
+        sum.children<G>(cmom, ceps2, info, use_eps);
     const NodeMom out = sum.moments(level, info.first, keys, box[node_scene(info)], use_eps, e2);
-    nmom[k] = out;
-    if (use_eps) neps2[k] = e2;
-    if (!nquad) return;
+    if constexpr (!QUAD) return out;
     // traceless quadrupole about the centre of mass: from the bodies of a leaf,
     // from the children by the parallel-axis shift
-    double q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int a = 0; a < 6; a++) q[a] = 0.0;
     auto add = [&](double dx, double dy, double dz, double m) {
         const double d2 = dx * dx + dy * dy + dz * dz;
         q[0] += m * (3.0 * dx * dx - d2);
@@ -1456,22 +1454,48 @@ __device__ inline void node_moments(int32_t k, const NodeInfo &info, int level,
         q[5] += m * 3.0 * dy * dz;
     };
     if (info.child0 < 0) {
-        for (int32_t s = info.first; s < info.first + info.count; s++) {
-            const Body b = body[s];
-            add(b.x - out.x, b.y - out.y, b.z - out.z, b.m);
+        const int32_t end = info.first + info.count;
+        for (int32_t s0 = info.first; s0 < end; s0 += 4) {
+            Body b[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) b[u] = body[s0 + u < end ? s0 + u : s0];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (s0 + u >= end) break;
+                add(b[u].x - out.x, b[u].y - out.y, b[u].z - out.z, b[u].m);
+            }
         }
     } else {
+        // (one child at a time: two or four are 1 to 3 % slower at 20,000 bodies)
         const int nch = node_nchild(info);
-        for (int32_t c = info.child0; c < info.child0 + nch; c++) {
-            const NodeMom cm = nmom[c];
-            for (int a = 0; a < 6; a++) q[a] += nquad[6 * (int64_t)c + a];
+        for (int64_t c = info.child0; c < info.child0 + nch; c++) {
+            const NodeMom cm = cmom[c];
+            for (int a = 0; a < 6; a++) q[a] += cquad[6 * c + a];
             add(cm.x - out.x, cm.y - out.y, cm.z - out.z, cm.m);
         }
     }
-    for (int a = 0; a < 6; a++) nquad[6 * (int64_t)k + a] = q[a];
+    return out;
+}
+
+// The same for node k of the node table.
+template <bool QUAD, int G = 8>
+__device__ inline void node_moments(int32_t k, const NodeInfo &info, int level,
+                                    const Body *__restrict__ body,
+                                    const double *__restrict__ beps2,
+                                    const uint64_t *__restrict__ keys,
+                                    const SceneBox *__restrict__ box, NodeMom *nmom, double *neps2,
+                                    double *nquad, int use_eps)
+{
+    double e2, q[6];
+    nmom[k] = node_sums<QUAD, G>(info, level, body, beps2, keys, box, nmom, neps2, nquad, use_eps,
+                                 e2, q);
+    if (use_eps) neps2[k] = e2;
+    if constexpr (QUAD)
+        for (int a = 0; a < 6; a++) nquad[6 * (int64_t)k + a] = q[a];
 }
 
 // The moments of every node of `level`.
+template <bool QUAD>
 __device__ inline void moments_nodes(int level, const int32_t *counts,
                                      const NodeInfo *__restrict__ ninfo,
                                      const Body *__restrict__ body,
@@ -1486,7 +1510,7 @@ __device__ inline void moments_nodes(int level, const int32_t *counts,
     level_range(counts, level, node_cap, &beg, &cnt);
     for (int64_t g = g_first; g < cnt; g += stride) {
         const int32_t k = beg + (int32_t)g;
-        node_moments(k, ninfo[k], level, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
+        node_moments<QUAD>(k, ninfo[k], level, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
     }
 }
 
@@ -1522,6 +1546,7 @@ constexpr int kSubThreads = 512;
 constexpr int kSubNodes = kSubThreads / 8;
 constexpr int kSubBodies = 256;  // 1024: 64 uneven scenes take 15 % longer a step; 64: 4 % at 2^20
 constexpr int kSubList = 2048;
+template <bool QUAD>
 __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
     int level0, const uint64_t *__restrict__ keys, TreeHeader *__restrict__ hdr, NodeInfo *ninfo,
     int64_t node_cap, int leaf, const Body *__restrict__ body, const double *__restrict__ beps2,
@@ -1567,7 +1592,7 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
                 raise_max(&hdr->cell_max[level0], most);
             }
             if (mine && !split)
-                node_moments<4>(k, info, level0, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
+                node_moments<QUAD, 4>(k, info, level0, body, beps2, keys, box, nmom, neps2, nquad, use_eps);
         }
         __syncthreads();
         int d = 0, hi = lbeg[1], par = 0;
@@ -1643,7 +1668,7 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
                     ninfo[cid] = ci;
                     if (level + 1 == kHintLevel) atomicMax(&s_hint, nb);
                     if (!deeper)
-                        node_moments<4>(cid, ci, level + 1, body, beps2, keys, box, nmom, neps2,
+                        node_moments<QUAD, 4>(cid, ci, level + 1, body, beps2, keys, box, nmom, neps2,
                                      nquad, use_eps);
                 }
                 if (deeper) {
@@ -1671,7 +1696,7 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
         for (d--; d >= 0; d--) {
             for (int i = lbeg[d] + tid; i < lbeg[d + 1]; i += kSubThreads) {
                 const int32_t id = entry(i);
-                node_moments<4>(id, ninfo[id], level0 + d, body, beps2, keys, box, nmom, neps2, nquad,
+                node_moments<QUAD, 4>(id, ninfo[id], level0 + d, body, beps2, keys, box, nmom, neps2, nquad,
                              use_eps);
             }
             __syncthreads();
@@ -1711,6 +1736,7 @@ __device__ inline void report_hints(TreeHeader *__restrict__ hdr, int32_t *out)
     }
 }
 
+template <bool QUAD>
 __global__ __launch_bounds__(256) void k_moments_level(
     int level, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
@@ -1718,38 +1744,75 @@ __global__ __launch_bounds__(256) void k_moments_level(
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
     int64_t node_cap, int use_eps, int32_t *__restrict__ depth_out)
 {
-    moments_nodes(level, hdr->level_count, ninfo, body, beps2, keys, box, nmom, neps2, nquad,
+    moments_nodes<QUAD>(level, hdr->level_count, ninfo, body, beps2, keys, box, nmom, neps2, nquad,
                   node_cap, use_eps, (int64_t)blockIdx.x * 256 + threadIdx.x,
                   (int64_t)gridDim.x * 256);
     // the root level reports the launch hints for the next build
     if (level == 0 && blockIdx.x == 0 && threadIdx.x < 64) report_hints(hdr, depth_out);
 }
 
-// Levels from-1 down to 0 of a single scene in one block, then the depth
-// report of k_moments_level at level 0.
-__global__ __launch_bounds__(1024) void k_moments_head(
+// Levels from-1 down to 0 of a single scene in one block (at most kHeadNodes
+// nodes, one a thread), then the depth report of k_moments_level at level 0. A
+// chain of latencies: the node table is read once, the leaves and level from-1 are
+// summed from global memory at once, and the levels above from a copy of the
+// moments in LDS: 13.5 us -> 9.5 at 50,000 bodies, 26 -> 18 with quadrupoles at
+// 20,000, against a pass over global memory a level.
+constexpr int kHeadLevels = 4, kHeadNodes = 1 + 8 + 64 + 512;
+constexpr int kHeadThreads = 640;
+static_assert(kHeadThreads >= kHeadNodes, "a node a thread");
+template <bool QUAD>
+__global__ __launch_bounds__(kHeadThreads) void k_moments_head(
     int from, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const uint64_t *__restrict__ keys, const SceneBox *__restrict__ box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
     int64_t node_cap, int use_eps, int32_t *__restrict__ depth_out)
 {
-    __shared__ int32_t scnt[kLevels + 1];
-    if (threadIdx.x <= kLevels) scnt[threadIdx.x] = hdr->level_count[threadIdx.x];
+    __shared__ NodeMom s_mom[kHeadNodes];
+    __shared__ double s_eps2[kHeadNodes], s_quad[QUAD ? 6 * kHeadNodes : 1];
+    const int t = threadIdx.x;
+    int level = -1;  // of node t
+    int32_t end = 0;
+    for (int l = 0; l < from; l++) {
+        int32_t beg, cnt;
+        level_range(hdr->level_count, l, node_cap, &beg, &cnt);
+        end = beg + cnt;
+        if (t >= beg && t < end) level = l;
+    }
+    BHX_CHECK(end <= kHeadNodes, CK_PARTITION);
+    NodeInfo info{0, 0, -1, 0};
+    if (level >= 0) info = ninfo[t];
+    auto put = [&](const NodeMom &m, double e2, const double *q) {
+        nmom[t] = s_mom[t] = m;
+        if (use_eps) neps2[t] = s_eps2[t] = e2;
+        if constexpr (QUAD)
+#pragma unroll
+            for (int a = 0; a < 6; a++) nquad[6 * t + a] = s_quad[6 * t + a] = q[a];
+    };
+    if (level >= 0 && (level == from - 1 || info.child0 < 0)) {
+        double e2, q[6];
+        const NodeMom m = node_sums<QUAD>(info, level, body, beps2, keys, box, nmom, neps2, nquad,
+                                    use_eps, e2, q);
+        put(m, e2, q);
+    }
     __syncthreads();
-    for (int level = from - 1; level >= 0; level--) {
-        moments_nodes(level, scnt, ninfo, body, beps2, keys, box, nmom, neps2, nquad, node_cap,
-                      use_eps,
-                      threadIdx.x, 1024);
+    for (int l = from - 2; l >= 0; l--) {
+        if (level == l && info.child0 >= 0) {
+            double e2, q[6];
+            const NodeMom m = node_sums<QUAD>(info, level, body, beps2, keys, box, s_mom, s_eps2,
+                                        s_quad, use_eps, e2, q);
+            put(m, e2, q);
+        }
         __syncthreads();
     }
-    if (threadIdx.x < 64) report_hints(hdr, depth_out);
+    if (t < 64) report_hints(hdr, depth_out);
 }
 
 // The deep levels in one block (they hold few nodes): with `split`, first
 // the split of levels to..kMaxLevel-1 (stopping at the first empty level,
 // the node counts kept in LDS), then the moments of levels kMaxLevel down
 // to `to`.
+template <bool QUAD>
 __global__ __launch_bounds__(1024) void k_moments_tail(
     int to, int split, const uint64_t *__restrict__ keys, TreeHeader *__restrict__ hdr,
     NodeInfo *__restrict__ ninfo, const Body *__restrict__ body,
@@ -1767,7 +1830,7 @@ __global__ __launch_bounds__(1024) void k_moments_tail(
     }
     for (int level = kMaxLevel; level >= to; level--) {
         if (scnt[level] == 0) continue;  // the same on every thread
-        moments_nodes(level, scnt, ninfo, body, beps2, keys, box, nmom, neps2, nquad, node_cap,
+        moments_nodes<QUAD>(level, scnt, ninfo, body, beps2, keys, box, nmom, neps2, nquad, node_cap,
                       use_eps, threadIdx.x, 1024);
         __syncthreads();
     }
@@ -1924,6 +1987,7 @@ __device__ inline void euler_axis(double &x, double &v, double a, double dt, int
 
 // With adv.vel the bodies are moved first (a launch of its own took 5 us of a
 // 65 us substep of 1000 bodies), and pos holds the moved positions.
+template <bool QUAD>
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     const double *pos, Advance adv, const double *__restrict__ mass,
     const double *__restrict__ eps, int64_t n64, int leaf, SceneBox *__restrict__ box,
@@ -2155,7 +2219,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
 
     // 6. moments
     const int cache = few ? (kSmallLds - kBodyLds) / kNodeLds : kCacheNodes;
-    if (total <= cache && total <= node_cap && !nquad) {
+    if (total <= cache && total <= node_cap && !QUAD) {
         NodeMom *cm = (NodeMom *)lds;
         double *ce = (double *)(lds + cache * sizeof(NodeMom));
         int inner[4];  // an internal node's first child, children << 12 and level << 16
@@ -2203,7 +2267,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         }
     } else {
         for (int level = depth; level >= 0; level--) {
-            moments_nodes(level, scnt, ninfo, body, beps2, key, box, nmom, neps2, nquad, node_cap,
+            moments_nodes<QUAD>(level, scnt, ninfo, body, beps2, key, box, nmom, neps2, nquad, node_cap,
                           use_eps, tid, kSmallThreads);
             __syncthreads();
         }
@@ -2363,6 +2427,9 @@ LevelPlan plan_levels(const Workspace &w, const Layout &lay)
 }
 
 // Stages 5-6 on the sorted bodies (with the plan the gather was launched with).
+// The kernels are short and start cold: code for the quadrupoles beside the plain
+// sums made each of them 1 to 2 us longer, so it is instantiated apart.
+template <bool QUAD>
 void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int leaf, bool use_eps,
                     const LevelPlan &plan)
 {
@@ -2377,7 +2444,7 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     // bodies run four passes deep there.) The split only affects speed.
     const int deep = plan.sub >= 0 ? plan.sub : plan.deep, prev = plan.prev;
     const volatile int32_t *hint = w.depth_host;
-    const int head = ns == 1 ? (deep < 4 ? deep : 4) : 0;
+    const int head = ns == 1 ? (deep < kHeadLevels ? deep : kHeadLevels) : 0;
     // one scene: levels 1..kPrefixLevels from the marks of the gather in one
     // block instead of one launch per level (when the previous build went deeper)
     if (plan.prefix)
@@ -2405,23 +2472,25 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     if (plan.sub >= 0) {
         // as many blocks as the level's nodes need, by the previous build's count
         const int64_t nodes = hint[2 + deep] > 0 ? (int64_t)hint[2 + deep] : 1;
-        k_build_subtrees<<<blocks_for(nodes, kSubNodes, 1u << 16), kSubThreads, 0, s>>>(
+        k_build_subtrees<QUAD><<<blocks_for(nodes, kSubNodes, 1u << 16), kSubThreads, 0, s>>>(
             deep, w.keys[0], w.hdr, w.ninfo, w.node_cap, leaf, w.body, w.beps2, w.box, w.nmom,
             w.neps2, w.nquad, ue, w.inner);
     } else {
         // the levels from `deep` down: their split and their moments in one block
-        k_moments_tail<<<1, 1024, 0, s>>>(deep, deep < kMaxLevel ? 1 : 0, w.keys[0], w.hdr,
-                                          w.ninfo, w.body, w.beps2, w.box, w.nmom, w.neps2,
-                                          w.nquad, w.node_cap, leaf, ue);
+        k_moments_tail<QUAD><<<1, 1024, 0, s>>>(deep, deep < kMaxLevel ? 1 : 0, w.keys[0], w.hdr,
+                                                w.ninfo, w.body, w.beps2, w.box, w.nmom, w.neps2,
+                                                w.nquad, w.node_cap, leaf, ue);
     }
     for (int level = deep - 1; level >= head; level--) {
         const unsigned g = blocks_for(level_bound(level, n, ns), 256, 4096);
-        k_moments_level<<<g, 256, 0, s>>>(level, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0], w.box,
-                                          w.nmom, w.neps2, w.nquad, w.node_cap, ue, w.depth_dev);
+        k_moments_level<QUAD><<<g, 256, 0, s>>>(level, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0],
+                                                w.box, w.nmom, w.neps2, w.nquad, w.node_cap, ue,
+                                                w.depth_dev);
     }
     if (head > 0)
-        k_moments_head<<<1, 1024, 0, s>>>(head, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0], w.box,
-                                          w.nmom, w.neps2, w.nquad, w.node_cap, ue, w.depth_dev);
+        k_moments_head<QUAD><<<1, kHeadThreads, 0, s>>>(head, w.hdr, w.ninfo, w.body, w.beps2,
+                                                        w.keys[0], w.box, w.nmom, w.neps2, w.nquad,
+                                                        w.node_cap, ue, w.depth_dev);
 }
 
 }  // namespace
@@ -2464,9 +2533,10 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
     const int64_t n = lay.n;
     const int ns = lay.n_scenes;
     if (one_block_build(lay)) {
-        k_build_small<<<1, kSmallThreads, 0, s>>>(pos, adv ? *adv : Advance{}, mass, eps, n, leaf, w.box, w.hdr, w.keys[0],
-                                                  w.idx[0], w.body, w.beps2, w.ninfo, w.nmom,
-                                                  w.neps2, w.nquad, w.node_cap, w.depth_dev);
+        const auto kernel = w.nquad ? k_build_small<true> : k_build_small<false>;
+        kernel<<<1, kSmallThreads, 0, s>>>(pos, adv ? *adv : Advance{}, mass, eps, n, leaf, w.box,
+                                           w.hdr, w.keys[0], w.idx[0], w.body, w.beps2, w.ninfo,
+                                           w.nmom, w.neps2, w.nquad, w.node_cap, w.depth_dev);
         return hipGetLastError();
     }
     if (adv) return hipErrorInvalidValue;
@@ -2486,7 +2556,7 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
     k_gather<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(pos, mass, eps, w.idx[0], n, w.body,
                                                           w.beps2, w.keys[0],
                                                           plan.prefix ? w.prefix_mark : nullptr);
-    enqueue_levels(w, s, lay, leaf, eps != nullptr, plan);
+    (w.nquad ? enqueue_levels<true> : enqueue_levels<false>)(w, s, lay, leaf, eps != nullptr, plan);
     return hipGetLastError();
 }
 
@@ -2511,7 +2581,7 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
     k_gather_state<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(
         w.sbody, w.svel, use_eps ? w.seps2 : nullptr, w.scidx, n, w.idx[0], w.body, w.tvel,
         w.beps2, w.keys[0], plan.prefix ? w.prefix_mark : nullptr);
-    enqueue_levels(w, s, lay, leaf, use_eps, plan);
+    (w.nquad ? enqueue_levels<true> : enqueue_levels<false>)(w, s, lay, leaf, use_eps, plan);
     return hipGetLastError();
 }
 
