@@ -51,8 +51,9 @@ __host__ __device__ inline int node_scene(const NodeInfo &i)
 }
 constexpr int kMaxScenes = 65535;
 
-// Root cube of one scene. lo_enc / hi_enc hold the per-axis minimum and
-// maximum as order-preserving integers while the box is being reduced.
+// Root cube of one scene. lo_enc / hi_enc hold the per-axis minimum and the
+// complement of the maximum as order-preserving integers while the box is being
+// reduced, and all ones (no bodies yet) before and after a build.
 struct SceneBox {
     unsigned long long lo_enc[3], hi_enc[3];
     double lo[3], hi[3];  // per-axis bounding box

@@ -639,6 +639,7 @@ bool ensure_tree_slots(bh_ctx *c, int32_t nsteps, int64_t n)
     A(dalloc(&t.neps2, k * node_cap));
     A(dalloc(&t.box, k));
     A(dalloc(&t.hdr, k));
+    if (r == hipSuccess) r = hipMemset(t.box, 0xff, nsteps * sizeof(bhx::SceneBox));
     if (r == hipSuccess) r = init_headers(t.hdr, nsteps, c->w.status_dev);
     if (r != hipSuccess) {
         (void)hipGetLastError();
@@ -760,6 +761,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
         for (auto &ev : c->ev_pool)
             if (r == hipSuccess) r = hipEventCreate(&ev);
     }
+    if (r == hipSuccess) r = hipMemset(w.box, 0xff, max_scenes * sizeof(bhx::SceneBox));
     if (r == hipSuccess) r = init_headers(w.hdr, 1, w.status_dev);
     if (r == hipSuccess) r = hipDeviceSynchronize();
     if (r != hipSuccess) {

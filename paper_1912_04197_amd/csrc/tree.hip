@@ -99,29 +99,39 @@ __device__ inline double order_dec(unsigned long long e)
     return __longlong_as_double((long long)b);
 }
 
-__global__ __launch_bounds__(256) void k_box_init(SceneBox *__restrict__ box, int n_scenes)
+// Encodings of a box without bodies. A context's boxes hold these from its creation
+// and between builds: a build's last kernel sets them again (a launch of its own at
+// the build's start cost 5 us).
+__device__ inline void reset_box(SceneBox *box)
 {
-    const int sc = blockIdx.x * 256 + threadIdx.x;
-    if (sc >= n_scenes) return;
-    for (int a = 0; a < 3; a++) {
-        box[sc].lo_enc[a] = ~0ull;
-        box[sc].hi_enc[a] = 0ull;
-    }
+    for (int a = 0; a < 3; a++) box->lo_enc[a] = box->hi_enc[a] = ~0ull;
 }
 
 // One work item: a chunk of at most kBoxChunk bodies of one scene (for one
-// scene, chunk c is bodies c*kBoxChunk onwards). Reduces its box in the block
+// scene, chunk c is the `per` bodies from c*per on). Reduces its box in the block
 // and merges it into the scene's with integer atomics; flags bad input.
-constexpr int kBoxThreads = 1024;  // one block per chunk: 4 bodies per thread
+constexpr int kBoxThreads = 1024;  // one block per chunk: up to 4 bodies per thread
+
+// Bodies per chunk of a single scene: one a thread while that leaves no more
+// blocks than CUs (each block ends in six atomics on shared words).
+// 50,000 bodies: 13 blocks of 4096 took 13 us for the kick and drift, 49 of 1024
+// take 8.7; 2^20: 256 blocks either way.
+inline int box_chunk(int64_t n)
+{
+    int per = kBoxThreads;
+    while (per < kBoxChunk && n > 256 * (int64_t)per) per *= 2;
+    return per;
+}
+
 __global__ __launch_bounds__(kBoxThreads) void k_box_chunk(const double *__restrict__ pos,
                                                    const double *__restrict__ mass,
                                                    const double *__restrict__ eps, int64_t n,
-                                                   const int32_t *__restrict__ chunks,
+                                                   int per, const int32_t *__restrict__ chunks,
                                                    SceneBox *__restrict__ box,
                                                    TreeHeader *__restrict__ hdr)
 {
     int sc = 0;
-    int64_t first = (int64_t)blockIdx.x * kBoxChunk, end = first + kBoxChunk;
+    int64_t first = (int64_t)blockIdx.x * per, end = first + per;
     if (chunks) {
         sc = chunks[3 * blockIdx.x];
         first = chunks[3 * blockIdx.x + 1];
@@ -163,7 +173,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_box_chunk(const double *__restr
         if (a < 3)
             atomicMin(&box[sc].lo_enc[a], order_enc(v));
         else
-            atomicMax(&box[sc].hi_enc[a - 3], order_enc(v));
+            atomicMin(&box[sc].hi_enc[a - 3], ~order_enc(v));
     }
 }
 
@@ -175,13 +185,13 @@ __global__ __launch_bounds__(kBoxThreads) void k_box_chunk(const double *__restr
 __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
     const Body *__restrict__ body, const double *__restrict__ tvel,
     const double *__restrict__ tacc, const double *__restrict__ beps2,
-    const uint32_t *__restrict__ cidx, int64_t n, double h, double dt,
+    const uint32_t *__restrict__ cidx, int64_t n, double h, double dt, int per,
     const int32_t *__restrict__ chunks, Body *__restrict__ sbody, double *__restrict__ svel,
     double *__restrict__ seps2, uint32_t *__restrict__ scidx, SceneBox *__restrict__ box,
     TreeHeader *__restrict__ hdr)
 {
     int sc = 0;
-    int64_t first = (int64_t)blockIdx.x * kBoxChunk, end = first + kBoxChunk;
+    int64_t first = (int64_t)blockIdx.x * per, end = first + per;
     if (chunks) {
         sc = chunks[3 * blockIdx.x];
         first = chunks[3 * blockIdx.x + 1];
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
         if (a < 3)
             atomicMin(&box[sc].lo_enc[a], order_enc(v));
         else
-            atomicMax(&box[sc].hi_enc[a - 3], order_enc(v));
+            atomicMin(&box[sc].hi_enc[a - 3], ~order_enc(v));
     }
 }
 
@@ -273,7 +283,7 @@ __device__ inline void scene_root_cube(SceneBox &out, const SceneBox &in, bool a
     double lo[3], hi[3];
     for (int a = 0; a < 3; a++) {
         lo[a] = any ? order_dec(in.lo_enc[a]) : 0.0;
-        hi[a] = any ? order_dec(in.hi_enc[a]) : 0.0;
+        hi[a] = any ? order_dec(~in.hi_enc[a]) : 0.0;
     }
     root_cube(out, lo, hi);
 }
@@ -1740,15 +1750,19 @@ template <bool QUAD>
 __global__ __launch_bounds__(256) void k_moments_level(
     int level, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
-    const uint64_t *__restrict__ keys, const SceneBox *__restrict__ box,
+    const uint64_t *__restrict__ keys, SceneBox *box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
-    int64_t node_cap, int use_eps, int32_t *__restrict__ depth_out)
+    int64_t node_cap, int use_eps, int n_scenes,
+    int32_t *__restrict__ depth_out)
 {
     moments_nodes<QUAD>(level, hdr->level_count, ninfo, body, beps2, keys, box, nmom, neps2, nquad,
                   node_cap, use_eps, (int64_t)blockIdx.x * 256 + threadIdx.x,
                   (int64_t)gridDim.x * 256);
     // the root level reports the launch hints for the next build
-    if (level == 0 && blockIdx.x == 0 && threadIdx.x < 64) report_hints(hdr, depth_out);
+    if (level == 0 && blockIdx.x == 0) {
+        if (threadIdx.x < 64) report_hints(hdr, depth_out);
+        for (int sc = threadIdx.x; sc < n_scenes; sc += 256) reset_box(box + sc);
+    }
 }
 
 // Levels from-1 down to 0 of a single scene in one block (at most kHeadNodes
@@ -1764,7 +1778,7 @@ template <bool QUAD>
 __global__ __launch_bounds__(kHeadThreads) void k_moments_head(
     int from, TreeHeader *__restrict__ hdr, const NodeInfo *__restrict__ ninfo,
     const Body *__restrict__ body, const double *__restrict__ beps2,
-    const uint64_t *__restrict__ keys, const SceneBox *__restrict__ box,
+    const uint64_t *__restrict__ keys, SceneBox *box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
     int64_t node_cap, int use_eps, int32_t *__restrict__ depth_out)
 {
@@ -1806,6 +1820,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_moments_head(
         __syncthreads();
     }
     if (t < 64) report_hints(hdr, depth_out);
+    if (t == 0) reset_box(box);
 }
 
 // The deep levels in one block (they hold few nodes): with `split`, first
@@ -2067,10 +2082,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
                 const double u = __shfl_xor(v[a], o);
                 v[a] = a < 3 ? fmin(v[a], u) : fmax(v[a], u);
             }
-        for (int a = 0; a < 3; a++) {  // every lane stores the same
-            sbox.lo_enc[a] = order_enc(v[a]);
-            sbox.hi_enc[a] = order_enc(v[3 + a]);
-        }
+        if (lane == 0) reset_box(&sbox);
         root_cube(sbox, v, v + 3, lane, 64);
     }
     __syncthreads();
@@ -2484,7 +2496,7 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     for (int level = deep - 1; level >= head; level--) {
         const unsigned g = blocks_for(level_bound(level, n, ns), 256, 4096);
         k_moments_level<QUAD><<<g, 256, 0, s>>>(level, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0],
-                                                w.box, w.nmom, w.neps2, w.nquad, w.node_cap, ue,
+                                                w.box, w.nmom, w.neps2, w.nquad, w.node_cap, ue, ns,
                                                 w.depth_dev);
     }
     if (head > 0)
@@ -2541,10 +2553,11 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
     }
     if (adv) return hipErrorInvalidValue;
     const unsigned sb = (unsigned)((ns + 255) / 256);
-    k_box_init<<<sb, 256, 0, s>>>(w.box, ns);
-    const int nchunks = lay.chunks ? lay.n_chunks : (int)((n + kBoxChunk - 1) / kBoxChunk);
+    const int per = box_chunk(n);
+    const int nchunks = lay.chunks ? lay.n_chunks : (int)((n + per - 1) / per);
     if (nchunks > 0)
-        k_box_chunk<<<nchunks, kBoxThreads, 0, s>>>(pos, mass, eps, n, lay.chunks, w.box, w.hdr);
+        k_box_chunk<<<nchunks, kBoxThreads, 0, s>>>(pos, mass, eps, n, per, lay.chunks, w.box,
+                                                  w.hdr);
     // the sort is chosen once (a host read of the previous build's hint); a
     // single scene's bucket sort finishes the box in its key kernel
     const bool bk = n > 0 && bucket_sort_hint(w, lay);
@@ -2568,11 +2581,11 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
     const int ns = lay.n_scenes;
     if (n <= 0) return hipSuccess;
     const unsigned sb = (unsigned)((ns + 255) / 256);
-    k_box_init<<<sb, 256, 0, s>>>(w.box, ns);
-    const int nchunks = lay.chunks ? lay.n_chunks : (int)((n + kBoxChunk - 1) / kBoxChunk);
+    const int per = box_chunk(n);
+    const int nchunks = lay.chunks ? lay.n_chunks : (int)((n + per - 1) / per);
     k_state_kick_drift<<<nchunks, kBoxThreads, 0, s>>>(
-        w.body, w.tvel, w.tacc, w.beps2, w.idx[0], n, 0.5 * dt, dt, lay.chunks, w.sbody, w.svel,
-        use_eps ? w.seps2 : nullptr, w.scidx, w.box, w.hdr);
+        w.body, w.tvel, w.tacc, w.beps2, w.idx[0], n, 0.5 * dt, dt, per, lay.chunks, w.sbody,
+        w.svel, use_eps ? w.seps2 : nullptr, w.scidx, w.box, w.hdr);
     const bool bk = bucket_sort_hint(w, lay);  // read once, as in launch_build
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     enqueue_keys_sort(w, s, lay, reinterpret_cast<const double *>(w.sbody), 4, bk);
