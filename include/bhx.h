@@ -356,15 +356,16 @@ typedef struct {
 bh_status bh_tree_export(bh_ctx *ctx, bh_tree_view *out);
 
 /* Summary (synchronises): node count and depth of the last build, and which
- * sort it used (bucket_sort = 1: two passes on the top 16 key bits, one more
- * on the scene index for a batch, and one block per range of whole buckets,
+ * sort it used (bucket_sort = 1: two or three passes on the top key bits, one
+ * more on the scene index for a batch, and one block per range of whole buckets,
  * chosen for one scene, or a batch of at most 256 scenes, of more than 4096
  * bodies when the previous build's level-5 nodes held at most 1024 bodies
- * each; 0: eight 8-bit passes, or the one-block build); totals of accepted
+ * each; 0: three passes and the buckets where only the nodes of a level 6 to 8
+ * were that small, eight 8-bit passes, or the one-block build); totals of accepted
  * nodes and leaf pairs over all bodies of the last walk (0 unless
  * BH_FLAG_COUNTS); with BH_FLAG_TIMING, the number of tree force evaluations
  * and the summed device time (ms, HIP events on the context's stream) of their
- * build and walk phases since creation or the last bh_timing_reset(). Both
+ * build and walk phases since creation or the last bh_timing_reset(). All
  * sorts give the same order. */
 typedef struct {
     int64_t nnodes;

@@ -293,7 +293,7 @@ inline int64_t node_capacity(int64_t n, int leaf, int scenes = 1)
 }
 
 // Launchers (tree.hip). All enqueue on `s` and never synchronise; `bucket`
-// (if given) receives the sort the build enqueued (bucket_sort_hint). The build
+// (if given) receives bucket_sort_hint's `even`. The build
 // launches one kernel per tree level down to one below the depth the
 // previous build reported (a host read of pinned memory, frozen in a
 // captured graph) and handles deeper levels in one block: any depth is
@@ -320,12 +320,12 @@ inline bool one_block_build(const Layout &lay)
 // softening and caller indices into the new order.
 hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &lay, bool use_eps,
                               int leaf, double dt, bool *bucket = nullptr);
-// Whether the next build of `lay` sorts by buckets of the top key bits (one
-// scene above kSmallBuild bodies whose last build's level-kHintLevel nodes
-// all fit a block's range) rather than by eight key passes; a host read of
-// the pinned hints, frozen in a captured graph. Either sort gives the same
-// order; the choice only affects speed.
-bool bucket_sort_hint(const Workspace &w, const Layout &lay);
+// How the next build of `lay` sorts: by buckets after 2 or 3 passes on the top key
+// bits (above kSmallBuild bodies, when the last build's nodes of level kHintLevel,
+// or of a level down to 8, all fit a block's range) or, 0, by passes over the whole
+// keys; a host read of the pinned hints, frozen in a captured graph. Every sort gives
+// the same order; the choice only affects speed. even: whether level kHintLevel's did.
+int bucket_sort_hint(const Workspace &w, const Layout &lay, bool *even = nullptr);
 // The level from which the next build of `lay` builds whole subtrees in one
 // launch, or -1; a host read of the pinned hints like bucket_sort_hint.
 int subtree_hint(const Workspace &w, const Layout &lay);

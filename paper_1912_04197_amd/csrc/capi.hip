@@ -22,7 +22,7 @@ struct bh_ctx {
     Workspace w;
     std::string err;
     int64_t tree_n = -1;   // n of the last build, -1 before any
-    bool bucket = false;   // the last build sorted by buckets of the top key bits
+    bool bucket = false;   // bh_stats_t::bucket_sort of the last build
     bool tree_eps = false; // the last build had per-body eps
     int64_t walk_n = -1;   // n of the last walk that wrote counts
     double *diag_out = nullptr;
@@ -527,8 +527,8 @@ bh_status run_steps(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
     // capture had no hint yet (it launched every level).
     const int depth_now = c->w.depth_host ? *(const volatile int32_t *)c->w.depth_host : -1;
     const bool deeper = depth_now >= 0 && (c->gdepth < 0 || depth_now > c->gdepth + 1);
-    // likewise when the hints now pick the other sort (same order, other speed)
-    const int bucket_now = bhx::bucket_sort_hint(c->w, lay) ? 1 : 0;
+    // likewise when the hints now pick another sort (same order, other speed)
+    const int bucket_now = bhx::bucket_sort_hint(c->w, lay);
     // or another level for the subtrees that are built whole
     const int sub_now = bhx::subtree_hint(c->w, lay);
     if (!c->gexec || key != c->gkey || deeper || bucket_now != c->gbucket || sub_now != c->gsub) {

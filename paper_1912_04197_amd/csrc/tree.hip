@@ -567,8 +567,10 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
 
 // ------------------------------------------------------- 3b. bucket sort
 
-// One scene: two stable passes on the top 16 key bits (bits 47..62) group the
-// keys by bucket (equal top bits), in input order within each bucket; then
+// Stable passes on the top key bits group the keys by bucket (equal top bits), in
+// input order within each bucket: two on the top 16 (bits 47..62) or, where those
+// leave large buckets, three on the top 24 (in place of eight on whole keys: builds
+// of a Plummer sphere of 131,072 bodies take 155 us, not 217); then
 // one block per tile of sorted positions takes the buckets that start in its
 // tile (through the end of the last one) and sorts them by the whole key,
 // stably: in LDS when they hold at most its capacity of keys, else in
@@ -576,7 +578,12 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
 // digit is the same for every key of the range leaves it as it is and is
 // skipped. A stable sort has one result, so this is the order of the
 // eight-pass sort.
-constexpr int kTopShift = 47;
+__host__ __device__ inline int top_shift(int passes) { return 63 - 8 * passes; }
+// The buckets of two passes lie inside cells of level kHintLevel, of three of:
+constexpr int kBucketLevel3 = 8;
+static_assert(63 - 8 * 2 <= 3 * (kMaxLevel - kHintLevel) &&
+                  63 - 8 * 3 <= 3 * (kMaxLevel - kBucketLevel3),
+              "a bucket inside a cell");
 // Block shapes of the bucket sort: a block of T threads holds up to 5 rounds
 // of 64 keys per wave (kCap = 5 T) and starts from tiles of kCap - 1024
 // keys, so a range never exceeds kCap when no bucket holds more than 1024
@@ -593,13 +600,16 @@ struct LocalShape {
 using LocalBig = LocalShape<1024>;
 using LocalSmall = LocalShape<256>;
 constexpr int kBucketMax = 1024;  // bucket bound both shapes are sized for
-// Buckets sorted by comparison instead of radix passes: when the previous
-// build held at most kRankPerNode bodies per level-5 node on average (a
-// bucket is half such a node), in ranges whose buckets all hold at most
-// kRankMax keys. Each key's comparisons walk its bucket in LDS, so the cost
-// grows with the bucket; with tens of keys per bucket the passes are faster.
+// A range whose buckets all hold at most kRankMax keys is sorted by comparison
+// instead of radix passes (200,000 bodies, 18 a level-5 node: builds of 108 us, not
+// 132). Each key's comparisons walk its bucket in LDS, so the cost grows with the
+// bucket.
 constexpr int kRankMax = 32;
-constexpr int64_t kRankPerNode = 8;
+// From this mean number of bodies per level-5 node (two buckets) most ranges hold a
+// larger bucket, and a third pass costs less than radix passes in LDS: builds of
+// 2^20 evenly spread bodies (32 a node) take 194 us with it and 211 without, of 2^21
+// 315 and 357; 500,000 (15) 146 and 140, 200,000 of a ball (18) 118 and 108.
+constexpr int64_t kThirdPassFrom = 24;
 static_assert(LocalBig::kTile > 0 && LocalSmall::kTile > 0, "tiles");
 constexpr int64_t kBigSortFrom = (int64_t)256 * LocalBig::kTile;  // 256 blocks of the big shape
 
@@ -705,7 +715,7 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
                                                              uint32_t *__restrict__ idx,
                                                              uint64_t *__restrict__ ktmp,
                                                              uint32_t *__restrict__ itmp,
-                                                             int64_t n, int rank_small,
+                                                             int64_t n, int shift,
                                                              const int64_t *__restrict__ offsets,
                                                              int ns)
 {
@@ -745,10 +755,10 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
         const int64_t from = wave == 0 ? t0 : t1;
         int64_t pos = from;
         if (wave == 1 || t0 > 0) {
-            const uint64_t top = keys[wave == 0 ? t0 - 1 : t1 - 1] >> kTopShift;
+            const uint64_t top = keys[wave == 0 ? t0 - 1 : t1 - 1] >> shift;
             for (int64_t c = from;; c += 64) {
                 const int64_t i = c + lane;
-                const bool differs = i >= n || (keys[i] >> kTopShift) != top;
+                const bool differs = i >= n || (keys[i] >> shift) != top;
                 const uint64_t bal = __ballot(differs);
                 if (bal) {
                     pos = c + __builtin_ctzll(bal);
@@ -785,31 +795,29 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
                 skey[0][i] = keys[a + i];
                 sval[0][i] = idx[a + i];
             }
-            if (tid == 0) sbig = rank_small ? 0u : 1u;
+            if (tid == 0) sbig = 0u;
             __syncthreads();
-            // With rank_small, and buckets of at most kRankMax keys: each key's
-            // place is its bucket's start plus the number of keys of the bucket
-            // before it in (key, position) order, a stable sort by comparison,
-            // with no radix passes. A larger bucket sends the whole range to the
-            // radix passes below.
+            // With buckets of at most kRankMax keys (no key has its top bits again
+            // kRankMax places on) each key's place is its bucket's start plus the
+            // number of keys of the bucket before it in (key, position) order, a
+            // stable sort by comparison, with no radix passes. A larger bucket sends
+            // the whole range to the radix passes below.
             constexpr int kR = Sh::kCap / Sh::kThreads;
+            for (int i = tid; i + kRankMax < m; i += Sh::kThreads)
+                if (skey[0][i] >> shift == skey[0][i + kRankMax] >> shift) sbig = 1u;
+            __syncthreads();
+            const bool by_rank = sbig == 0u;  // the same on every thread
             int32_t dest[kR];
 #pragma unroll
             for (int r = 0; r < kR; r++) {
                 const int i = tid + r * Sh::kThreads;
                 dest[r] = -1;
-                if (!rank_small || i >= m) continue;
+                if (!by_rank || i >= m) continue;
                 const uint64_t k = skey[0][i];
-                const uint64_t top = k >> kTopShift;
+                const uint64_t top = k >> shift;
                 int bs = i, be = i + 1;
-                while (bs > 0 && i - bs < kRankMax && (skey[0][bs - 1] >> kTopShift) == top) bs--;
-                while (be < m && be - bs <= kRankMax && (skey[0][be] >> kTopShift) == top) be++;
-                const bool big = be - bs > kRankMax ||
-                                 (bs > 0 && i - bs == kRankMax && (skey[0][bs - 1] >> kTopShift) == top);
-                if (big) {
-                    sbig = 1u;
-                    continue;
-                }
+                while (bs > 0 && (skey[0][bs - 1] >> shift) == top) bs--;
+                while (be < m && (skey[0][be] >> shift) == top) be++;
                 int32_t rank = bs;
                 for (int j = bs; j < be; j++) {
                     const uint64_t kj = skey[0][j];
@@ -817,8 +825,7 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
                 }
                 dest[r] = rank;
             }
-            __syncthreads();
-            if (sbig == 0u) {  // the same on every thread
+            if (by_rank) {
 #pragma unroll
                 for (int r = 0; r < kR; r++) {
                     const int i = tid + r * Sh::kThreads;
@@ -2332,29 +2339,29 @@ hipError_t launch_scene_of(hipStream_t s, const int64_t *offsets, int n_scenes,
 namespace {
 
 // Stages 2-3: keys of the bodies (coordinates at pos + stride * i) and the
-// sort, leaving the sorted order in idx[0]; returns whether it sorted by
-// buckets.
-bool enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
-                       int stride, bool bucket)
+// sort, leaving the sorted order in idx[0]: by buckets after top_passes passes on the
+// top key bits (bucket_sort_hint), or with none by passes over the whole keys.
+void enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
+                       int stride, int top_passes)
 {
     const int64_t n = lay.n;
     const int ns = lay.n_scenes;
     const int nblk = (int)((n + kSortTile - 1) / kSortTile);
     const unsigned nb0 = blocks_for(n, 256, 1u << 30);
-    if (bucket) {
-        // two passes on the top 16 key bits and, for several scenes, one on
-        // the scene index (ending in buffer 0), then the buckets in place
-        const int passes = ns > 1 ? 3 : 2;
-        const int first = passes & 1;
+    if (top_passes) {
+        // passes on the top key bits and, for several scenes, one on the scene
+        // index (ending in buffer 0), then the buckets in place
+        const int passes = ns > 1 ? top_passes + 1 : top_passes;
+        const int first = passes & 1, top = top_shift(top_passes);
         if (ns == 1)  // the root cube, the keys and the first pass's digit counts
             k_keys_hist<<<nblk, kSortThreads, 0, s>>>(pos, stride, n, w.box, w.hdr, w.ninfo,
-                                                      w.keys[0], w.idx[0], kTopShift,
+                                                      w.keys[first], w.idx[first], top,
                                                       w.sort_counts, nblk);
         else
             k_keys<<<nb0, 256, 0, s>>>(pos, stride, n, w.box, lay.scene_of, w.keys[first],
                                        w.idx[first]);
         for (int pass = 0; pass < passes; pass++) {
-            const int shift = pass < 2 ? kTopShift + 8 * pass : 64;
+            const int shift = pass < top_passes ? top + 8 * pass : 64;
             const int src = (pass + first) & 1, dst = src ^ 1;
             if (ns > 1 || pass > 0)
                 k_sort_hist<<<nblk, kSortThreads, 0, s>>>(w.keys[src], w.idx[src], lay.scene_of,
@@ -2366,23 +2373,19 @@ bool enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, con
                                                          n, shift, w.sort_counts, w.sort_totals,
                                                          nblk);
         }
-        // small buckets are placed by comparison (the previous build's mean
-        // bodies per level-5 node picks it; only speed depends on it)
-        const int32_t n5 = ((const volatile int32_t *)w.depth_host)[2 + kHintLevel];
-        const int rank_small = n5 > 0 && n <= kRankPerNode * (int64_t)n5 ? 1 : 0;
         if (n >= kBigSortFrom)
             k_sort_local<LocalBig>
                 <<<(unsigned)((n + LocalBig::kTile - 1) / LocalBig::kTile), LocalBig::kThreads, 0,
-                   s>>>(w.keys[0], w.idx[0], w.keys[1], w.idx[1], n, rank_small, lay.offsets, ns);
+                   s>>>(w.keys[0], w.idx[0], w.keys[1], w.idx[1], n, top, lay.offsets, ns);
         else
             k_sort_local<LocalSmall>
                 <<<(unsigned)((n + LocalSmall::kTile - 1) / LocalSmall::kTile),
                    LocalSmall::kThreads, 0, s>>>(w.keys[0], w.idx[0], w.keys[1], w.idx[1], n,
-                                                 rank_small, lay.offsets, ns);
+                                                 top, lay.offsets, ns);
 #ifdef BHX_CHECKS
         k_check_order<<<nb0, 256, 0, s>>>(w.keys[0], w.idx[0], n, lay.offsets, ns);
 #endif
-        return true;
+        return;
     }
     // 8 passes on the Morton key, then (several scenes) one on each byte of
     // the scene index that is not always zero; the keys start in the buffer
@@ -2403,7 +2406,6 @@ bool enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, con
 #ifdef BHX_CHECKS
     k_check_order<<<nb0, 256, 0, s>>>(w.keys[0], w.idx[0], n, lay.offsets, ns);
 #endif
-    return false;
 }
 
 // How a build launches its levels, read once from the previous build's hints:
@@ -2526,13 +2528,24 @@ Workspace slot_view(const Workspace &w, const TreeSlots &t, int k)
     return v;
 }
 
-bool bucket_sort_hint(const Workspace &w, const Layout &lay)
+int bucket_sort_hint(const Workspace &w, const Layout &lay, bool *even)
 {
-    if (lay.n_scenes > kLdsScenes || lay.n <= kSmallBuild || !w.depth_host) return false;
+    if (even) *even = false;
+    if (lay.n_scenes > kLdsScenes || lay.n <= kSmallBuild || !w.depth_host) return 0;
     // a range is a tile plus at most one bucket, and a bucket lies inside one
-    // node of level kHintLevel (its top 16 bits fix the first 5 levels)
-    const int cell = ((const volatile int32_t *)w.depth_host)[1];
-    return cell >= 0 && cell <= kBucketMax;
+    // cell of level kHintLevel or kBucketLevel3; a cell that is no node holds at
+    // most a leaf's bodies, and a level's bound holds for the levels below it
+    const volatile int32_t *hint = w.depth_host;
+    if (hint[1] < 0) return 0;
+    if (hint[1] <= kBucketMax) {
+        if (even) *even = true;
+        return lay.n > kThirdPassFrom * (int64_t)hint[2 + kHintLevel] && hint[2 + kHintLevel] > 0
+                   ? 3 : 2;
+    }
+    const volatile int32_t *most = hint + 2 + kLevels;
+    for (int l = kHintLevel + 1; l <= kBucketLevel3; l++)
+        if (most[l] > 0 && most[l] <= kBucketMax) return 3;
+    return 0;
 }
 
 int subtree_hint(const Workspace &w, const Layout &lay) { return plan_levels(w, lay).sub; }
@@ -2560,11 +2573,10 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
                                                   w.hdr);
     // the sort is chosen once (a host read of the previous build's hint); a
     // single scene's bucket sort finishes the box in its key kernel
-    const bool bk = n > 0 && bucket_sort_hint(w, lay);
+    const int bk = n > 0 ? bucket_sort_hint(w, lay, bucket) : 0;
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     if (n == 0) return hipGetLastError();
     enqueue_keys_sort(w, s, lay, pos, 3, bk);
-    if (bucket) *bucket = bk;
     const LevelPlan plan = plan_levels(w, lay);
     k_gather<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(pos, mass, eps, w.idx[0], n, w.body,
                                                           w.beps2, w.keys[0],
@@ -2586,10 +2598,9 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
     k_state_kick_drift<<<nchunks, kBoxThreads, 0, s>>>(
         w.body, w.tvel, w.tacc, w.beps2, w.idx[0], n, 0.5 * dt, dt, per, lay.chunks, w.sbody,
         w.svel, use_eps ? w.seps2 : nullptr, w.scidx, w.box, w.hdr);
-    const bool bk = bucket_sort_hint(w, lay);  // read once, as in launch_build
+    const int bk = bucket_sort_hint(w, lay, bucket);  // read once, as in launch_build
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     enqueue_keys_sort(w, s, lay, reinterpret_cast<const double *>(w.sbody), 4, bk);
-    if (bucket) *bucket = bk;
     const LevelPlan plan = plan_levels(w, lay);
     k_gather_state<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(
         w.sbody, w.svel, use_eps ? w.seps2 : nullptr, w.scidx, n, w.idx[0], w.body, w.tvel,
