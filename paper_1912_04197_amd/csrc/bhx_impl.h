@@ -292,6 +292,10 @@ inline int64_t node_capacity(int64_t n, int leaf, int scenes = 1)
     return (int64_t)(scenes > 1 ? scenes : 1) + (int64_t)kMaxLevel * per_level;
 }
 
+// What a new workspace holds before its first build: empty boxes, a zero header with
+// the status words' address, and no cell marks. On the null stream.
+hipError_t launch_init(const Workspace &w);
+
 // Launchers (tree.hip). All enqueue on `s` and never synchronise; `bucket`
 // (if given) receives bucket_sort_hint's `even`. The build
 // launches one kernel per tree level down to one below the depth the

@@ -711,8 +711,6 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     A(dalloc(&w.ninfo, node_cap));
     A(dalloc(&w.inner, node_cap + 1));  // the contact search's cell table: two words at least
     A(dalloc(&w.prefix_mark, bhx::kPrefixCells));
-    if (r == hipSuccess)
-        r = hipMemsetD32((hipDeviceptr_t)w.prefix_mark, INT32_MAX, bhx::kPrefixCells);
     A(dalloc(&w.nmom, node_cap));
     A(dalloc(&w.neps2, node_cap));
     A(dalloc(&w.box, max_scenes));
@@ -761,8 +759,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
         for (auto &ev : c->ev_pool)
             if (r == hipSuccess) r = hipEventCreate(&ev);
     }
-    if (r == hipSuccess) r = hipMemset(w.box, 0xff, max_scenes * sizeof(bhx::SceneBox));
-    if (r == hipSuccess) r = init_headers(w.hdr, 1, w.status_dev);
+    if (r == hipSuccess) r = bhx::launch_init(w);
     if (r == hipSuccess) r = hipDeviceSynchronize();
     if (r != hipSuccess) {
         bh_status st = (r == hipErrorOutOfMemory) ? BH_E_OOM : BH_E_HIP;
