@@ -104,8 +104,8 @@ typedef struct {
                           test, moments and outputs */
     double G;          /* gravitational constant */
     uint32_t flags;    /* BH_FLAG_* */
-    int32_t walk_group; /* target bodies served by one wavefront in the tree
-                           walk: 64, 32 or 16 (64/walk_group lanes per body);
+    int32_t walk_group; /* target bodies served by one workgroup in the tree
+                           walk: 64, 32 or 16 (64/walk_group lanes of a wavefront per body);
                            0 = the library's default (forces: 16 for calls
                            on fewer than 2^17 bodies, else 64; force VJPs: 16
                            below 2^15, 32 below 2^19, else 64). Results do not
@@ -162,7 +162,7 @@ bh_status bh_compute_accel_direct(bh_ctx *ctx, const double *pos, const double *
  * kernels in `precision` (BH_FP64 or BH_FP32C) with gravitational constant G,
  * on hip_stream (NULL = the default stream), asynchronously. It allocates
  * nothing: when the targets alone give too few blocks to fill the GPU
- * (n < 262144), the split-row partial sums go to a library-owned device array
+ * (4096 < n <= 131072), the split-row partial sums go to a library-owned device array
  * of 2^20 doubles (8 MiB) on each device, reserved with the library's code
  * and held until the process ends. Every call on a device shares that array
  * and keeps the last call's contents, so calls that overlap on one device

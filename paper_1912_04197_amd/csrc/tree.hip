@@ -6,13 +6,16 @@
 //      validation); a call may hold many independent scenes, stored as
 //      contiguous body ranges, each with its own root,
 //   2. 63-bit Morton keys on a 2^21 grid,
-//   3. stable LSD radix sort of (key, index), 8-bit digits, LDS ranking, then
-//      (several scenes) two stable passes on the scene index,
+//   3. stable sort of (key, index): radix passes on 8-bit digits over the whole
+//      key, or on its top digits and the rest in LDS; for several scenes passes on
+//      the scene index too,
 //   4. gather of positions, masses and softening into Morton order,
 //   5. top-down octree, one launch per level: each split cell finds its
 //      octant ranges by binary search in the sorted keys,
 //   6. bottom-up moments, one launch per level: mass and centre of mass from
-//      the children by eq. (COMinternal), leaves from their bodies.
+//      the children by eq. (COMinternal), leaves from their bodies; from the
+//      level where nodes are small one launch makes whole subtrees, 5 and 6 both.
+// A single scene of at most kSmallBuild bodies takes one launch for all of it.
 // Every launch reads its sizes from the device tree header, so the sequence
 // needs no host round trip and can be captured in a graph.
 #include <cmath>
@@ -1545,7 +1548,7 @@ __device__ inline void raise_max(int32_t *p, int32_t v)
 // the moments of all their nodes bottom-up, so that the levels from level0 down
 // take one launch whatever their depth instead of two each. Bound by latency (a
 // block's dependent loads, two barriers a step and the atomic on the node count
-// that all blocks share): at 2^20 bodies and leaf 4 it takes 87 us where the
+// that all blocks share): at 2^20 bodies and leaf 4 it takes 66 us where the
 // launches of those levels and their moments took 130, at 50,000 (leaf 8) 11
 // instead of 24; steps of 40,000 to 2^20 bodies are 1 to 5 % shorter. 256 threads
 // a block are 1 % slower at 2^20 (more atomics), 1024 the same. The
