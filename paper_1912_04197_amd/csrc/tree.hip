@@ -22,6 +22,7 @@
 #include <cstddef>
 
 #include "bhx_impl.h"
+#include "sort_pieces.h"
 
 namespace bhx {
 namespace {
@@ -577,11 +578,13 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
 // of a Plummer sphere of 131,072 bodies take 155 us, not 217); then
 // one block per tile of sorted positions takes the buckets that start in its
 // tile (through the end of the last one) and sorts them by the whole key,
-// stably: in LDS when they hold at most its capacity of keys, else in
+// stably: in LDS when they hold at most its capacity of keys, else the last
+// bucket apart from the others and, where it alone is beyond the capacity, in
 // place in global memory with the other key buffer as scratch. A pass whose
 // digit is the same for every key of the range leaves it as it is and is
-// skipped. A stable sort has one result, so this is the order of the
-// eight-pass sort.
+// skipped. No store changes the top bits at any position, so a block that starts
+// late finds its buckets where they were. A stable sort has one result, so this is
+// the order of the eight-pass sort.
 __host__ __device__ inline int top_shift(int passes) { return 63 - 8 * passes; }
 // The buckets of two passes lie inside cells of level kHintLevel, of three of:
 constexpr int kBucketLevel3 = 8;
@@ -776,7 +779,7 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
     __syncthreads();
     const int64_t ra = srange[0], rb = srange[1];
     if (ra >= t1) return;  // no bucket starts here: the block of its start sorts it
-    // the range [ra, rb) one scene at a time
+    // the range [ra, rb) one scene, and one piece of it, at a time
     auto sort_range = [&](const int64_t a, const int64_t m) {
         __syncthreads();  // the previous range is done with the LDS
         if (tid < 2) sdiff[tid] = 0u;
@@ -871,10 +874,13 @@ __global__ __launch_bounds__(Sh::kThreads) void k_sort_local(uint64_t *__restric
             }
         }
     };
+    // (of a range beyond the LDS only the last bucket, which alone leaves the tile,
+    // goes through global memory: see piece_end)
     for (int64_t sa = ra; sa < rb;) {
         const int64_t sb = min(rb, next_start(sa + 1));
-        sort_range(sa, sb - sa);
-        sa = sb;
+        const int64_t pe = piece_end(keys, sa, sb, Sh::kCap, shift);
+        sort_range(sa, pe - sa);
+        sa = pe;
     }
 }
 
