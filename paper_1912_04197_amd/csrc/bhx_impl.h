@@ -8,11 +8,11 @@
 #include <cstdint>
 
 #include "bhx.h"
+#include "capacity.h"
 #include "checks.h"
 
 namespace bhx {
 
-constexpr int kMaxLevel = 21;           // cells on a 2^21 grid per axis
 constexpr int kLevels = kMaxLevel + 1;  // levels 0..21
 constexpr uint32_t kQMax = 2097151u;    // 2^21 - 1
 
@@ -69,8 +69,9 @@ struct TreeHeader {
     int32_t level_count[kLevels + 1];  // nodes created per level (all scenes)
     uint32_t *status;                  // ST_* words, set at creation
     int32_t cell_max[kLevels];         // most bodies in one node per level (0: not looked at)
-    int32_t inner_top;                 // entries of Workspace::inner in use
-    alignas(128) int32_t deep_count;   // nodes k_build_subtrees has created
+    unsigned long long inner_top;      // words of Workspace::inner in use
+    // nodes k_build_subtrees has created (past the node table too)
+    alignas(128) unsigned long long deep_count;
     // and how many of them per level, spread over lines of their own (all blocks
     // adding to one line took longer than the rest of that kernel); added to
     // level_count, and cleared, by the kernel that reports the launch hints
@@ -236,11 +237,14 @@ struct Workspace {
     double *tvel = nullptr;           // [n_cap][3]
     double *tacc = nullptr;           // [n_cap][3]
     Body *sbody = nullptr;            // [n_cap]
-    double *svel = nullptr;           // [n_cap][3]
-    double *seps2 = nullptr;          // [n_cap]
+    double *svel = nullptr;           // [n_cap][3], after sbody in one allocation
+    double *seps2 = nullptr;          // [n_cap], the same
     uint32_t *scidx = nullptr;        // [n_cap]
     NodeInfo *ninfo = nullptr;
-    int32_t *inner = nullptr;     // [node_cap] k_build_subtrees' lists beyond LDS
+    // [inner_words] k_build_subtrees' lists beyond LDS, then the contact search's
+    // table: the memory of the drifted state, which nothing reads after the gather
+    int32_t *inner = nullptr;
+    int64_t inner_words = 0;
     NodeMom *nmom = nullptr;
     double *neps2 = nullptr;
     double *nquad = nullptr;      // [node_cap][6] quadrupoles, only with BH_FLAG_QUAD
@@ -279,18 +283,6 @@ constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
 constexpr int kRedBlocks = 512;
-
-// Upper bound on the node count of the trees of n bodies in up to `scenes`
-// scenes with the given bucket size: one root per scene, and every level
-// below holds at most min(n, 8 n / (leaf + 1)) nodes, because its nodes are
-// disjoint non-empty children of cells holding more than `leaf` bodies.
-inline int64_t node_capacity(int64_t n, int leaf, int scenes = 1)
-{
-    if (n <= 0) return scenes > 1 ? scenes : 1;
-    int64_t internal = n / (leaf + 1);
-    int64_t per_level = 8 * internal < n ? 8 * internal : n;
-    return (int64_t)(scenes > 1 ? scenes : 1) + (int64_t)kMaxLevel * per_level;
-}
 
 // What a new workspace holds before its first build: empty boxes, a zero header with
 // the status words' address, and no cell marks. On the null stream.

@@ -139,7 +139,7 @@ void free_ws(Workspace &w)
     void *ptrs[] = {w.keys[0], w.keys[1], w.idx[0],  w.idx[1],      w.sort_counts,
                     w.sort_totals, w.body, w.beps2, w.ninfo, w.nmom, w.neps2, w.box,
                     w.hdr, w.counts, w.scratch, w.red_part, w.nquad, w.dpart,
-                    w.tvel, w.tacc, w.sbody, w.svel, w.seps2, w.scidx, w.prefix_mark, w.inner};
+                    w.tvel, w.tacc, w.inner, w.scidx, w.prefix_mark};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (w.depth_host) (void)hipHostFree(w.depth_host);
@@ -704,12 +704,15 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     A(dalloc(&w.beps2, n));
     A(dalloc(&w.tvel, 3 * n));
     A(dalloc(&w.tacc, 3 * n));
-    A(dalloc(&w.sbody, n));
-    A(dalloc(&w.svel, 3 * n));
-    A(dalloc(&w.seps2, n));
+    static_assert(4 * bhx::kInnerWords == sizeof(bhx::Body) + 4 * sizeof(double),
+                  "the drifted state: body, velocity, squared softening");
+    w.inner_words = bhx::kInnerWords * n;
+    A(dalloc(&w.inner, w.inner_words));
+    w.sbody = reinterpret_cast<bhx::Body *>(w.inner);
+    w.svel = reinterpret_cast<double *>(w.sbody + n);
+    w.seps2 = w.svel + 3 * n;
     A(dalloc(&w.scidx, n));
     A(dalloc(&w.ninfo, node_cap));
-    A(dalloc(&w.inner, node_cap + 1));  // the contact search's cell table: two words at least
     A(dalloc(&w.prefix_mark, bhx::kPrefixCells));
     A(dalloc(&w.nmom, node_cap));
     A(dalloc(&w.neps2, node_cap));

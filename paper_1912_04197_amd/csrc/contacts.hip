@@ -257,7 +257,7 @@ hipError_t launch_contacts(const Workspace &w, hipStream_t s, const double *radi
     // the build's list buffer is free after it: the cell table, of the deepest
     // level that fits (two words a cell) and has at most about eight cells a body
     int table_level = 0;
-    while (table_level < kMaxLevel && (2ll << (3 * (table_level + 1))) <= w.node_cap &&
+    while (table_level < kMaxLevel && (2ll << (3 * (table_level + 1))) <= w.inner_words &&
            (1ll << (3 * table_level)) < n)
         table_level++;
     int32_t *table = w.inner;

@@ -1568,7 +1568,8 @@ __device__ inline void raise_max(int32_t *p, int32_t v)
 // once; one that splits goes on the block's list, which holds the splitting
 // nodes in level order and is walked backwards for their moments. The list is in
 // LDS and, beyond kSubList entries, in `inner`, of which the block then reserves
-// what its subtrees can need (their levels times their bodies / (leaf + 1)).
+// what its subtrees can need (subtree_splits; in all at most the buffer, see
+// kInnerWords).
 constexpr int kSubThreads = 512;
 constexpr int kSubNodes = kSubThreads / 8;
 constexpr int kSubBodies = 256;  // 1024: 64 uneven scenes take 15 % longer a step; 64: 4 % at 2^20
@@ -1578,15 +1579,21 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
     int level0, const uint64_t *__restrict__ keys, TreeHeader *__restrict__ hdr, NodeInfo *ninfo,
     int64_t node_cap, int leaf, const Body *__restrict__ body, const double *__restrict__ beps2,
     const SceneBox *__restrict__ box, NodeMom *nmom, double *neps2, double *nquad, int use_eps,
-    int32_t *inner)
+    int32_t *inner, int64_t inner_words)
 {
     static_assert(kSubNodes <= 64, "one wave lists the subtrees' roots");
+    static_assert(sizeof(hdr->inner_top) == 8 && sizeof(hdr->deep_count) == 8,
+                  "totals of 2^30 bodies exceed 32 bits");
     constexpr int W = kSubThreads / 64;
     __shared__ int32_t list[kSubList];
-    __shared__ int32_t lbeg[kLevels + 2];     // first list entry per level, from level0
+    // first list entry per level, from level0 (entries are nodes, of which there are
+    // less than 2^31)
+    __shared__ int32_t lbeg[kLevels + 2];
     __shared__ int32_t made[kLevels + 1];     // nodes made per level
     __shared__ uint32_t s_wtot[2][W], s_wdeep[2][W];
-    __shared__ int32_t s_base[2], s_inner, s_need, s_hint;
+    __shared__ int64_t s_base[2], s_inner, s_need;  // s_inner: kNotYet, or the reserved words' first
+    __shared__ int32_t s_hint;
+    constexpr int64_t kNotYet = -1, kNoRoom = -2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int o = tid & 7, gl = lane & ~7;
     int32_t beg, cnt;
@@ -1614,8 +1621,8 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
             if (lane == 0) {
                 lbeg[0] = 0;
                 lbeg[1] = __popcll(sb);
-                s_inner = -1;
-                s_need = (kMaxLevel - level0) * (bodies / (leaf + 1));
+                s_inner = kNotYet;
+                s_need = subtree_splits(level0, bodies, leaf);
                 raise_max(&hdr->cell_max[level0], most);
             }
             if (mine && !split)
@@ -1677,40 +1684,46 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
                     dtot += u;
                 }
                 if (tid == 0) {
-                    s_base[par] = atomicAdd(&hdr->deep_count, (int32_t)btot);
-                    if (top + (int)dtot > kSubList && s_inner < 0)
-                        s_inner = atomicAdd(&hdr->inner_top, s_need);
+                    s_base[par] = (int64_t)atomicAdd(&hdr->deep_count, (unsigned long long)btot);
+                    if (top + (int)dtot > kSubList && s_inner == kNotYet) {
+                        s_inner =
+                            (int64_t)atomicAdd(&hdr->inner_top, (unsigned long long)s_need);
+                        if (s_inner + s_need > inner_words) {
+                            s_inner = kNoRoom;
+                            flag_status(hdr->status, ST_CAPACITY);
+                        }
+                    }
                 }
                 __syncthreads();
                 const int64_t base = (int64_t)deep0 + s_base[par];
-                total += (int32_t)btot;
-                if (base + btot > node_cap) {  // the same on every thread
-                    if (tid == 0) flag_status(hdr->status, ST_CAPACITY);
-                    continue;
-                }
-                const int32_t cid = (int32_t)base + (int32_t)(before + lanes_below(cb));
+                const int64_t cid = base + (int64_t)(before + lanes_below(cb));
                 const int32_t scene_bits = info.lvl_nch & (int32_t)0xffff0000;
-                if (child) {
+                const bool fits = base + btot <= node_cap;  // the same on every thread
+                total += (int32_t)btot;
+                if (child && (fits || cid < node_cap)) {
+                    const int at = top + (int)(dbefore + lanes_below(sb));
                     const NodeInfo ci{start, nb, -1, (level + 1) | scene_bits};
                     ninfo[cid] = ci;
                     if (level + 1 == kHintLevel) atomicMax(&s_hint, nb);
-                    if (!deeper)
-                        node_moments<QUAD, 4>(cid, ci, level + 1, body, beps2, keys, box, nmom, neps2,
-                                     nquad, use_eps);
+                    if (deeper && fits && at < kSubList)
+                        list[at] = (int32_t)cid;
+                    else if (deeper && fits && s_inner != kNoRoom)
+                        inner[s_inner + at - kSubNodes] = (int32_t)cid;
+                    else  // a leaf, or one for want of room
+                        node_moments<QUAD, 4>((int32_t)cid, ci, level + 1, body, beps2, keys, box,
+                                              nmom, neps2, nquad, use_eps);
                 }
-                if (deeper) {
-                    const int at = top + (int)(dbefore + lanes_below(sb));
-                    if (at < kSubList)
-                        list[at] = cid;
-                    else
-                        inner[s_inner + at - kSubNodes] = cid;
+                if (!fits) {
+                    if (tid == 0) flag_status(hdr->status, ST_CAPACITY);
+                    continue;
                 }
                 if (live && o == 0) {
-                    ninfo[id].child0 = cid;
+                    ninfo[id].child0 = (int32_t)cid;
                     ninfo[id].lvl_nch =
                         level | ((int)__popcll((cb >> gl) & 0xffull) << 8) | scene_bits;
                 }
                 top += (int)dtot;
+                if (s_inner == kNoRoom && top > kSubList) top = kSubList;
             }
             if (tid == 0) {
                 made[level + 1] += total;
@@ -2519,7 +2532,7 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
         const int64_t nodes = hint[2 + deep] > 0 ? (int64_t)hint[2 + deep] : 1;
         k_build_subtrees<QUAD><<<blocks_for(nodes, kSubNodes, 1u << 16), kSubThreads, 0, s>>>(
             deep, w.keys[0], w.hdr, w.ninfo, w.node_cap, leaf, w.body, w.beps2, w.box, w.nmom,
-            w.neps2, w.nquad, ue, w.inner);
+            w.neps2, w.nquad, ue, w.inner, w.inner_words);
     } else {
         // the levels from `deep` down: their split and their moments in one block
         k_moments_tail<QUAD><<<1, 1024, 0, s>>>(deep, deep < kMaxLevel ? 1 : 0, w.keys[0], w.hdr,
