@@ -6,6 +6,7 @@
 #include <dlfcn.h>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <string>
@@ -687,6 +688,12 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
     const int max_scenes = cfg->max_scenes > 0 ? cfg->max_scenes : 1;
     int64_t node_cap = bhx::node_capacity(n, cfg->leaf_size, max_scenes);
     if (node_cap > INT32_MAX - 16) node_cap = INT32_MAX - 16;
+#ifdef BHX_CHECKS
+    // a smaller node table, for the tests of its overflow (no input reaches it
+    // otherwise below about 2^29 bodies)
+    if (const char *cap = std::getenv("BHX_CHECKED_NODE_CAP"))
+        node_cap = std::min(node_cap, std::max<int64_t>(max_scenes, std::atoll(cap)));
+#endif
     w.node_cap = node_cap;
     w.sort_blocks_cap = (int)((n + bhx::kSortTile - 1) / bhx::kSortTile);
     w.max_scenes = max_scenes;

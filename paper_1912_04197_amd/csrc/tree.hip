@@ -1116,13 +1116,14 @@ __device__ inline void build_nodes(int level, const uint64_t *__restrict__ keys,
             __syncthreads();  // s_wtot and s_base are rewritten by the next chunk
             if (!split) continue;
             const int64_t cfirst = (int64_t)next_beg + slot;
+            const int32_t scene_bits = info.lvl_nch & (int32_t)0xffff0000;
+            // (counted nodes are written although an overflow leaves them unlinked)
+            if (nonempty && cfirst + rank < node_cap)
+                ninfo[cfirst + rank] = NodeInfo{start, end - start, -1, (level + 1) | scene_bits};
             if (cfirst + nch > node_cap) {
                 if (o == 0) flag_status(status, ST_CAPACITY);
                 continue;
             }
-            const int32_t scene_bits = info.lvl_nch & (int32_t)0xffff0000;
-            if (nonempty)
-                ninfo[cfirst + rank] = NodeInfo{start, end - start, -1, (level + 1) | scene_bits};
             if (o == 0) {
                 ninfo[k].child0 = (int32_t)cfirst;
                 ninfo[k].lvl_nch = level | (nch << 8) | scene_bits;
@@ -2197,9 +2198,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         if (tid == 0) nsplit[(level + 2) % 3] = 0;
         for (int g0 = 8 * wave; g0 < ns; g0 += kSmallThreads / 8) {
             const int g = g0 + (lane >> 3);
-            const bool live = g < ns;
-            const SplitNode nd = now[live ? g : g0];
-            const int first = nd.first, count = live ? nd.count : 0;
+            const SplitNode nd = now[g < ns ? g : g0];
+            const int first = nd.first, count = g < ns ? nd.count : 0;
+            const bool live = count > 0;  // (0: listed by an overflow)
             int start;
             if (count <= kLinearSplit) {
                 uint64_t hist = 0;  // one byte per octant
@@ -2235,12 +2236,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
             }
             base = beg + __builtin_amdgcn_readfirstlane(base);
             at = __builtin_amdgcn_readfirstlane(at);
+            const int id = base + (int)lanes_below(cb);
             if (base + __popcll(cb) > node_cap) {  // the same on every lane
+                // nothing is linked, but all that was counted is written
                 if (lane == 0) flag_status(hdr->status, ST_CAPACITY);
                 if (live && o == 0) ninfo[nd.id] = NodeInfo{first, count, -1, level};
+                if (deeper) next[at + (int)lanes_below(sb)] = SplitNode{0, 0, 0};
+                if (child && id < node_cap) ninfo[id] = NodeInfo{start, end - start, -1, level + 1};
                 continue;
             }
-            const int id = base + (int)lanes_below(cb);
             if (deeper)
                 next[at + (int)lanes_below(sb)] =
                     SplitNode{id, (uint16_t)start, (uint16_t)(end - start)};

@@ -1,0 +1,47 @@
+"""A build that runs out of its node table reports it and stays inside its arrays: the
+checked library, which can be given a smaller table, in a child process. Each scene is
+built (and walked) twice (the second build from the first one's hints), then the same library
+builds it with a whole table."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+pytest.importorskip("torch")
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+WORKLOAD = r"""
+import os, sys
+import numpy as np, torch
+from paper_1912_04197_amd import api, ics, _lib as L
+
+up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+n, leaf = int(sys.argv[1]), int(sys.argv[2])
+s = ics.plummer(n, seed=n)
+pos, mass = up(s.pos), up(s.mass)
+full = api.Context(n, leaf_size=leaf, precision="fp64")
+ref = [full.compute_accel(pos, mass, 0.5, softening=1e-2) for _ in range(2)][1]
+nodes = full.stats()["nnodes"]
+for cap in sorted({1, 2, 9, nodes // 50 + 3, nodes // 3, nodes - 1, nodes}):
+    print("cap", cap, "of", nodes, flush=True)
+    os.environ["BHX_CHECKED_NODE_CAP"] = str(cap)
+    ctx = api.Context(n, leaf_size=leaf, precision="fp64")
+    del os.environ["BHX_CHECKED_NODE_CAP"]
+    for _ in range(2):
+        try:
+            acc = ctx.compute_accel(pos, mass, 0.5, softening=1e-2)
+            assert cap == nodes and torch.equal(acc, ref)
+        except api.BHError as e:
+            assert cap < nodes and e.status == L.BH_E_CAPACITY, e
+"""
+
+
+@pytest.mark.parametrize("n,leaf", [(1000, 1), (4096, 16), (6000, 1), (40000, 4)])
+def test_node_table_overflow(n, leaf):
+    r = subprocess.run([sys.executable, "-c", WORKLOAD, str(n), str(leaf)],
+                       env=dict(os.environ, BHX_LIBRARY="checked", PYTHONPATH=ROOT),
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-2000:]
