@@ -8,12 +8,12 @@
 #include <cstdint>
 
 #include "bhx.h"
+#include "build_plan.h"
 #include "capacity.h"
 #include "checks.h"
 
 namespace bhx {
 
-constexpr int kLevels = kMaxLevel + 1;  // levels 0..21
 constexpr uint32_t kQMax = 2097151u;    // 2^21 - 1
 
 // Device errors, latched until bh_sync(): words of pinned host memory, one an
@@ -79,15 +79,8 @@ struct TreeHeader {
         int32_t level[kLevels];
     } deep[kDeepSlots];
 };
-// The level whose largest node the build reports for the choice of sort.
-constexpr int kHintLevel = 5;
-constexpr int kHintWords = 2 + 2 * kLevels;  // pinned launch-hint words of a workspace
 constexpr int kStatusAt = 64;  // the status words follow, on a line of their own
 static_assert(kHintWords <= kStatusAt, "pinned words");
-// The levels 1..kPrefixLevels of a single scene's tree are read off the
-// sorted keys: a level-kPrefixLevels cell is the key's top 3 kPrefixLevels
-// bits, and the first body of each such cell gives every cell range above it.
-constexpr int kPrefixLevels = 5;
 constexpr int kPrefixCells = 1 << (3 * kPrefixLevels);  // 32768
 constexpr int kPrefixShift = 63 - 3 * kPrefixLevels;
 
@@ -107,7 +100,6 @@ struct Layout {
     int n_groups = 0;
 };
 constexpr int kBoxChunk = 4096;  // bodies per bbox work item
-constexpr int64_t kSmallBuild = 4096;  // a single scene this small is built by one block
 
 // Morton interleave of 21-bit cell coordinates (x in the highest bit of
 // each triplet) and its inverse.
@@ -255,13 +247,10 @@ struct Workspace {
     double *red_part = nullptr;   // [reduction blocks][8][2] compensated partial sums
     double *dpart = nullptr;      // [kDirectPart] partial direct sums of split source ranges
     // Launch hints of the last build, written by the device into pinned host
-    // memory (-1 before the first build): [0] its deepest non-empty level (the
-    // next build launches the levels down to one below it one by one and the
-    // rest in one block), [1] the most bodies in one node of level kHintLevel
-    // (which picks the next build's sort), [2 + l] its node count on level l
-    // (which picks how level l is split), [2 + kLevels + l] the most bodies in
-    // one node of level l (0 or less: not known; which picks the level below
-    // which subtrees are built whole), kHintWords words in all.
+    // memory: the words of HintWord. The next build launches the levels down to
+    // one below the depth one by one and the rest in one block, or whole subtrees
+    // from a level of small nodes on (plan_levels), picks its sort (sort_passes)
+    // and how each level is split (by the node counts).
     int32_t *depth_host = nullptr;
     int32_t *depth_dev = nullptr;  // the same memory as the device sees it
     // the ST_* words, kStatusAt words into the same allocation
@@ -316,15 +305,20 @@ inline bool one_block_build(const Layout &lay)
 // softening and caller indices into the new order.
 hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &lay, bool use_eps,
                               int leaf, double dt, bool *bucket = nullptr);
-// How the next build of `lay` sorts: by buckets after 2 or 3 passes on the top key
-// bits (above kSmallBuild bodies, when the last build's nodes of level kHintLevel,
-// or of a level down to 8, all fit a block's range) or, 0, by passes over the whole
-// keys; a host read of the pinned hints, frozen in a captured graph. Every sort gives
-// the same order; the choice only affects speed. even: whether level kHintLevel's did.
-int bucket_sort_hint(const Workspace &w, const Layout &lay, bool *even = nullptr);
+// How the next build of `lay` sorts, and whether level kHintLevel alone allows it
+// (sort_passes): a host read of the pinned hints, frozen in a captured graph. Every
+// sort gives the same order; the choice only affects speed.
+inline int bucket_sort_hint(const Workspace &w, const Layout &lay, bool *even = nullptr)
+{
+    bool e;
+    return sort_passes(w.depth_host, lay.n, lay.n_scenes, even ? even : &e);
+}
 // The level from which the next build of `lay` builds whole subtrees in one
 // launch, or -1; a host read of the pinned hints like bucket_sort_hint.
-int subtree_hint(const Workspace &w, const Layout &lay);
+inline int subtree_hint(const Workspace &w, const Layout &lay)
+{
+    return plan_levels(w.depth_host, lay.n, lay.n_scenes).sub;
+}
 // scene_of[i] = scene of body i, from device offsets of n_scenes scenes
 hipError_t launch_scene_of(hipStream_t s, const int64_t *offsets, int n_scenes,
                            uint16_t *scene_of);

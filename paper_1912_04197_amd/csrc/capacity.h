@@ -7,6 +7,7 @@
 namespace bhx {
 
 constexpr int kMaxLevel = 21;           // cells on a 2^21 grid per axis
+constexpr int kLevels = kMaxLevel + 1;  // levels 0..21
 
 // Upper bound on the node count of the trees of n bodies in up to `scenes`
 // scenes with the given bucket size: one root per scene, and every level

@@ -352,7 +352,6 @@ __global__ __launch_bounds__(256) void k_keys(const double *__restrict__ pos, in
 
 // Scene index of caller index v: for at most kLdsScenes scenes a binary
 // search of the scene offsets staged in LDS (soff), else scene_of[v].
-constexpr int kLdsScenes = 256;
 __device__ inline uint32_t scene_index(const int64_t *soff, int ns,
                                        const uint16_t *__restrict__ scene_of, uint32_t v)
 {
@@ -586,8 +585,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
 // late finds its buckets where they were. A stable sort has one result, so this is
 // the order of the eight-pass sort.
 __host__ __device__ inline int top_shift(int passes) { return 63 - 8 * passes; }
-// The buckets of two passes lie inside cells of level kHintLevel, of three of:
-constexpr int kBucketLevel3 = 8;
 static_assert(63 - 8 * 2 <= 3 * (kMaxLevel - kHintLevel) &&
                   63 - 8 * 3 <= 3 * (kMaxLevel - kBucketLevel3),
               "a bucket inside a cell");
@@ -606,17 +603,11 @@ struct LocalShape {
 };
 using LocalBig = LocalShape<1024>;
 using LocalSmall = LocalShape<256>;
-constexpr int kBucketMax = 1024;  // bucket bound both shapes are sized for
 // A range whose buckets all hold at most kRankMax keys is sorted by comparison
 // instead of radix passes (200,000 bodies, 18 a level-5 node: builds of 108 us, not
 // 132). Each key's comparisons walk its bucket in LDS, so the cost grows with the
 // bucket.
 constexpr int kRankMax = 32;
-// From this mean number of bodies per level-5 node (two buckets) most ranges hold a
-// larger bucket, and a third pass costs less than radix passes in LDS: builds of
-// 2^20 evenly spread bodies (32 a node) take 194 us with it and 211 without, of 2^21
-// 315 and 357; 500,000 (15) 146 and 140, 200,000 of a ball (18) 118 and 108.
-constexpr int64_t kThirdPassFrom = 24;
 static_assert(LocalBig::kTile > 0 && LocalSmall::kTile > 0, "tiles");
 constexpr int64_t kBigSortFrom = (int64_t)256 * LocalBig::kTile;  // 256 blocks of the big shape
 
@@ -1573,7 +1564,7 @@ __device__ inline void raise_max(int32_t *p, int32_t v)
 // kInnerWords).
 constexpr int kSubThreads = 512;
 constexpr int kSubNodes = kSubThreads / 8;
-constexpr int kSubBodies = 256;  // 1024: 64 uneven scenes take 15 % longer a step; 64: 4 % at 2^20
+// (kSubBodies: with 1024 bodies 64 uneven scenes take 15 % longer a step, with 64 2^20 bodies 4 %)
 constexpr int kSubList = 2048;
 template <bool QUAD>
 __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
@@ -1751,9 +1742,8 @@ __global__ __launch_bounds__(kSubThreads) void k_build_subtrees(
 
 // The end of a build, by one wave: the nodes that k_build_subtrees made and
 // counted apart are added to their levels, and the launch hints go to pinned
-// host memory: the deepest non-empty level, the largest level-kHintLevel node, and
-// the node count and the largest node looked at per level.
-__device__ inline void report_hints(TreeHeader *__restrict__ hdr, int32_t *out)
+// host memory (HintWord; n: the build's bodies).
+__device__ inline void report_hints(TreeHeader *__restrict__ hdr, int32_t n, int32_t *out)
 {
     const int l = threadIdx.x & 63;
     int32_t c = 0, most = 0;
@@ -1769,11 +1759,15 @@ __device__ inline void report_hints(TreeHeader *__restrict__ hdr, int32_t *out)
     }
     const uint64_t some = __ballot(c > 0) & ~1ull;
     if (!out) return;
-    if (l == 0) out[0] = some ? 63 - __builtin_clzll(some) : 0;
-    if (l == kHintLevel) out[1] = most;
+    if (l == 0) {
+        out[kHintDepth] = some ? 63 - __builtin_clzll(some) : 0;
+        out[kHintBodies] = n;
+        out[kHintScenes] = c;
+    }
+    if (l == kHintLevel) out[kHintMost5] = most;
     if (l < kLevels) {
-        out[2 + l] = c;
-        out[2 + kLevels + l] = most;
+        out[kHintCount + l] = c;
+        out[kHintMost + l] = most;
     }
 }
 
@@ -1783,7 +1777,7 @@ __global__ __launch_bounds__(256) void k_moments_level(
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const uint64_t *__restrict__ keys, SceneBox *box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
-    int64_t node_cap, int use_eps, int n_scenes,
+    int64_t node_cap, int use_eps, int n_bodies, int n_scenes,
     int32_t *__restrict__ depth_out)
 {
     moments_nodes<QUAD>(level, hdr->level_count, ninfo, body, beps2, keys, box, nmom, neps2, nquad,
@@ -1791,7 +1785,7 @@ __global__ __launch_bounds__(256) void k_moments_level(
                   (int64_t)gridDim.x * 256);
     // the root level reports the launch hints for the next build
     if (level == 0 && blockIdx.x == 0) {
-        if (threadIdx.x < 64) report_hints(hdr, depth_out);
+        if (threadIdx.x < 64) report_hints(hdr, n_bodies, depth_out);
         for (int sc = threadIdx.x; sc < n_scenes; sc += 256) reset_box(box + sc);
     }
 }
@@ -1811,7 +1805,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_moments_head(
     const Body *__restrict__ body, const double *__restrict__ beps2,
     const uint64_t *__restrict__ keys, SceneBox *box,
     NodeMom *__restrict__ nmom, double *__restrict__ neps2, double *__restrict__ nquad,
-    int64_t node_cap, int use_eps, int32_t *__restrict__ depth_out)
+    int64_t node_cap, int use_eps, int n_bodies, int32_t *__restrict__ depth_out)
 {
     __shared__ NodeMom s_mom[kHeadNodes];
     __shared__ double s_eps2[kHeadNodes], s_quad[QUAD ? 6 * kHeadNodes : 1];
@@ -1850,7 +1844,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_moments_head(
         }
         __syncthreads();
     }
-    if (t < 64) report_hints(hdr, depth_out);
+    if (t < 64) report_hints(hdr, n_bodies, depth_out);
     if (t == 0) reset_box(box);
 }
 
@@ -2320,12 +2314,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     }
     if (tid <= kLevels) hdr->level_count[tid] = scnt[tid];
     if (depth_out && tid == 0) {
-        depth_out[0] = depth;
-        depth_out[1] = -1;  // no sort hint from a one-block build
+        depth_out[kHintDepth] = depth;
+        depth_out[kHintMost5] = -1;  // no sort hint from a one-block build
+        depth_out[kHintBodies] = n;
+        depth_out[kHintScenes] = 1;
     }
     if (depth_out && tid < kLevels) {
-        depth_out[2 + tid] = scnt[tid];
-        depth_out[2 + kLevels + tid] = -1;
+        depth_out[kHintCount + tid] = scnt[tid];
+        depth_out[kHintMost + tid] = -1;
     }
 }
 
@@ -2456,38 +2452,6 @@ void enqueue_keys_sort(const Workspace &w, hipStream_t s, const Layout &lay, con
 #endif
 }
 
-// How a build launches its levels, read once from the previous build's hints:
-// levels 0..deep-1 get a launch each (the deeper ones share one block), and
-// with `prefix` a single scene's levels 1..kPrefixLevels are read off the
-// sorted keys instead (the gather writes the marks k_prefix_levels reads).
-// With sub >= 0 the levels below it, and its moments, are left to one launch
-// of k_build_subtrees: sub is the first level (from the first that is launched) whose
-// nodes held at most kSubBodies bodies in the previous build.
-struct LevelPlan {
-    int deep = kMaxLevel, prev = -1, sub = -1;
-    bool prefix = false;
-};
-
-LevelPlan plan_levels(const Workspace &w, const Layout &lay)
-{
-    LevelPlan p;
-    if (w.depth_host) {
-        p.prev = *(const volatile int32_t *)w.depth_host;
-        if (p.prev >= 0 && p.prev + 1 < p.deep) p.deep = p.prev + 1;
-    }
-    p.prefix = lay.n_scenes == 1 && p.deep > kPrefixLevels && w.prefix_mark != nullptr;
-    if (p.prev >= 0) {
-        const volatile int32_t *most = w.depth_host + 2 + kLevels;
-        // (not the root's: its moments launch reports the hints)
-        for (int l = p.prefix ? kPrefixLevels : 1; l < kMaxLevel && most[l] > 0; l++)
-            if (most[l] <= kSubBodies) {
-                p.sub = l;
-                break;
-            }
-    }
-    return p;
-}
-
 // Stages 5-6 on the sorted bodies (with the plan the gather was launched with).
 // The kernels are short and start cold: code for the quadrupoles beside the plain
 // sums made each of them 1 to 2 us longer, so it is instantiated apart.
@@ -2518,8 +2482,8 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
         // blocks (fewer reservations on the level counter), small ones 256
         // (more CUs for their searches). The choice only affects speed.
         const bool compact =
-            prev >= 0 && level < kMaxLevel && hint[2 + level] > 0 &&
-            hint[3 + level] <= hint[2 + level];
+            prev >= 0 && level < kMaxLevel && hint[kHintCount + level] > 0 &&
+            hint[kHintCount + level + 1] <= hint[kHintCount + level];
         const int64_t threads = level_bound(level, n, ns) * (compact ? 1 : 8);
         const int bs = threads >= 65536 ? 1024 : 256;
         const unsigned g = blocks_for(threads, bs, bs == 1024 ? 1024 : 4096);
@@ -2533,8 +2497,8 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     const int ue = use_eps ? 1 : 0;
     if (plan.sub >= 0) {
         // as many blocks as the level's nodes need, by the previous build's count
-        const int64_t nodes = hint[2 + deep] > 0 ? (int64_t)hint[2 + deep] : 1;
-        k_build_subtrees<QUAD><<<blocks_for(nodes, kSubNodes, 1u << 16), kSubThreads, 0, s>>>(
+        const unsigned blocks = blocks_for(plan.sub_nodes, kSubNodes, 1u << 16);
+        k_build_subtrees<QUAD><<<blocks, kSubThreads, 0, s>>>(
             deep, w.keys[0], w.hdr, w.ninfo, w.node_cap, leaf, w.body, w.beps2, w.box, w.nmom,
             w.neps2, w.nquad, ue, w.inner, w.inner_words);
     } else {
@@ -2546,13 +2510,13 @@ void enqueue_levels(const Workspace &w, hipStream_t s, const Layout &lay, int le
     for (int level = deep - 1; level >= head; level--) {
         const unsigned g = blocks_for(level_bound(level, n, ns), 256, 4096);
         k_moments_level<QUAD><<<g, 256, 0, s>>>(level, w.hdr, w.ninfo, w.body, w.beps2, w.keys[0],
-                                                w.box, w.nmom, w.neps2, w.nquad, w.node_cap, ue, ns,
-                                                w.depth_dev);
+                                                w.box, w.nmom, w.neps2, w.nquad, w.node_cap, ue,
+                                                (int)n, ns, w.depth_dev);
     }
     if (head > 0)
         k_moments_head<QUAD><<<1, kHeadThreads, 0, s>>>(head, w.hdr, w.ninfo, w.body, w.beps2,
                                                         w.keys[0], w.box, w.nmom, w.neps2, w.nquad,
-                                                        w.node_cap, ue, w.depth_dev);
+                                                        w.node_cap, ue, (int)n, w.depth_dev);
 }
 
 }  // namespace
@@ -2575,28 +2539,6 @@ Workspace slot_view(const Workspace &w, const TreeSlots &t, int k)
     v.max_scenes = 1;
     return v;
 }
-
-int bucket_sort_hint(const Workspace &w, const Layout &lay, bool *even)
-{
-    if (even) *even = false;
-    if (lay.n_scenes > kLdsScenes || lay.n <= kSmallBuild || !w.depth_host) return 0;
-    // a range is a tile plus at most one bucket, and a bucket lies inside one
-    // cell of level kHintLevel or kBucketLevel3; a cell that is no node holds at
-    // most a leaf's bodies, and a level's bound holds for the levels below it
-    const volatile int32_t *hint = w.depth_host;
-    if (hint[1] < 0) return 0;
-    if (hint[1] <= kBucketMax) {
-        if (even) *even = true;
-        return lay.n > kThirdPassFrom * (int64_t)hint[2 + kHintLevel] && hint[2 + kHintLevel] > 0
-                   ? 3 : 2;
-    }
-    const volatile int32_t *most = hint + 2 + kLevels;
-    for (int l = kHintLevel + 1; l <= kBucketLevel3; l++)
-        if (most[l] > 0 && most[l] <= kBucketMax) return 3;
-    return 0;
-}
-
-int subtree_hint(const Workspace &w, const Layout &lay) { return plan_levels(w, lay).sub; }
 
 hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
                         const double *mass, const double *eps, int leaf, bool *bucket,
@@ -2625,7 +2567,7 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     if (n == 0) return hipGetLastError();
     enqueue_keys_sort(w, s, lay, pos, 3, bk);
-    const LevelPlan plan = plan_levels(w, lay);
+    const LevelPlan plan = plan_levels(w.depth_host, n, ns);
     k_gather<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(pos, mass, eps, w.idx[0], n, w.body,
                                                           w.beps2, w.keys[0],
                                                           plan.prefix ? w.prefix_mark : nullptr);
@@ -2649,7 +2591,7 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
     const int bk = bucket_sort_hint(w, lay, bucket);  // read once, as in launch_build
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     enqueue_keys_sort(w, s, lay, reinterpret_cast<const double *>(w.sbody), 4, bk);
-    const LevelPlan plan = plan_levels(w, lay);
+    const LevelPlan plan = plan_levels(w.depth_host, n, ns);
     k_gather_state<<<blocks_for(n, 256, 1u << 30), 256, 0, s>>>(
         w.sbody, w.svel, use_eps ? w.seps2 : nullptr, w.scidx, n, w.idx[0], w.body, w.tvel,
         w.beps2, w.keys[0], plan.prefix ? w.prefix_mark : nullptr);
