@@ -355,17 +355,15 @@ typedef struct {
 } bh_tree_view;
 bh_status bh_tree_export(bh_ctx *ctx, bh_tree_view *out);
 
-/* Summary (synchronises): node count and depth of the last build, and which
- * sort it used (bucket_sort = 1: two or three passes on the top key bits, one
- * more on the scene index for a batch, and one block per range of whole buckets,
- * chosen for one scene, or a batch of at most 256 scenes, of more than 4096
- * bodies when the previous build's level-5 nodes held at most 1024 bodies
- * each; 0: three passes and the buckets where only the nodes of a level 6 to 8
- * were that small, eight 8-bit passes, or the one-block build); totals of accepted
+/* Summary (synchronises): node count and depth of the last build, and whether
+ * the nodes of level 5 let it sort by buckets (bucket_sort = 1: one scene, or a
+ * batch of at most 256 scenes, of more than 4096 bodies, whose previous build's
+ * level-5 nodes held at most 1024 bodies each; bh_sort_passes tells which sort
+ * ran); totals of accepted
  * nodes and leaf pairs over all bodies of the last walk (0 unless
  * BH_FLAG_COUNTS); with BH_FLAG_TIMING, the number of tree force evaluations
  * and the summed device time (ms, HIP events on the context's stream) of their
- * build and walk phases since creation or the last bh_timing_reset(). All
+ * build and walk phases (the walk makes a step's second kick) since creation or the last bh_timing_reset(). All
  * sorts give the same order. */
 typedef struct {
     int64_t nnodes;
@@ -376,6 +374,13 @@ typedef struct {
     double build_ms, walk_ms;
 } bh_stats_t;
 bh_status bh_stats(bh_ctx *ctx, bh_stats_t *out);
+
+/* The sort of the last build: 2 or 3, stable 8-bit passes on the top key bits (and
+ * one on the scene index for a batch), then one block per range of whole buckets
+ * of equal top bits, where the previous build's nodes of level 5, or (3) of a
+ * level from 6 to 8, held at most 1024 bodies each; 0, 8-bit passes over the whole
+ * keys, or the one-block build; -1, NULL context. */
+int32_t bh_sort_passes(const bh_ctx *ctx);
 
 /* Zeroes the BH_FLAG_TIMING totals (synchronises). */
 bh_status bh_timing_reset(bh_ctx *ctx);

@@ -348,6 +348,11 @@ class Context:
                 "timed_evals": int(s.timed_evals), "build_ms": float(s.build_ms),
                 "walk_ms": float(s.walk_ms)}
 
+    def sort_passes(self) -> int:
+        """Passes on the top key bits of the last build's sort by buckets (2 or 3), or 0 for
+        passes over the whole keys and the one-block build (see bh_sort_passes)."""
+        return int(self._lib.bh_sort_passes(self._h))
+
     def timing_reset(self):
         self._bind()
         self._rc(self._lib.bh_timing_reset(self._h))

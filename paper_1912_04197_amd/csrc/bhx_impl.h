@@ -277,8 +277,15 @@ constexpr int kRedBlocks = 512;
 // the status words' address, and no cell marks. On the null stream.
 hipError_t launch_init(const Workspace &w);
 
-// Launchers (tree.hip). All enqueue on `s` and never synchronise; `bucket`
-// (if given) receives bucket_sort_hint's `even`. The build
+// The sort that a build enqueued: what bucket_sort_hint gave (0 and false for a
+// one-block build).
+struct SortUsed {
+    bool even = false;
+    int passes = 0;
+};
+
+// Launchers (tree.hip). All enqueue on `s` and never synchronise; `sort` (if
+// given) receives the sort that was enqueued. The build
 // launches one kernel per tree level down to one below the depth the
 // previous build reported (a host read of pinned memory, frozen in a
 // captured graph) and handles deeper levels in one block: any depth is
@@ -292,7 +299,7 @@ struct Advance {
     int substeps = 0;  // > 0: as launch_euler_substeps; 0: as launch_kick_drift
 };
 hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
-                        const double *mass, const double *eps, int leaf, bool *bucket = nullptr,
+                        const double *mass, const double *eps, int leaf, SortUsed *sort = nullptr,
                         const Advance *adv = nullptr);
 inline bool one_block_build(const Layout &lay)
 {
@@ -304,7 +311,7 @@ inline bool one_block_build(const Layout &lay)
 // sorted state of the previous build, and the gather carries velocities,
 // softening and caller indices into the new order.
 hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &lay, bool use_eps,
-                              int leaf, double dt, bool *bucket = nullptr);
+                              int leaf, double dt, SortUsed *sort = nullptr);
 // How the next build of `lay` sorts, and whether level kHintLevel alone allows it
 // (sort_passes): a host read of the pinned hints, frozen in a captured graph. Every
 // sort gives the same order; the choice only affects speed.

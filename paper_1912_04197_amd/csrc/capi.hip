@@ -23,7 +23,7 @@ struct bh_ctx {
     Workspace w;
     std::string err;
     int64_t tree_n = -1;   // n of the last build, -1 before any
-    bool bucket = false;   // bh_stats_t::bucket_sort of the last build
+    bhx::SortUsed sort;    // of the last build
     bool tree_eps = false; // the last build had per-body eps
     int64_t walk_n = -1;   // n of the last walk that wrote counts
     double *diag_out = nullptr;
@@ -297,7 +297,7 @@ bh_status force_tree(bh_ctx *c, const bhx::Layout &lay, const double *pos, const
     {
         Marker m(c, "bhx build");
         BHX_HIP(c, bhx::launch_build(ws, c->stream, lay, pos, mass, eps, c->cfg.leaf_size,
-                                     &c->bucket, adv));
+                                     &c->sort, adv));
     }
     st = record(c, 1);
     if (st) return st;
@@ -328,7 +328,7 @@ bh_status vjp(bh_ctx *c, const double *pos, const double *mass, double softening
         // recomputation and kept in a slot; else build it here
         if (!tree) {
             BHX_HIP(c, bhx::launch_build(c->w, c->stream, single(n), pos, mass, eps,
-                                         c->cfg.leaf_size, &c->bucket));
+                                         c->cfg.leaf_size, &c->sort));
             c->tree_n = n;
             c->tree_eps = eps != nullptr;
         }
@@ -471,7 +471,7 @@ bh_status kdk_step_state(bh_ctx *c, const bhx::Layout &lay, double softening, bo
     {
         Marker mb(c, "bhx build");
         BHX_HIP(c, bhx::launch_build_state(w, c->stream, lay, use_eps, c->cfg.leaf_size, dt,
-                                           &c->bucket));
+                                           &c->sort));
     }
     st = record(c, 1);
     if (st) return st;
@@ -838,7 +838,7 @@ bh_status bh_build_tree(bh_ctx *c, const double *pos, const double *mass, const 
     bh_status s = check_bodies(c, pos, mass, n);
     if (s) return s;
     BHX_HIP(c, bhx::launch_build(c->w, c->stream, single(n), pos, mass, eps, c->cfg.leaf_size,
-                                 &c->bucket));
+                                 &c->sort));
     c->tree_n = n;
     c->tree_eps = eps != nullptr;
     return BH_OK;
@@ -927,7 +927,7 @@ bh_status bh_contact_components(bh_ctx *c, const double *pos, const double *mass
     *n_aggregates = 0;
     if (n == 0) return BH_OK;
     BHX_HIP(c, bhx::launch_build(c->w, c->stream, single(n), pos, mass, radius, c->cfg.leaf_size,
-                                 &c->bucket));
+                                 &c->sort));
     c->tree_n = n;
     c->tree_eps = true;
     auto *counters = (unsigned long long *)c->diag_out;
@@ -1107,7 +1107,7 @@ bh_status bh_stats(bh_ctx *c, bh_stats_t *out)
     std::memset(out, 0, sizeof(*out));
     out->nnodes = v.nnodes;
     out->depth = v.depth;
-    out->bucket_sort = c->bucket ? 1 : 0;
+    out->bucket_sort = c->sort.even ? 1 : 0;
     if (c->walk_n > 0) {
         std::vector<int32_t> h((size_t)c->walk_n * 2);
         BHX_HIP(c, hipMemcpyAsync(h.data(), c->w.counts, h.size() * sizeof(int32_t),
@@ -1125,6 +1125,8 @@ bh_status bh_stats(bh_ctx *c, bh_stats_t *out)
     out->walk_ms = c->walk_ms;
     return BH_OK;
 }
+
+int32_t bh_sort_passes(const bh_ctx *c) { return c ? c->sort.passes : -1; }
 
 bh_status bh_timing_reset(bh_ctx *c)
 {

@@ -2541,10 +2541,10 @@ Workspace slot_view(const Workspace &w, const TreeSlots &t, int k)
 }
 
 hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, const double *pos,
-                        const double *mass, const double *eps, int leaf, bool *bucket,
+                        const double *mass, const double *eps, int leaf, SortUsed *sort,
                         const Advance *adv)
 {
-    if (bucket) *bucket = false;
+    if (sort) *sort = SortUsed{};
     const int64_t n = lay.n;
     const int ns = lay.n_scenes;
     if (one_block_build(lay)) {
@@ -2563,7 +2563,9 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
                                                   w.hdr);
     // the sort is chosen once (a host read of the previous build's hint); a
     // single scene's bucket sort finishes the box in its key kernel
-    const int bk = n > 0 ? bucket_sort_hint(w, lay, bucket) : 0;
+    bool even = false;
+    const int bk = n > 0 ? bucket_sort_hint(w, lay, &even) : 0;
+    if (sort) *sort = SortUsed{even, bk};
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     if (n == 0) return hipGetLastError();
     enqueue_keys_sort(w, s, lay, pos, 3, bk);
@@ -2576,9 +2578,9 @@ hipError_t launch_build(const Workspace &w, hipStream_t s, const Layout &lay, co
 }
 
 hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &lay, bool use_eps,
-                              int leaf, double dt, bool *bucket)
+                              int leaf, double dt, SortUsed *sort)
 {
-    if (bucket) *bucket = false;
+    if (sort) *sort = SortUsed{};
     const int64_t n = lay.n;
     const int ns = lay.n_scenes;
     if (n <= 0) return hipSuccess;
@@ -2588,7 +2590,9 @@ hipError_t launch_build_state(const Workspace &w, hipStream_t s, const Layout &l
     k_state_kick_drift<<<nchunks, kBoxThreads, 0, s>>>(
         w.body, w.tvel, w.tacc, w.beps2, w.idx[0], n, 0.5 * dt, dt, per, lay.chunks, w.sbody,
         w.svel, use_eps ? w.seps2 : nullptr, w.scidx, w.box, w.hdr);
-    const int bk = bucket_sort_hint(w, lay, bucket);  // read once, as in launch_build
+    bool even;
+    const int bk = bucket_sort_hint(w, lay, &even);  // read once, as in launch_build
+    if (sort) *sort = SortUsed{even, bk};
     if (!(bk && ns == 1)) k_box_final<<<sb, 256, 0, s>>>(w.box, ns, lay.offsets, n, w.hdr, w.ninfo);
     enqueue_keys_sort(w, s, lay, reinterpret_cast<const double *>(w.sbody), 4, bk);
     const LevelPlan plan = plan_levels(w.depth_host, n, ns);
