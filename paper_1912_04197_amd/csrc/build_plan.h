@@ -30,10 +30,18 @@ constexpr int kPrefixLevels = 5;
 // The buckets of two passes lie inside cells of level kHintLevel, of three of:
 constexpr int kBucketLevel3 = 8;
 constexpr int kBucketMax = 1024;  // bucket bound the bucket sort's blocks are sized for
+// A range whose buckets all hold at most kRankMax keys is sorted by comparison
+// instead of radix passes (200,000 bodies, 18 a level-5 node: builds of 108 us, not
+// 132). Each key's comparisons walk its bucket in LDS, so the cost grows with the
+// bucket.
+constexpr int kRankMax = 32;
 // From this mean number of bodies per level-5 node (two buckets) most ranges hold a
 // larger bucket, and a third pass costs less than radix passes in LDS: builds of
 // 2^20 evenly spread bodies (32 a node) take 194 us with it and 211 without, of 2^21
-// 315 and 357; 500,000 (15) 146 and 140, 200,000 of a ball (18) 118 and 108.
+// 315 and 357; 500,000 (15) 146 and 140, 200,000 of a ball (18) 118 and 108. Where no
+// level-5 node is larger than a comparison takes, the mean is high because most bodies
+// are in leaves above, and the pass would be lost (20,000 bodies of a ball, leaf 16: 98
+// us with it, 83 without; 131,072, leaf 64: 124 and 113).
 constexpr int64_t kThirdPassFrom = 24;
 constexpr int kLdsScenes = 256;   // scenes whose offsets a sorting block holds
 constexpr int kSubBodies = 256;   // see k_build_subtrees
@@ -107,12 +115,13 @@ inline int sort_passes(const volatile int32_t *hint, int64_t n, int scenes, bool
 {
     *even = false;
     if (!hint || scenes > kLdsScenes || n <= kSmallBuild || hint[kHintMost5] < 0) return 0;
+    const double growth = hint_growth(hint, n, scenes);
     const int64_t nodes = hint[kHintCount + kHintLevel];
     if (hint[kHintMost5] <= kBucketMax) {
         *even = true;
-        return nodes > 0 && n > kThirdPassFrom * nodes ? 3 : 2;
+        return nodes > 0 && n > kThirdPassFrom * nodes && hint[kHintMost5] * growth > kRankMax ? 3
+                                                                                               : 2;
     }
-    const double growth = hint_growth(hint, n, scenes);
     for (int l = kHintLevel + 1; l <= kBucketLevel3; l++)
         if (hint[kHintMost + l] > 0 && hint[kHintMost + l] * growth <= kBucketMax) return 3;
     return 0;

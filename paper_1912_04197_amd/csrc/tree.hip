@@ -603,11 +603,6 @@ struct LocalShape {
 };
 using LocalBig = LocalShape<1024>;
 using LocalSmall = LocalShape<256>;
-// A range whose buckets all hold at most kRankMax keys is sorted by comparison
-// instead of radix passes (200,000 bodies, 18 a level-5 node: builds of 108 us, not
-// 132). Each key's comparisons walk its bucket in LDS, so the cost grows with the
-// bucket.
-constexpr int kRankMax = 32;
 static_assert(LocalBig::kTile > 0 && LocalSmall::kTile > 0, "tiles");
 constexpr int64_t kBigSortFrom = (int64_t)256 * LocalBig::kTile;  // 256 blocks of the big shape
 

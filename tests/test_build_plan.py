@@ -83,7 +83,7 @@ def test_a_large_scene_after_a_small_one(plan):
     assert plan(10488, TINY)["sub"] == 2 and plan(10489, TINY)["sub"] == 3
     assert plan(10489, TINY)["sub_nodes"] == 8 ** 3
     # as many blocks as the level's cells need, not those of the small scene's nodes
-    assert plan(40000, BALL) == dict(deep=7, sub=5, sub_nodes=8 ** 5, prefix=1, passes=3, even=1)
+    assert plan(40000, BALL) == dict(deep=7, sub=5, sub_nodes=8 ** 5, prefix=1, passes=2, even=1)
     assert plan(9000, BALL)["sub_nodes"] == 709
 
 
@@ -110,11 +110,14 @@ def test_scenes(plan):
 
 
 def test_third_pass(plan):
-    def at(nodes, n):
-        return plan(n, _hint(n, [1, 8, 64, 512, 4096, nodes], [0] * 5 + [1024]))["passes"]
+    def at(nodes, n, most=1024, of=None):
+        return plan(n, _hint(of or n, [1, 8, 64, 512, 4096, nodes], [0] * 5 + [most]))["passes"]
 
     assert at(10000, 240000) == 2
     assert at(10000, 240001) == 3
+    # few level-5 nodes because most bodies are in leaves above: all buckets are small
+    assert at(500, 20000, most=32) == 2 and at(500, 20000, most=33) == 3
+    assert at(500, 40001, most=32, of=20000) == 3  # grown past it
     # crowded level-5 nodes: a level of small nodes down to 8
     for most, passes in (([1025, 1024], 3), ([1025, 1025, 1024], 3), ([4000, 4000, 4000, 1024], 3),
                          ([4000, 4000, 4000, 1025, 900], 0), ([1025], 0)):

@@ -36,7 +36,7 @@ def test_third_pass(per_node, want):
     """512 level-5 cells of the diagonal blocks of a cube, evenly filled but one, with
     more bodies than a comparison takes."""
     from paper_1912_04197_amd import api
-    from test_gpu_parity import _dev
+    from test_gpu_parity import _check_tree
 
     rng = np.random.default_rng(per_node)
     cells = np.stack(np.meshgrid(*[np.arange(0, 32, 4)] * 3), -1).reshape(-1, 3)
@@ -44,11 +44,24 @@ def test_third_pass(per_node, want):
     pos = (np.repeat(cells, per_node, 0) + rng.random((512 * per_node, 3))) / 32
     pos[0], pos[-1] = 0.0, 1.0
     pos[1 : 1 + 40] = (cells[0] + rng.random((40, 3))) / 32
-    ctx = api.Context(len(pos), leaf_size=4)
-    mass = np.full(len(pos), 1.0 / len(pos))
+    s = ics.uniform_cube(len(pos), seed=1)
+    s.pos[:] = pos
+    ctx = api.Context(s.n, leaf_size=4)
     for k in range(3):
-        ctx.build_tree(_dev(pos), _dev(mass))
+        _check_tree(ctx, s, 4, False)
         assert ctx.sort_passes() == (want if k else 0)
+
+
+def test_no_third_pass_for_leaves_above():
+    """A ball whose level-5 nodes are few (most bodies are in leaves of level 4) and small."""
+    from paper_1912_04197_amd import api
+    from test_gpu_parity import _dev
+
+    s = ics.uniform_ball(20000, seed=20000)
+    ctx = api.Context(s.n, leaf_size=16)
+    for want in (0, 2, 2):
+        ctx.build_tree(_dev(s.pos), _dev(s.mass))
+        assert ctx.sort_passes() == want
 
 
 def test_batch():
