@@ -191,8 +191,8 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
             const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
             const bool live = on && positive_normal(r2);
             const double ld = ux * dx + uy * dy + uz * dz;
-            double i2;
-            double i3 = inv_cube_sq_f64(r2, i2, cc);
+            double i2, ri;
+            double i3 = inv_cube_sq_f64(r2, i2, ri, cc);
             i3 = live ? i3 : 0.0;
             const double li = live ? ld * i2 : 0.0;
             const double g3 = G * it.m * i3, k3 = 3.0 * li;
@@ -554,8 +554,8 @@ __global__ __launch_bounds__(256) void k_direct_vjp(const double *__restrict__ p
     // adds the pair with source s to (ax, ay, az, am)
     auto pair = [&](const SrcV &s, double dx, double dy, double dz, double r2, double &ax,
                     double &ay, double &az, double &am) {
-        double i2;
-        const double i3 = inv_cube_sq_f64(r2, i2, k), i5 = i3 * i2;
+        double i2, ri;
+        const double i3 = inv_cube_sq_f64(r2, i2, ri, k), i5 = i3 * i2;
         // w = m_p lambda_q - m_q lambda_p
         const double wx = fma(mp, s.lx, -(s.m * lpx)), wy = fma(mp, s.ly, -(s.m * lpy)),
                      wz = fma(mp, s.lz, -(s.m * lpz));

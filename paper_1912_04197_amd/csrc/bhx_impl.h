@@ -193,11 +193,13 @@ __device__ inline double inv_cube_f64(double r2, double &ri, const CubeConsts &k
 }
 
 // The same, with i2 = 1 / r2 = y^2 (1 + e + e^2) up to e^3.
-__device__ inline double inv_cube_sq_f64(double r2, double &i2, const CubeConsts &k)
+template <bool RI = false>
+__device__ inline double inv_cube_sq_f64(double r2, double &i2, double &ri, const CubeConsts &k)
 {
     const double y = __builtin_amdgcn_rsq(r2), y2 = y * y;
     const double e = fma(-r2, y2, 1.0);
     i2 = fma(y2, fma(e, e, e), y2);
+    if (RI) ri = fma(y * e, fma(e, k.h2, 0.5), y);
     const double y3 = y * y2;
     return fma(y3 * e, fma(e, k.c2, k.c1), y3);
 }

@@ -266,8 +266,7 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
                 const bool live = on && positive_normal(r2);
                 double ri = 0.0, i2 = 0.0, i3;
                 if constexpr (QUAD) {
-                    i3 = inv_cube_sq_f64(r2, i2, cc);
-                    if (PHI) ri = r2 * i3;
+                    i3 = inv_cube_sq_f64<PHI>(r2, i2, ri, cc);
                 } else {
                     i3 = inv_cube_f64<PHI>(r2, ri, cc);
                 }
@@ -275,7 +274,7 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
                 sx = fma(c3, dx, sx);
                 sy = fma(c3, dy, sy);
                 sz = fma(c3, dz, sz);
-                if (PHI) sp -= live ? it.m * ri : 0.0;
+                if (PHI) sp = fma(-it.m, live ? ri : 0.0, sp);
                 if constexpr (QUAD && PREC == BH_FP64)
                     if (node && live) {
                         const double *Q = sh.quad + 6 * j;
