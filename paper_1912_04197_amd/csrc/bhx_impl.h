@@ -53,9 +53,12 @@ constexpr int kMaxScenes = 65535;
 
 // Root cube of one scene. lo_enc / hi_enc hold the per-axis minimum and the
 // complement of the maximum as order-preserving integers while the box is being
-// reduced, and all ones (no bodies yet) before and after a build.
+// reduced, and all ones (no bodies yet) before and after a build; the same for
+// mild_acc, zero once a mass or softening out of the ranges of kMild* was found.
 struct SceneBox {
     unsigned long long lo_enc[3], hi_enc[3];
+    uint32_t mild_acc;
+    uint32_t mild;        // masses, softenings and side in those ranges
     double lo[3], hi[3];  // per-axis bounding box
     double L, S;          // root cube side and quantisation scale 2^21 / L
     double x0[3];         // root cube corner
@@ -213,6 +216,43 @@ __device__ inline bool positive_normal(double r2) { return __builtin_amdgcn_clas
 // The FP32 pair terms' form of the same test (finite r2 at or above FLT_MIN).
 constexpr float kFltMin = __FLT_MIN__;
 __device__ inline bool positive_normal_f(float r2) { return r2 >= kFltMin; }
+
+// The FP64 sums form a term as (m r^-3) d, two products fewer than m d r^-3 in each
+// axis. The factor m r^-3 leaves the number range in places where the term does not
+// (m = 1e10 at d = 1e-100). With numbers in the ranges below it is at most 2^930 and, but
+// for m = 0, at least 2^-905 wherever r^2 >= kMildEps2Min; other terms are formed by
+// pair_term_f64.
+constexpr double kMildLength = 0x1p200;  // largest offset
+constexpr double kMildEps2 = 0x1p400;    // largest squared softening
+constexpr double kMildEps2Min = 0x1p-400;
+constexpr double kMildMassMin = 0x1p-300, kMildMassMax = 0x1p300;
+__device__ inline bool mild_mass(double m)
+{
+    return m == 0.0 || (fabs(m) >= kMildMassMin && fabs(m) <= kMildMassMax);
+}
+// The factor of numbers in those ranges, of any r^2, is right: a normal number or zero.
+// Where r^2 is not a positive normal number it is not a number or infinite.
+__device__ inline bool factor_ok(double c) { return __builtin_amdgcn_class(c, 0x168); }
+
+// One term in the order that keeps every intermediate result in range with it: adds m d /
+// r^3 to s and -m / r to ph if r2 is a positive normal number. Returns whether it is, and
+// r^-5 and r^-2 for a quadrupole's term.
+template <bool PHI>
+__device__ inline bool pair_term_f64(double m, double dx, double dy, double dz, double r2,
+                                     double &sx, double &sy, double &sz, double &ph, double &inv5,
+                                     double &inv2)
+{
+    if (!positive_normal(r2)) return false;
+    const double rinv = rsqrt_f64(r2);
+    inv2 = rinv * rinv;
+    const double inv3 = inv2 * rinv;
+    inv5 = inv3 * inv2;
+    sx += m * dx * inv3;
+    sy += m * dy * inv3;
+    sz += m * dz * inv3;
+    if (PHI) ph -= m * rinv;
+    return true;
+}
 
 // Workspace owned by a context; sized once for n_max bodies.
 struct Workspace {

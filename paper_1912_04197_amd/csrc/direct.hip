@@ -79,7 +79,8 @@ struct Target {
 // target meets itself needs no index test. In FP32C, where every pair's FP32
 // softening is a positive normal number, so is its r^2, and the r^2 test is
 // dropped too; other FP32C pairs are tested one by one. In FP64 the pairs of a
-// group are tested together: only a group with a dead pair takes them singly.
+// group are tested together (factor_ok): only a group with a dead or extreme pair
+// takes them singly.
 enum { kPlain = 0, kTest = 1, kSkip = 2 };
 
 // Adds the terms of `cnt` sources at q to the T targets of this lane. skip[t]
@@ -105,14 +106,9 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
             double e2 = eps0sq;
             if constexpr (PEPS) e2 = g.eh + s.eh;
             const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
-            if (positive_normal(r2) && (MODE != kSkip || jj != own)) {
-                double ri;
-                const double c = s.m * inv_cube_f64<PHI>(r2, ri, k);
-                g.ax = fma(c, dx, g.ax);
-                g.ay = fma(c, dy, g.ay);
-                g.az = fma(c, dz, g.az);
-                if (PHI) g.ph -= s.m * ri;
-            }
+            double i5, i2;
+            if (MODE != kSkip || jj != own)
+                pair_term_f64<PHI>(s.m, dx, dy, dz, r2, g.ax, g.ay, g.az, g.ph, i5, i2);
         };
         if constexpr (FULL) {
             // every pair live but a target's own: the group's sums, kept if so
@@ -130,9 +126,9 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
                     double e2 = eps0sq;
                     if constexpr (PEPS) e2 = tg[t].eh + s.eh;
                     const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
-                    live = live && (own || positive_normal(r2));
                     double ri;
                     double c = s.m * inv_cube_f64<PHI>(r2, ri, k);
+                    live = live && (own || factor_ok(c));
                     if (own) c = ri = 0.0;
                     sx[t] = fma(c, dx, sx[t]);
                     sy[t] = fma(c, dy, sy[t]);
@@ -192,18 +188,19 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
 }
 
 // The same, choosing the form: `own` (the same on every active lane) where a
-// target may be among the sources, `soft` (the same on every active lane) where
-// every pair of the group is softened as kPlain asks.
+// target may be among the sources, `plain` (the same on every active lane) where
+// every pair of the group is softened as kPlain asks (FP32C), or its numbers are in
+// the ranges that factor_ok asks for (FP64).
 template <int PREC, bool PEPS, bool PHI, int T>
 __device__ __forceinline__ void add_group(const Src<PREC, PEPS> *q, int cnt, bool full,
                                           Target (&tg)[T], double eps0sq, float eps0f,
-                                          const int (&skip)[T], bool own, bool soft)
+                                          const int (&skip)[T], bool own, bool plain)
 {
-    if (!full)
+    if (!full || (PREC == BH_FP64 && !plain))
         sum_group<PREC, PEPS, PHI, T, kSkip, false>(q, cnt, tg, eps0sq, eps0f, skip);
     else if (own)
         sum_group<PREC, PEPS, PHI, T, kSkip, true>(q, cnt, tg, eps0sq, eps0f, skip);
-    else if (PREC == BH_FP64 || soft)
+    else if (PREC == BH_FP64 || plain)
         sum_group<PREC, PEPS, PHI, T, kPlain, true>(q, cnt, tg, eps0sq, eps0f, skip);
     else
         sum_group<PREC, PEPS, PHI, T, kTest, true>(q, cnt, tg, eps0sq, eps0f, skip);
@@ -227,11 +224,27 @@ __device__ inline Target load_target(const double *__restrict__ pos,
     return g;
 }
 
-// A softening that makes every r^2 of its target a positive normal FP32
-// number, given that the other half is a number (not NaN).
-__device__ inline bool softened(bool peps, float ehf, float eps0f)
+// A target all of whose groups may be plain, given plain sources. FP32C: its softening
+// makes every r^2 a positive normal FP32 number if the other half is a number (not NaN).
+// FP64: its numbers are in the ranges that factor_ok asks for.
+template <int PREC, bool PEPS>
+__device__ inline bool plain_target(const Target &g, double eps0sq, float eps0f)
 {
-    return positive_normal_f(peps ? ehf : eps0f);
+    if (PREC == BH_FP64)
+        return fabs(g.x) + fabs(g.y) + fabs(g.z) <= 0.25 * kMildLength &&
+               (PEPS ? g.eh : eps0sq) <= 0.5 * kMildEps2;
+    return positive_normal_f(PEPS ? g.ehf : eps0f);
+}
+template <int PREC, bool PEPS>
+__device__ inline bool plain_source(const Src<PREC, PEPS> &s)
+{
+    if constexpr (PREC == BH_FP64) {
+        bool ok = fabs(s.x) + fabs(s.y) + fabs(s.z) <= 0.25 * kMildLength && mild_mass(s.m);
+        if constexpr (PEPS) ok = ok && s.eh <= 0.5 * kMildEps2;
+        return ok;
+    } else {
+        return !PEPS || s.eh >= 0.f;
+    }
 }
 
 template <int PREC, bool PEPS, bool PHI>
@@ -251,26 +264,27 @@ __global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
     Target tg[kTargets];
     int64_t ti[kTargets];
     const float eps0f = (float)eps0sq;
-    bool soft = true;
+    bool plain = true;
 #pragma unroll
     for (int t = 0; t < kTargets; t++) {
         ti[t] = b0 + 64 * t + lane;
         // lanes past the end repeat the last target; nothing of theirs is stored
         tg[t] = load_target<PEPS>(pos, eps, ti[t] < n ? ti[t] : n - 1);
-        soft = soft && softened(PEPS, tg[t].ehf, eps0f);
+        plain = plain && plain_target<PREC, PEPS>(tg[t], eps0sq, eps0f);
     }
-    soft = __ballot(!soft) == 0;
+    plain = __ballot(!plain) == 0;
     // this block row's sources: [s_lo, s_hi)
     const int64_t s_lo = (int64_t)blockIdx.y * chunk;
     const int64_t s_hi = s_lo + chunk < n ? s_lo + chunk : n;
     for (int64_t base = s_lo; base < s_hi; base += kTile) {
         const int64_t j = base + tid;
-        bool number = true;  // no NaN among the tile's FP32 softenings
+        bool ok = true;  // the tile's sources are plain
         if (j < s_hi) {
-            src[tid] = load_source<PREC, PEPS>(pos, mass, eps, j);
-            if constexpr (PREC != BH_FP64 && PEPS) number = src[tid].eh >= 0.f;
+            const S s = load_source<PREC, PEPS>(pos, mass, eps, j);
+            src[tid] = s;
+            ok = plain_source<PREC, PEPS>(s);
         }
-        const bool tile_ok = __syncthreads_and(number);
+        const bool tile_ok = __syncthreads_and(ok);
         const int cnt = (int)((s_hi - base) < kTile ? (s_hi - base) : kTile);
         const bool own = base < b0 + kBlockTargets && base + cnt > b0;
 #pragma unroll 1
@@ -283,7 +297,7 @@ __global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
                 skip[t] = own && at >= 0 && at < gc ? (int)at : -1;
             }
             add_group<PREC, PEPS, PHI, kTargets>(src + g * kGroup, gc, gc == kGroup, tg, eps0sq,
-                                                 eps0f, skip, own, soft && tile_ok);
+                                                 eps0f, skip, own, plain && tile_ok);
         }
         __syncthreads();
     }
@@ -369,16 +383,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_direct_small(
     const int b0 = (int)blockIdx.x * TG, i = b0 + tl;
     const float eps0f = (float)eps0sq;
     Target tg[1] = {load_target<PEPS>(pos, eps, i < n ? i : n - 1)};
-    const bool soft = __ballot(!softened(PEPS, tg[0].ehf, eps0f)) == 0;
+    const bool plain = __ballot(!plain_target<PREC, PEPS>(tg[0], eps0sq, eps0f)) == 0;
     for (int base = 0; base < n; base += kShares * kGroup) {
-        bool number = true;
+        bool ok = true;
         const int in = n - base < kShares * kGroup ? n - base : kShares * kGroup;
         for (int k = tid; k < in; k += kSmallThreads) {
             const S s = load_source<PREC, PEPS>(pos, mass, eps, base + k);
             *(S *)(tile + (k / kGroup) * kStride + (k % kGroup) * (int)sizeof(S)) = s;
-            if constexpr (PREC != BH_FP64 && PEPS) number = number && s.eh >= 0.f;
+            ok = ok && plain_source<PREC, PEPS>(s);
         }
-        const bool tile_ok = __syncthreads_and(number);
+        const bool tile_ok = __syncthreads_and(ok);
         const int left = in - share * kGroup;
         const int cnt = left < 0 ? 0 : left < kGroup ? left : kGroup;
         const int at = i - base - share * kGroup;
@@ -390,7 +404,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_direct_small(
         const bool full = __ballot(cnt != kGroup) == 0;
         if (__ballot(cnt > 0) != 0)
             add_group<PREC, PEPS, PHI, 1>((const S *)(tile + share * kStride), cnt, full, tg,
-                                          eps0sq, eps0f, skip, own, soft && tile_ok);
+                                          eps0sq, eps0f, skip, own, plain && tile_ok);
         __syncthreads();
     }
     // the shares in a fixed order: over the wave, then over the waves

@@ -110,6 +110,13 @@ __device__ inline double order_dec(unsigned long long e)
 __device__ inline void reset_box(SceneBox *box)
 {
     for (int a = 0; a < 3; a++) box->lo_enc[a] = box->hi_enc[a] = ~0ull;
+    box->mild_acc = ~0u;
+}
+
+// Whether a body's mass and softening (squared) leave the ranges of kMild*.
+__device__ inline bool wild_body(double m, double e2)
+{
+    return !(mild_mass(m) && e2 <= kMildEps2);
 }
 
 // One work item: a chunk of at most kBoxChunk bodies of one scene (for one
@@ -144,22 +151,21 @@ __global__ __launch_bounds__(kBoxThreads) void k_box_chunk(const double *__restr
     }
     if (end > n) end = n;
     double lo[3] = {kInf, kInf, kInf}, hi[3] = {-kInf, -kInf, -kInf};
-    bool bad = false;
+    bool bad = false, wild = false;
     for (int64_t i = first + threadIdx.x; i < end; i += kBoxThreads) {
         double x[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
-        double m = mass[i];
+        double m = mass[i], e = eps ? eps[i] : 0.0;
         bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
         bad |= !(isfinite(m) && m >= 0.0);
-        if (eps) {
-            double e = eps[i];
-            bad |= !(isfinite(e) && e >= 0.0);
-        }
+        bad |= !(isfinite(e) && e >= 0.0);
+        wild |= wild_body(m, e * e);
         for (int a = 0; a < 3; a++) {
             lo[a] = fmin(lo[a], x[a]);
             hi[a] = fmax(hi[a], x[a]);
         }
     }
     if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(hdr->status, ST_NONFINITE);
+    if (__ballot(wild) && (threadIdx.x & 63) == 0) atomicAnd(&box[sc].mild_acc, 0u);
     __shared__ double red[kBoxThreads / 64][6];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int a = 0; a < 3; a++) {
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
     }
     if (end > n) end = n;
     double lo[3] = {kInf, kInf, kInf}, hi[3] = {-kInf, -kInf, -kInf};
-    bool bad = false;
+    bool bad = false, wild = false;
     for (int64_t i = first + threadIdx.x; i < end; i += kBoxThreads) {
         const Body b = body[i];
         const double x0[3] = {b.x, b.y, b.z};
@@ -215,7 +221,9 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
         }
         sbody[i] = Body{x[0], x[1], x[2], b.m};
         for (int a = 0; a < 3; a++) svel[3 * i + a] = v[a];
-        if (seps2) seps2[i] = beps2[i];
+        const double e2 = seps2 ? beps2[i] : 0.0;
+        if (seps2) seps2[i] = e2;
+        wild |= wild_body(b.m, e2);
         scidx[i] = cidx[i];
         bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
         for (int a = 0; a < 3; a++) {
@@ -224,6 +232,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_state_kick_drift(
         }
     }
     if (__ballot(bad) && (threadIdx.x & 63) == 0) flag_status(hdr->status, ST_NONFINITE);
+    if (__ballot(wild) && (threadIdx.x & 63) == 0) atomicAnd(&box[sc].mild_acc, 0u);
     __shared__ double red[kBoxThreads / 64][6];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int a = 0; a < 3; a++) {
@@ -291,6 +300,7 @@ __device__ inline void scene_root_cube(SceneBox &out, const SceneBox &in, bool a
         hi[a] = any ? order_dec(~in.hi_enc[a]) : 0.0;
     }
     root_cube(out, lo, hi);
+    out.mild = in.mild_acc != 0u && out.L <= kMildLength ? 1u : 0u;
 }
 
 // One thread per scene: root cube from the box, and the scene's root node
@@ -2037,6 +2047,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     static_assert(kSmallThreads / 16 == 64, "one row of 16 lanes a lane");
     __shared__ double red[64][6];
     __shared__ SceneBox sbox;
+    __shared__ bool swild[kSmallThreads / 64];
     __shared__ int32_t scnt[kLevels + 1];
     __shared__ int32_t nsplit[3];
     const int n = (int)n64;
@@ -2049,7 +2060,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
     double x[kPer][3];
     {
         double lo[3] = {kInf, kInf, kInf}, hi[3] = {-kInf, -kInf, -kInf};
-        bool bad = false;
+        bool bad = false, wild = false;
 #pragma unroll
         for (int j = 0; j < kPer; j++) {
             const int i = tid + j * kSmallThreads;
@@ -2072,16 +2083,17 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
             const double m = mass[i];
             bad |= !(isfinite(x[j][0]) && isfinite(x[j][1]) && isfinite(x[j][2]));
             bad |= !(isfinite(m) && m >= 0.0);
-            if (use_eps) {
-                const double e = eps[i];
-                bad |= !(isfinite(e) && e >= 0.0);
-            }
+            const double e = use_eps ? eps[i] : 0.0;
+            bad |= !(isfinite(e) && e >= 0.0);
+            wild |= wild_body(m, e * e);
             for (int a = 0; a < 3; a++) {
                 lo[a] = fmin(lo[a], x[j][a]);
                 hi[a] = fmax(hi[a], x[j][a]);
             }
         }
         if (__ballot(bad) && lane == 0) flag_status(hdr->status, ST_NONFINITE);
+        const bool any_wild = __ballot(wild) != 0;
+        if (lane == 0) swild[wave] = any_wild;
         for (int a = 0; a < 3; a++) {
             const double l = row_min(lo[a]), h = row_max(hi[a]);
             if ((lane & 15) == 0) {
@@ -2102,8 +2114,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
                 const double u = __shfl_xor(v[a], o);
                 v[a] = a < 3 ? fmin(v[a], u) : fmax(v[a], u);
             }
+        const bool any_wild = __ballot(lane < kSmallThreads / 64 && swild[lane & 15]) != 0;
         if (lane == 0) reset_box(&sbox);
         root_cube(sbox, v, v + 3, lane, 64);
+        if (lane == 0) sbox.mild = !any_wild && sbox.L <= kMildLength ? 1u : 0u;
     }
     __syncthreads();
     if (tid < (int)(sizeof(SceneBox) / 8)) ((uint64_t *)box)[tid] = ((const uint64_t *)&sbox)[tid];

@@ -178,6 +178,16 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
             __ballot(!valid || positive_normal_f(PEPS ? e2hB : eps0f)) == ~0ull;
         const int woff = bq >= 32 ? 1 : 0;
         const CubeConsts cc = cube_consts();
+        // FP64: no factor m r^-3 is out of range while r^2 >= kMildEps2Min, and every
+        // pair is softened that far. Such waves test no term; the others, whose rare
+        // loops cost the batch registers, have code of their own.
+        // (softened, 100,000 bodies of a rubble pile at leaf 8: 398 us with a test
+        // of every term for a positive normal r^2, 384 without; unsoftened, 50,000 of
+        // a ball: 158 before, 160 with the terms outside the range kept.)
+        const bool mild = PREC == BH_FP64 && box[scene].mild != 0 &&
+                          (PEPS || eps0sq <= kMildEps2);
+        const bool mild_soft = mild && (PEPS ? __ballot(!(ebh >= kMildEps2Min)) == 0
+                                             : eps0sq >= kMildEps2Min);
 
         double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
         int32_t cnode = 0, cpair = 0;
@@ -193,8 +203,9 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
             for (int i = lane; i < 2 * GB; i += 64) pcnt[i] = 0;
 
         // Stages the batch and evaluates it: the dense items by a sweep of the
-        // lanes of each body, the sparse ones as pairs.
-        auto evaluate = [&](walkx::Batch &bt) {
+        // lanes of each body, the sparse ones as pairs. `plain`: mild_soft.
+        auto evaluate = [&](auto plain, walkx::Batch &bt) {
+            constexpr bool kPlain = decltype(plain)::value;
             const int c = bt.count;
             // Load item `lane` and its body mask; the split below decides where
             // in LDS it goes.
@@ -257,19 +268,27 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
                 }
             }
             walkx::wave_sync();
-            // one FP64 term of a source on a target, the mass and the softening
-            // test in its factor: zero unless `on` and r^2 is a positive normal number
+            // One FP64 term of a source on a target, nothing unless `on` and (not
+            // kPlain) r^2 is large enough for its factor; otherwise `lost` is set.
+            // (nothing is tried where !mild: offsets may be infinite)
+            bool lost = !kPlain && !mild;
+            const int nd_try = kPlain || PREC != BH_FP64 || mild ? nd : 0;
+            const int np_try = kPlain || PREC != BH_FP64 || mild ? np : 0;
+            constexpr double near = kMildEps2Min;
             auto term64 = [&](const ItemD &it, double bx, double by, double bz, double e2, bool on,
                               bool node, int j, double &sx, double &sy, double &sz, double &sp) {
                 const double dx = it.x - bx, dy = it.y - by, dz = it.z - bz;
                 const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
-                const bool live = on && positive_normal(r2);
-                double ri = 0.0, i2 = 0.0, i3;
-                if constexpr (QUAD) {
-                    i3 = inv_cube_sq_f64<PHI>(r2, i2, ri, cc);
-                } else {
-                    i3 = inv_cube_f64<PHI>(r2, ri, cc);
+                bool live = on;
+                if constexpr (!kPlain) {
+                    live = on && r2 >= near;
+                    lost = lost || (on && !live);
                 }
+                double ri = 0.0, i2 = 0.0, i3;
+                if constexpr (QUAD)
+                    i3 = inv_cube_sq_f64<PHI>(r2, i2, ri, cc);
+                else
+                    i3 = inv_cube_f64<PHI>(r2, ri, cc);
                 const double c3 = live ? it.m * i3 : 0.0;
                 sx = fma(c3, dx, sx);
                 sy = fma(c3, dy, sy);
@@ -286,7 +305,7 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
                 LdsPtr<ItemD> ip = lds_base(sh.items + sub);
                 LdsPtr<uint64_t> mp = lds_base(sh.mask + sub);
 #pragma unroll 2
-                for (int jj = 0; jj < nd; jj += LPB) {
+                for (int jj = 0; jj < nd_try; jj += LPB) {
                     const int j = jj + sub;  // past nd: a slot that is not taken
                     const ItemD it = ItemD{ip[jj].x, ip[jj].y, ip[jj].z, ip[jj].m};
                     const bool on = j < nd && ((mp[jj] >> bq) & 1ull);
@@ -360,8 +379,19 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
             }
             // Pairs: lane i takes pair i of the list; its body's coordinates come
             // from that body's lane. Each pair term goes into the body's FP64 sums.
+            auto add_pair = [&](int b, double fx, double fy, double fz, double fp) {
+                __hip_atomic_fetch_add(&pacc[3 * b], fx, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&pacc[3 * b + 1], fy, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&pacc[3 * b + 2], fz, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (PHI)
+                    __hip_atomic_fetch_add(&pphi[b], fp, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
 #pragma unroll 1
-            for (int i0 = 0; i0 < np; i0 += 64) {
+            for (int i0 = 0; i0 < np_try; i0 += 64) {
                 const int i = i0 + lane;
                 const bool on = i < np;
                 const uint32_t r = sh.rec[on ? i : i0];
@@ -397,18 +427,50 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
                     if (PHI) fp = (double)gpf;
                 }
                 if (on) {
-                    __hip_atomic_fetch_add(&pacc[3 * b], fx, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __hip_atomic_fetch_add(&pacc[3 * b + 1], fy, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __hip_atomic_fetch_add(&pacc[3 * b + 2], fz, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (PHI)
-                        __hip_atomic_fetch_add(&pphi[b], fp, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    add_pair(b, fx, fy, fz, fp);
                     if (CNT)
                         __hip_atomic_fetch_add(&pcnt[2 * b + (node ? 0 : 1)], 1, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            // the terms that are not in the sums yet, one by one
+            if constexpr (PREC == BH_FP64 && !kPlain) {
+                if (__ballot(lost) != 0) {
+                    auto left = [&](const auto &it, int k, const Body &t, double th, double &sx,
+                                    double &sy, double &sz, double &sp) {
+                        const double dx = it.x - t.x, dy = it.y - t.y, dz = it.z - t.z;
+                        const double r2 = fma(
+                            dx, dx, fma(dy, dy, fma(dz, dz, PEPS ? th + sh.e2h[PEPS ? k : 0] : eps0sq)));
+                        if (mild && r2 >= near) return;
+                        double i5, i2;
+                        const bool live =
+                            pair_term_f64<PHI>(it.m, dx, dy, dz, r2, sx, sy, sz, sp, i5, i2);
+                        if constexpr (QUAD && PREC == BH_FP64)
+                            if (live && sh.src[k] < 0)
+                                quad_term(sh.quad + 6 * k, dx, dy, dz, i5, i2, sx, sy, sz, sp);
+                    };
+#pragma unroll 1
+                    for (int j = sub; j < nd; j += LPB) {
+                        if (!((sh.mask[j] >> bq) & 1ull)) continue;
+                        left(sh.items[j], j, me, ebh, ax, ay, az, ph);
+                        if (CNT && !mild) {
+                            if (sh.src[CNT ? j : 0] < 0)
+                                cnode++;
+                            else
+                                cpair++;
+                        }
+                    }
+#pragma unroll 1
+                    for (int i = lane; i < np; i += 64) {
+                        const int k = sh.rec[i] >> 6, b = sh.rec[i] & 63;
+                        double fx = 0.0, fy = 0.0, fz = 0.0, fp = 0.0;
+                        left(sh.items[k], k, body[g0 + b], PEPS ? 0.5 * beps2[g0 + b] : 0.0, fx, fy, fz, fp);
+                        add_pair(b, fx, fy, fz, fp);
+                        if (CNT && !mild)
+                            __hip_atomic_fetch_add(&pcnt[2 * b + (sh.src[CNT ? k : 0] < 0 ? 0 : 1)],
+                                                   1, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                 }
             }
             walkx::wave_sync();
@@ -416,7 +478,10 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_walk(
 
         walkx::Batch bt;
         bt.start = (uint32_t)(kBatch * (wave - 1));
-        while (walkx::next_batch(L, wave - 1, bt)) evaluate(bt);
+        if (PREC == BH_FP64 && mild_soft)
+            while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::true_type{}, bt);
+        else
+            while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::false_type{}, bt);
 
         // add the lanes' partial sums of each body in a fixed order
 #pragma unroll
