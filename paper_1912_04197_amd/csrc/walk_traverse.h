@@ -88,14 +88,15 @@ struct Lds {
 constexpr uint32_t kDone = 0x80000000u;
 
 // The squared cell side per level, (L 2^-l)^2: the root's times 4^-l, which is
-// the same number while it is normal down to the last level; a root cube so
-// small that it is not (side below about 1e-139) reads its table.
+// the same number while it is normal from the first level to the last; a root cube
+// so small or large that it is not (side below about 1e-139 or above 1e154) reads its
+// table.
 struct SideSq {
     const double *tab;
     double root;
     bool scaled;
     __device__ explicit SideSq(const SceneBox &b)
-        : tab(b.s2), root(b.s2[0]), scaled(b.s2[kMaxLevel] > 0x1p-1000)
+        : tab(b.s2), root(b.s2[0]), scaled(b.s2[kMaxLevel] > 0x1p-1000 && b.s2[0] < __builtin_huge_val())
     {
     }
     __device__ double at(int level) const
