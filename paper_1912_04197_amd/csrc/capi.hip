@@ -54,6 +54,7 @@ struct bh_ctx {
     int gdepth = -1;  // depth hint the captured step's build was launched with
     int gbucket = -1; // sort the captured step's build was launched with (bucket_sort_hint)
     int gsub = -1;    // level of its subtrees (subtree_hint)
+    bhx::Recapture gagain;
 };
 
 namespace {
@@ -528,11 +529,14 @@ bh_status run_steps(bh_ctx *c, const bhx::Layout &lay, double *pos, double *vel,
     // capture had no hint yet (it launched every level).
     const int depth_now = c->w.depth_host ? *(const volatile int32_t *)c->w.depth_host : -1;
     const bool deeper = depth_now >= 0 && (c->gdepth < 0 || depth_now > c->gdepth + 1);
-    // likewise when the hints now pick another sort (same order, other speed)
+    // likewise when the hints now pick another sort or another level for the subtrees
+    // that are built whole (same tree, other speed), but not call after call
     const int bucket_now = bhx::bucket_sort_hint(c->w, lay);
-    // or another level for the subtrees that are built whole
     const int sub_now = bhx::subtree_hint(c->w, lay);
-    if (!c->gexec || key != c->gkey || deeper || bucket_now != c->gbucket || sub_now != c->gsub) {
+    const bool other = !c->gexec || key != c->gkey;
+    if (other) c->gagain = bhx::Recapture{};
+    if (other || deeper ||
+        c->gagain.due(c->w.depth_host, c->gbucket, c->gsub, bucket_now, sub_now)) {
         if (c->gexec) {
             (void)hipGraphExecDestroy(c->gexec);
             c->gexec = nullptr;

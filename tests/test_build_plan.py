@@ -28,6 +28,56 @@ int main(int argc, char **argv)  // n, scenes, hint words
 """
 
 
+RECAPTURE = r"""
+#include <cstdio>
+#include "build_plan.h"
+using namespace bhx;
+static int captures(int calls, int period, int most)  // the wanted level turns every `period` calls
+{
+    int32_t hint[kHintWords] = {};
+    Recapture r;
+    int sub = 5, n = 0;
+    for (int k = 0; k < calls; k++) {
+        const int now = 5 + (k / period) % 2;
+        hint[kHintMost + 5] = hint[kHintMost + 6] = most;
+        if (r.due(hint, 2, sub, 2, now)) sub = now, n++;
+    }
+    return n;
+}
+int main()
+{
+    int32_t hint[kHintWords] = {};
+    Recapture r;
+    // nothing new; a first change at once; a lasting one after at most kLongest calls
+    printf("%d", r.due(hint, 2, 5, 2, 5));
+    printf("%d", r.due(hint, 2, 5, 3, 5));
+    int waited = 0;
+    for (int k = 0; k < 10; k++)
+        for (int w = 0; !r.due(hint, 3, 5, 2, 5); w++) waited = w + 1 > waited ? w + 1 : waited;
+    printf(" %d", waited);
+    // what has stopped to fit: at once, whatever the wait
+    printf(" %d", r.due(hint, 2, 5, 0, 5));
+    hint[kHintMost + 5] = 1025;
+    printf("%d", r.due(hint, 2, 5, 2, 6));
+    hint[kHintMost + 5] = 1024;
+    printf("%d", r.due(hint, 2, 5, 2, 6));
+    printf(" %d %d\n", captures(1000, 1, 256), captures(1000, 1, 2000));
+}
+"""
+
+
+def test_recapture(tmp_path):
+    (tmp_path / "r.cpp").write_text(RECAPTURE)
+    subprocess.run(["g++", "-std=c++17", "-D__host__=", "-D__device__=", "-I",
+                    os.path.join(ROOT, "paper_1912_04197_amd", "csrc"), str(tmp_path / "r.cpp"),
+                    "-o", str(tmp_path / "r")], check=True)
+    out = subprocess.run([str(tmp_path / "r")], capture_output=True, text=True,
+                         check=True).stdout.split()
+    assert out[:3] == ["01", "64", "110"]
+    assert int(out[3]) <= 30  # a level that hovers: not a capture a call
+    assert int(out[4]) == 999  # subtrees that are too large: each time
+
+
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
