@@ -230,10 +230,6 @@ __device__ inline bool mild_mass(double m)
 {
     return m == 0.0 || (fabs(m) >= kMildMassMin && fabs(m) <= kMildMassMax);
 }
-// The factor of numbers in those ranges, of any r^2, is right: a normal number or zero.
-// Where r^2 is not a positive normal number it is not a number or infinite.
-__device__ inline bool factor_ok(double c) { return __builtin_amdgcn_class(c, 0x168); }
-
 // One term in the order that keeps every intermediate result in range with it: adds m d /
 // r^3 to s and -m / r to ph if r2 is a positive normal number. Returns whether it is, and
 // r^-5 and r^-2 for a quadrupole's term.

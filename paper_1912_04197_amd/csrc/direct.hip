@@ -79,8 +79,11 @@ struct Target {
 // target meets itself needs no index test. In FP32C, where every pair's FP32
 // softening is a positive normal number, so is its r^2, and the r^2 test is
 // dropped too; other FP32C pairs are tested one by one. In FP64 the pairs of a
-// group are tested together (factor_ok): only a group with a dead or extreme pair
-// takes them singly.
+// group are tested together, by their factors m r^-3: a pair counts if that is a
+// normal number, which it is only of a positive normal r^2 and in the number range, or
+// zero with the mass. Where no factor can underflow (kPlain) the rest is seen in the
+// sums: a factor that is infinite or not a number leaves none of them finite. Only a
+// group with a dead or extreme pair takes them singly.
 enum { kPlain = 0, kTest = 1, kSkip = 2 };
 
 // Adds the terms of `cnt` sources at q to the T targets of this lane. skip[t]
@@ -119,6 +122,8 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
 #pragma unroll 2
             for (int jj = 0; jj < kGroup; jj++) {
                 const Src<PREC, PEPS> s = q[jj];
+                // normal numbers, and with a massless source zeros
+                const int numbers = s.m == 0.0 ? 0x168 : 0x108;
 #pragma unroll
                 for (int t = 0; t < T; t++) {
                     const bool own = MODE == kSkip && jj == skip[t];  // d = 0 there
@@ -128,7 +133,8 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
                     const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
                     double ri;
                     double c = s.m * inv_cube_f64<PHI>(r2, ri, k);
-                    live = live && (own || factor_ok(c));
+                    if (MODE != kPlain)
+                        live = live && (own || __builtin_amdgcn_class(c, numbers));
                     if (own) c = ri = 0.0;
                     sx[t] = fma(c, dx, sx[t]);
                     sy[t] = fma(c, dy, sy[t]);
@@ -136,6 +142,9 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
                     if (PHI) sp[t] -= s.m * ri;
                 }
             }
+            if (MODE == kPlain)
+#pragma unroll
+                for (int t = 0; t < T; t++) live = live && isfinite(sx[t] + sy[t] + sz[t]);
             if (__ballot(!live) == 0) {
 #pragma unroll
                 for (int t = 0; t < T; t++) {
@@ -189,18 +198,17 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
 
 // The same, choosing the form: `own` (the same on every active lane) where a
 // target may be among the sources, `plain` (the same on every active lane) where
-// every pair of the group is softened as kPlain asks (FP32C), or its numbers are in
-// the ranges that factor_ok asks for (FP64).
+// every pair of the group is as kPlain asks.
 template <int PREC, bool PEPS, bool PHI, int T>
 __device__ __forceinline__ void add_group(const Src<PREC, PEPS> *q, int cnt, bool full,
                                           Target (&tg)[T], double eps0sq, float eps0f,
                                           const int (&skip)[T], bool own, bool plain)
 {
-    if (!full || (PREC == BH_FP64 && !plain))
+    if (!full)
         sum_group<PREC, PEPS, PHI, T, kSkip, false>(q, cnt, tg, eps0sq, eps0f, skip);
     else if (own)
         sum_group<PREC, PEPS, PHI, T, kSkip, true>(q, cnt, tg, eps0sq, eps0f, skip);
-    else if (PREC == BH_FP64 || plain)
+    else if (plain)
         sum_group<PREC, PEPS, PHI, T, kPlain, true>(q, cnt, tg, eps0sq, eps0f, skip);
     else
         sum_group<PREC, PEPS, PHI, T, kTest, true>(q, cnt, tg, eps0sq, eps0f, skip);
@@ -224,23 +232,24 @@ __device__ inline Target load_target(const double *__restrict__ pos,
     return g;
 }
 
-// A target all of whose groups may be plain, given plain sources. FP32C: its softening
-// makes every r^2 a positive normal FP32 number if the other half is a number (not NaN).
-// FP64: its numbers are in the ranges that factor_ok asks for.
+// Targets and sources whose groups may be plain. FP32C: the target's softening makes
+// every r^2 a positive normal FP32 number if the source's half is a number (not NaN).
+// FP64: lengths and masses keep every factor above 2^-910.
 template <int PREC, bool PEPS>
 __device__ inline bool plain_target(const Target &g, double eps0sq, float eps0f)
 {
     if (PREC == BH_FP64)
-        return fabs(g.x) + fabs(g.y) + fabs(g.z) <= 0.25 * kMildLength &&
-               (PEPS ? g.eh : eps0sq) <= 0.5 * kMildEps2;
+        return fabs(g.x) + fabs(g.y) + fabs(g.z) <= 0.5 * kMildLength &&
+               (PEPS ? g.eh : eps0sq) <= kMildEps2;
     return positive_normal_f(PEPS ? g.ehf : eps0f);
 }
 template <int PREC, bool PEPS>
 __device__ inline bool plain_source(const Src<PREC, PEPS> &s)
 {
     if constexpr (PREC == BH_FP64) {
-        bool ok = fabs(s.x) + fabs(s.y) + fabs(s.z) <= 0.25 * kMildLength && mild_mass(s.m);
-        if constexpr (PEPS) ok = ok && s.eh <= 0.5 * kMildEps2;
+        bool ok = fabs(s.x) + fabs(s.y) + fabs(s.z) <= 0.5 * kMildLength &&
+                  fabs(s.m) >= kMildMassMin;
+        if constexpr (PEPS) ok = ok && s.eh <= kMildEps2;
         return ok;
     } else {
         return !PEPS || s.eh >= 0.f;
