@@ -135,285 +135,285 @@ __global__ __launch_bounds__(64 * (1 + kEvals)) void k_vjp_walk(
         walkx::traverse<GB>(L, 0, active, ninfo, nmom, walkx::SideSq(box[0]), glo, ghi, me.x, me.y,
                             me.z, th2);
     } else {
-    EvalLds<GB> &sh = eval_lds[wave - 1];
-    ItemV *const items = sh.items;
-    uint16_t *const rec = sh.rec;
-    double *const tacc = sh.tacc;
-    double *const sacc = sh.sacc;
-    const double eb2 = PEPS ? beps2[valid ? s : g0] : 0.0;
-    const float ebhf = (float)(0.5 * eb2);  // FP32C: half the target's squared softening
-    const CubeConsts cc = cube_consts();
-    double lx = 0.0, ly = 0.0, lz = 0.0;
-    if (valid) {
-        const int64_t o = idx[s];
-        lx = lambda[3 * o];
-        ly = lambda[3 * o + 1];
-        lz = lambda[3 * o + 2];
-    }
-    // This lane's order of its share's eight items of a dense step: slot bits
-    // 2 and 1 follow lane bits 0 and 1, slot bit 0 lane bit 5 (GB = 64) or 3.
-    const int perm = ((lane & 1) << 2) | (lane & 2) | (GB == 64 ? lane >> 5 : (lane >> 3) & 1);
-
-    // every upstream value of the wave's bodies, and every offset, is finite; other
-    // waves have code of their own (a test a term made FP64 VJPs of 200,000 bodies 5 %
-    // longer)
-    const bool finite = __ballot(!(isfinite(lx) && isfinite(ly) && isfinite(lz))) == 0 &&
-                        box[0].L <= 0x1p1000;
-
-    double gx = 0.0, gy = 0.0, gz = 0.0;  // target-side gradient of this lane's body
-    const VT lxv = (VT)lx, lyv = (VT)ly, lzv = (VT)lz;
-    for (int i = lane; i < 3 * GB; i += 64) tacc[i] = 0.0;
-
-    // One softened term of source (x, y, z, m, e2) on a target at (bx, by, bz)
-    // with softening eb and upstream (ux, uy, uz): the target-side gradient is
-    // minus the first three source-side components. In FP32C the offset is the
-    // FP64 difference rounded once and the rest of the term is FP32; the term
-    // counts when its r^2 is a positive normal number of the precision used.
-    // In FP32C the pair softening is the sum of the two halves rounded to
-    // FP32 (ebh: the target's), as in the forward FP32C walk.
-    auto term = [&](auto all_finite, const ItemV &it, double bx, double by, double bz, double eb, float ebh, VT ux,
-                    VT uy, VT uz, bool on, VT out[5]) {
-        out[0] = out[1] = out[2] = out[3] = out[4] = VT(0);
-        if constexpr (F32) {
-            const float dx = (float)(it.x - bx), dy = (float)(it.y - by), dz = (float)(it.z - bz);
-            const float e2 = PEPS ? it.e2h + ebh : (float)eps0sq;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, e2)));
-            if (on && positive_normal_f(r2)) {
-                const float rinv = __builtin_amdgcn_rsqf(r2), inv2 = rinv * rinv;
-                const float inv3 = inv2 * rinv;
-                const float inv5 = inv3 * inv2;
-                const float ld = ux * dx + uy * dy + uz * dz;
-                const float gms = it.gm;
-                const float c = 3.0f * ld * inv5;
-                out[0] = gms * (ux * inv3 - dx * c);
-                out[1] = gms * (uy * inv3 - dy * c);
-                out[2] = gms * (uz * inv3 - dz * c);
-                out[3] = (float)G * ld * inv3;
-                out[4] = -1.5f * gms * ld * inv5;
-            }
-        } else {
-            const double dx = it.x - bx, dy = it.y - by, dz = it.z - bz;
-            const double e2 = PEPS ? 0.5 * (eb + it.e2) : eps0sq;
-            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
-            const bool live = on && positive_normal(r2);
-            const double ld = ux * dx + uy * dy + uz * dz;
-            double i2, ri;
-            double i3 = inv_cube_sq_f64(r2, i2, ri, cc);
-            i3 = live ? i3 : 0.0;
-            const double li = live ? ld * i2 : 0.0;
-            const double g3 = G * it.m * i3, k3 = 3.0 * li;
-            out[0] = g3 * fma(-k3, dx, ux);
-            out[1] = g3 * fma(-k3, dy, uy);
-            out[2] = g3 * fma(-k3, dz, uz);
-            out[3] = G * ld * i3;
-            out[4] = -1.5 * g3 * li;
-            // zero, where a factor of zero does not make it so
-            if (!decltype(all_finite)::value && !live)
-                out[0] = out[1] = out[2] = out[3] = out[4] = 0.0;
+        EvalLds<GB> &sh = eval_lds[wave - 1];
+        ItemV *const items = sh.items;
+        uint16_t *const rec = sh.rec;
+        double *const tacc = sh.tacc;
+        double *const sacc = sh.sacc;
+        const double eb2 = PEPS ? beps2[valid ? s : g0] : 0.0;
+        const float ebhf = (float)(0.5 * eb2);  // FP32C: half the target's squared softening
+        const CubeConsts cc = cube_consts();
+        double lx = 0.0, ly = 0.0, lz = 0.0;
+        if (valid) {
+            const int64_t o = idx[s];
+            lx = lambda[3 * o];
+            ly = lambda[3 * o + 1];
+            lz = lambda[3 * o + 2];
         }
-    };
-    // where component q (0..3) of an item's source-side sum is added, and its
-    // fifth, of a node (e2 = (eps_B^2 + <eps^2>_N) / 2)
-    auto adj = [&](int32_t src, int q) {
-        return src >= 0 ? badj + 4 * (int64_t)src + q : nadj + 4 * (int64_t)(~src) + q;
-    };
-    auto add_e2 = [&](int32_t src, double v) {
-        if (src < 0) unsafeAtomicAdd(nadj_e + ~src, 0.5 * v);
-    };
-    // After the exchanges of a dense step the lanes that agree in the bits of
-    // `perm` and `sub` hold the same item's sums. Lane t of the flush adds
-    // component t & 3 of the step's item t / 4 (16 items a flush for GB = 16 and
-    // 32, all 8 for GB = 64): it reads them from the lane that holds that item
-    // and has the component in the remaining lane bits.
-    constexpr int kFlushes = GB == 16 ? 2 : 1, kFlushItems = GB == 64 ? 8 : 16;
-    const int fq = lane & 3, fi = lane >> 2;
-    int from = ((fi >> 2) & 1) | (fi & 2);  // the lane bits of the item's place in its share
-    from |= GB == 64 ? (fi & 1) << 5 : (fi & 1) << 3;
-    if (GB == 64) from |= fq << 2;                                    // component: bits 2, 3
-    if (GB == 32) from |= (fq & 1) << 2 | (fq >> 1) << 4 | (fi >> 3) << 5;  // bits 2, 4
-    if (GB == 16) from |= (fq & 1) << 2 | (fi >> 3) << 4;             // bit 2 (and two values)
+        // This lane's order of its share's eight items of a dense step: slot bits
+        // 2 and 1 follow lane bits 0 and 1, slot bit 0 lane bit 5 (GB = 64) or 3.
+        const int perm = ((lane & 1) << 2) | (lane & 2) | (GB == 64 ? lane >> 5 : (lane >> 3) & 1);
 
-    auto evaluate = [&](auto all_finite, walkx::Batch &bt) {
-        const int c = bt.count;
-        uint64_t mk;
-        int32_t src;
-        walkx::take_batch(L, wave - 1, bt, src, mk);
-        ItemV ld_it{0.0, 0.0, 0.0, 0.0, 0.0, 0ull, 0, 0.f, 0.f, 0};
-        if (lane < c) {
-            if (src >= 0) {
-                if (!check_ok(src < n, CK_INDEX)) src = 0;
-                const int64_t rel = (int64_t)src - g0;
-                if (rel >= 0 && rel < GB) mk &= ~(1ull << rel);
-                const Body b = body[src];
-                const double e2 = PEPS ? beps2[src] : 0.0;
-                ld_it = ItemV{b.x,  b.y, b.z, b.m, e2, mk, src, (float)(G * b.m),
-                              (float)(0.5 * e2), 0};
-            } else {
-                const NodeMom nm = nmom[~src];
-                const double e2 = PEPS ? neps2[~src] : 0.0;
-                ld_it = ItemV{nm.x, nm.y, nm.z, nm.m, e2, mk, src, (float)(G * nm.m),
-                              (float)(0.5 * e2), 0};
-            }
-        }
-        const int pk = __popcll(mk);
-        const bool sparse = lane < c && pk <= kSparse;
-        const uint32_t pv = sparse ? (uint32_t)pk : 0u;
-        const uint32_t pend = wave_incl_scan(pv);
-        const bool fits = sparse && pend <= (uint32_t)kPairCap;
-        const bool dense = lane < c && !fits;
-        const uint64_t db = __ballot(dense);
-        const uint64_t fb = __ballot(fits && pk > 0);
-        const int nd = __popcll(db);
-        const int ns = __popcll(fb);
-        const int np = fb ? __builtin_amdgcn_readlane((int)pend, 63 - __builtin_clzll(fb)) : 0;
-        BHX_CHECK(np <= kPairCap, CK_PAIRS);
-        if (dense || (fits && pk > 0)) {
-            const int slot = dense ? (int)lanes_below(db) : nd + (int)lanes_below(fb);
-            items[slot] = ld_it;
-            if (fits) {
-#pragma unroll
-                for (int q = 0; q < 5; q++) sacc[5 * slot + q] = 0.0;
-                uint64_t bits = mk;
-                uint32_t at = pend - pv;
-                while (bits) {
-                    rec[at++] = (uint16_t)(slot << 6 | __builtin_ctzll(bits));
-                    bits &= bits - 1;
-                }
-            }
-        }
-        walkx::wave_sync();
+        // every upstream value of the wave's bodies, and every offset, is finite; other
+        // waves have code of their own (a test a term made FP64 VJPs of 200,000 bodies 5 %
+        // longer)
+        const bool finite = __ballot(!(isfinite(lx) && isfinite(ly) && isfinite(lz))) == 0 &&
+                            box[0].L <= 0x1p1000;
 
-        // dense items, eight per share of lanes per step
-#pragma unroll 1
-        for (int j0 = 0; j0 < nd; j0 += 8 * LPB) {
-            VT v[8][NC];
-            VT sx = VT(0), sy = VT(0), sz = VT(0);  // FP32C: this step's target-side terms
-#pragma unroll
-            for (int t = 0; t < 8; t++) {
-                const int j = j0 + 8 * sub + (t ^ perm);
-                const ItemV it = items[j < nd ? j : j0];
-                const bool on = j < nd && ((it.mask >> bq) & 1ull);
-                VT o[5];
-                term(all_finite, it, me.x, me.y, me.z, eb2, ebhf, lxv, lyv, lzv, on, o);
-                if constexpr (F32) {
-                    sx -= o[0];
-                    sy -= o[1];
-                    sz -= o[2];
-                } else {
-                    gx -= o[0];
-                    gy -= o[1];
-                    gz -= o[2];
-                }
-#pragma unroll
-                for (int q = 0; q < NC; q++) v[t][q] = o[q];
-            }
+        double gx = 0.0, gy = 0.0, gz = 0.0;  // target-side gradient of this lane's body
+        const VT lxv = (VT)lx, lyv = (VT)ly, lzv = (VT)lz;
+        for (int i = lane; i < 3 * GB; i += 64) tacc[i] = 0.0;
+
+        // One softened term of source (x, y, z, m, e2) on a target at (bx, by, bz)
+        // with softening eb and upstream (ux, uy, uz): the target-side gradient is
+        // minus the first three source-side components. In FP32C the offset is the
+        // FP64 difference rounded once and the rest of the term is FP32; the term
+        // counts when its r^2 is a positive normal number of the precision used.
+        // In FP32C the pair softening is the sum of the two halves rounded to
+        // FP32 (ebh: the target's), as in the forward FP32C walk.
+        auto term = [&](auto all_finite, const ItemV &it, double bx, double by, double bz, double eb, float ebh, VT ux,
+                        VT uy, VT uz, bool on, VT out[5]) {
+            out[0] = out[1] = out[2] = out[3] = out[4] = VT(0);
             if constexpr (F32) {
-                gx += (double)sx;
-                gy += (double)sy;
-                gz += (double)sz;
-            }
-#pragma unroll
-            for (int t = 0; t < 4; t++)
-#pragma unroll
-                for (int q = 0; q < NC; q++) v[t][q] += dpp<kDppXor1>(v[t + 4][q]);
-#pragma unroll
-            for (int t = 0; t < 2; t++)
-#pragma unroll
-                for (int q = 0; q < NC; q++) v[t][q] += dpp<kDppXor2>(v[t + 2][q]);
-#pragma unroll
-            for (int q = 0; q < NC; q++) {
-                VT w;
-                if constexpr (GB == 64) {
-                    w = v[0][q] + __shfl_xor(v[1][q], 32);
-                    w += dpp<kDppRor4>(w);
-                    w += dpp<kDppRor8>(w);
-                    w += __shfl_xor(w, 16);
-                } else {
-                    w = v[0][q] + dpp<kDppRor8>(v[1][q]);  // lane ^ 8 inside the row
-                    w += __shfl_xor(w, 4);
-                    if (GB == 32) w += __shfl_xor(w, 16);
-                }
-                v[0][q] = w;
-            }
-            if constexpr (GB == 16) {
-                // two of the four components per source lane, picked by the reader
-                const VT va = (lane & 4) ? v[0][1] : v[0][0], vb = (lane & 4) ? v[0][3] : v[0][2];
-#pragma unroll
-                for (int f = 0; f < kFlushes; f++) {
-                    const VT wa = __shfl(va, from | f << 5), wb = __shfl(vb, from | f << 5);
-                    const int j = j0 + kFlushItems * f + fi;
-                    if (j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)(fq >> 1 ? wb : wa));
+                const float dx = (float)(it.x - bx), dy = (float)(it.y - by), dz = (float)(it.z - bz);
+                const float e2 = PEPS ? it.e2h + ebh : (float)eps0sq;
+                const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, e2)));
+                if (on && positive_normal_f(r2)) {
+                    const float rinv = __builtin_amdgcn_rsqf(r2), inv2 = rinv * rinv;
+                    const float inv3 = inv2 * rinv;
+                    const float inv5 = inv3 * inv2;
+                    const float ld = ux * dx + uy * dy + uz * dz;
+                    const float gms = it.gm;
+                    const float c = 3.0f * ld * inv5;
+                    out[0] = gms * (ux * inv3 - dx * c);
+                    out[1] = gms * (uy * inv3 - dy * c);
+                    out[2] = gms * (uz * inv3 - dz * c);
+                    out[3] = (float)G * ld * inv3;
+                    out[4] = -1.5f * gms * ld * inv5;
                 }
             } else {
-                const int c = GB == 64 ? (lane >> 2) & 3 : ((lane >> 2) & 1) | ((lane >> 4) & 1) << 1;
-                const VT lo = c & 1 ? v[0][1] : v[0][0], hi = c & 1 ? v[0][3] : v[0][2];
-                const VT w = __shfl(c >> 1 ? hi : lo, from);
-                const int j = j0 + fi;
-                if (fi < kFlushItems && j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)w);
+                const double dx = it.x - bx, dy = it.y - by, dz = it.z - bz;
+                const double e2 = PEPS ? 0.5 * (eb + it.e2) : eps0sq;
+                const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
+                const bool live = on && positive_normal(r2);
+                const double ld = ux * dx + uy * dy + uz * dz;
+                double i2, ri;
+                double i3 = inv_cube_sq_f64(r2, i2, ri, cc);
+                i3 = live ? i3 : 0.0;
+                const double li = live ? ld * i2 : 0.0;
+                const double g3 = G * it.m * i3, k3 = 3.0 * li;
+                out[0] = g3 * fma(-k3, dx, ux);
+                out[1] = g3 * fma(-k3, dy, uy);
+                out[2] = g3 * fma(-k3, dz, uz);
+                out[3] = G * ld * i3;
+                out[4] = -1.5 * g3 * li;
+                // zero, where a factor of zero does not make it so
+                if (!decltype(all_finite)::value && !live)
+                    out[0] = out[1] = out[2] = out[3] = out[4] = 0.0;
             }
-            if constexpr (PEPS) {
-                // each share's sums of items j0 + 8 sub + perm sit in its lanes with
-                // lane bits 2 and 3, 4 (GB = 64) or 2 (and 4 for GB = 32) clear
-                const int j = j0 + 8 * sub + perm;
-                const bool lead =
-                    GB == 64 ? (lane & 28) == 0 : GB == 32 ? (lane & 20) == 0 : (lane & 4) == 0;
-                if (lead && j < nd) add_e2(items[j].src, (double)v[0][4]);
-            }
-        }
+        };
+        // where component q (0..3) of an item's source-side sum is added, and its
+        // fifth, of a node (e2 = (eps_B^2 + <eps^2>_N) / 2)
+        auto adj = [&](int32_t src, int q) {
+            return src >= 0 ? badj + 4 * (int64_t)src + q : nadj + 4 * (int64_t)(~src) + q;
+        };
+        auto add_e2 = [&](int32_t src, double v) {
+            if (src < 0) unsafeAtomicAdd(nadj_e + ~src, 0.5 * v);
+        };
+        // After the exchanges of a dense step the lanes that agree in the bits of
+        // `perm` and `sub` hold the same item's sums. Lane t of the flush adds
+        // component t & 3 of the step's item t / 4 (16 items a flush for GB = 16 and
+        // 32, all 8 for GB = 64): it reads them from the lane that holds that item
+        // and has the component in the remaining lane bits.
+        constexpr int kFlushes = GB == 16 ? 2 : 1, kFlushItems = GB == 64 ? 8 : 16;
+        const int fq = lane & 3, fi = lane >> 2;
+        int from = ((fi >> 2) & 1) | (fi & 2);  // the lane bits of the item's place in its share
+        from |= GB == 64 ? (fi & 1) << 5 : (fi & 1) << 3;
+        if (GB == 64) from |= fq << 2;                                    // component: bits 2, 3
+        if (GB == 32) from |= (fq & 1) << 2 | (fq >> 1) << 4 | (fi >> 3) << 5;  // bits 2, 4
+        if (GB == 16) from |= (fq & 1) << 2 | (fi >> 3) << 4;             // bit 2 (and two values)
 
-        // sparse items as pairs
+        auto evaluate = [&](auto all_finite, walkx::Batch &bt) {
+            const int c = bt.count;
+            uint64_t mk;
+            int32_t src;
+            walkx::take_batch(L, wave - 1, bt, src, mk);
+            ItemV ld_it{0.0, 0.0, 0.0, 0.0, 0.0, 0ull, 0, 0.f, 0.f, 0};
+            if (lane < c) {
+                if (src >= 0) {
+                    if (!check_ok(src < n, CK_INDEX)) src = 0;
+                    const int64_t rel = (int64_t)src - g0;
+                    if (rel >= 0 && rel < GB) mk &= ~(1ull << rel);
+                    const Body b = body[src];
+                    const double e2 = PEPS ? beps2[src] : 0.0;
+                    ld_it = ItemV{b.x,  b.y, b.z, b.m, e2, mk, src, (float)(G * b.m),
+                                  (float)(0.5 * e2), 0};
+                } else {
+                    const NodeMom nm = nmom[~src];
+                    const double e2 = PEPS ? neps2[~src] : 0.0;
+                    ld_it = ItemV{nm.x, nm.y, nm.z, nm.m, e2, mk, src, (float)(G * nm.m),
+                                  (float)(0.5 * e2), 0};
+                }
+            }
+            const int pk = __popcll(mk);
+            const bool sparse = lane < c && pk <= kSparse;
+            const uint32_t pv = sparse ? (uint32_t)pk : 0u;
+            const uint32_t pend = wave_incl_scan(pv);
+            const bool fits = sparse && pend <= (uint32_t)kPairCap;
+            const bool dense = lane < c && !fits;
+            const uint64_t db = __ballot(dense);
+            const uint64_t fb = __ballot(fits && pk > 0);
+            const int nd = __popcll(db);
+            const int ns = __popcll(fb);
+            const int np = fb ? __builtin_amdgcn_readlane((int)pend, 63 - __builtin_clzll(fb)) : 0;
+            BHX_CHECK(np <= kPairCap, CK_PAIRS);
+            if (dense || (fits && pk > 0)) {
+                const int slot = dense ? (int)lanes_below(db) : nd + (int)lanes_below(fb);
+                items[slot] = ld_it;
+                if (fits) {
+#pragma unroll
+                    for (int q = 0; q < 5; q++) sacc[5 * slot + q] = 0.0;
+                    uint64_t bits = mk;
+                    uint32_t at = pend - pv;
+                    while (bits) {
+                        rec[at++] = (uint16_t)(slot << 6 | __builtin_ctzll(bits));
+                        bits &= bits - 1;
+                    }
+                }
+            }
+            walkx::wave_sync();
+
+            // dense items, eight per share of lanes per step
 #pragma unroll 1
-        for (int i0 = 0; i0 < np; i0 += 64) {
-            const int i = i0 + lane;
-            const bool on = i < np;
-            const uint32_t r = rec[on ? i : i0];
-            const int k = (int)(r >> 6), b = (int)(r & 63u);
-            const double bx = __shfl(me.x, b), by = __shfl(me.y, b), bz = __shfl(me.z, b);
-            const double eb = PEPS && !F32 ? __shfl(eb2, b) : 0.0;
-            const float ebh = PEPS && F32 ? __shfl(ebhf, b) : 0.f;
-            const VT ux = __shfl(lxv, b), uy = __shfl(lyv, b), uz = __shfl(lzv, b);
-            const ItemV it = items[k];
-            VT o[5];
-            term(all_finite, it, bx, by, bz, eb, ebh, ux, uy, uz, on, o);
-            if (on) {
+            for (int j0 = 0; j0 < nd; j0 += 8 * LPB) {
+                VT v[8][NC];
+                VT sx = VT(0), sy = VT(0), sz = VT(0);  // FP32C: this step's target-side terms
 #pragma unroll
-                for (int q = 0; q < 3; q++)
-                    __hip_atomic_fetch_add(&tacc[3 * b + q], -(double)o[q], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                for (int t = 0; t < 8; t++) {
+                    const int j = j0 + 8 * sub + (t ^ perm);
+                    const ItemV it = items[j < nd ? j : j0];
+                    const bool on = j < nd && ((it.mask >> bq) & 1ull);
+                    VT o[5];
+                    term(all_finite, it, me.x, me.y, me.z, eb2, ebhf, lxv, lyv, lzv, on, o);
+                    if constexpr (F32) {
+                        sx -= o[0];
+                        sy -= o[1];
+                        sz -= o[2];
+                    } else {
+                        gx -= o[0];
+                        gy -= o[1];
+                        gz -= o[2];
+                    }
 #pragma unroll
-                for (int q = 0; q < NC; q++)
-                    __hip_atomic_fetch_add(&sacc[5 * k + q], (double)o[q], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    for (int q = 0; q < NC; q++) v[t][q] = o[q];
+                }
+                if constexpr (F32) {
+                    gx += (double)sx;
+                    gy += (double)sy;
+                    gz += (double)sz;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; t++)
+#pragma unroll
+                    for (int q = 0; q < NC; q++) v[t][q] += dpp<kDppXor1>(v[t + 4][q]);
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int q = 0; q < NC; q++) v[t][q] += dpp<kDppXor2>(v[t + 2][q]);
+#pragma unroll
+                for (int q = 0; q < NC; q++) {
+                    VT w;
+                    if constexpr (GB == 64) {
+                        w = v[0][q] + __shfl_xor(v[1][q], 32);
+                        w += dpp<kDppRor4>(w);
+                        w += dpp<kDppRor8>(w);
+                        w += __shfl_xor(w, 16);
+                    } else {
+                        w = v[0][q] + dpp<kDppRor8>(v[1][q]);  // lane ^ 8 inside the row
+                        w += __shfl_xor(w, 4);
+                        if (GB == 32) w += __shfl_xor(w, 16);
+                    }
+                    v[0][q] = w;
+                }
+                if constexpr (GB == 16) {
+                    // two of the four components per source lane, picked by the reader
+                    const VT va = (lane & 4) ? v[0][1] : v[0][0], vb = (lane & 4) ? v[0][3] : v[0][2];
+#pragma unroll
+                    for (int f = 0; f < kFlushes; f++) {
+                        const VT wa = __shfl(va, from | f << 5), wb = __shfl(vb, from | f << 5);
+                        const int j = j0 + kFlushItems * f + fi;
+                        if (j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)(fq >> 1 ? wb : wa));
+                    }
+                } else {
+                    const int c = GB == 64 ? (lane >> 2) & 3 : ((lane >> 2) & 1) | ((lane >> 4) & 1) << 1;
+                    const VT lo = c & 1 ? v[0][1] : v[0][0], hi = c & 1 ? v[0][3] : v[0][2];
+                    const VT w = __shfl(c >> 1 ? hi : lo, from);
+                    const int j = j0 + fi;
+                    if (fi < kFlushItems && j < nd) unsafeAtomicAdd(adj(items[j].src, fq), (double)w);
+                }
+                if constexpr (PEPS) {
+                    // each share's sums of items j0 + 8 sub + perm sit in its lanes with
+                    // lane bits 2 and 3, 4 (GB = 64) or 2 (and 4 for GB = 32) clear
+                    const int j = j0 + 8 * sub + perm;
+                    const bool lead =
+                        GB == 64 ? (lane & 28) == 0 : GB == 32 ? (lane & 20) == 0 : (lane & 4) == 0;
+                    if (lead && j < nd) add_e2(items[j].src, (double)v[0][4]);
+                }
             }
-        }
-        walkx::wave_sync();
-        for (int i = lane; i < 4 * ns; i += 64) {
-            const int k = nd + (i >> 2);
-            unsafeAtomicAdd(adj(items[k].src, i & 3), sacc[5 * k + (i & 3)]);
-        }
-        if (PEPS && lane < ns) add_e2(items[nd + lane].src, sacc[5 * (nd + lane) + 4]);
-        walkx::wave_sync();
-    };
 
-    walkx::Batch bt;
-    bt.start = (uint32_t)(kBatch * (wave - 1));
-    if (F32 || finite)
-        while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::true_type{}, bt);
-    else if constexpr (!F32)
-        while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::false_type{}, bt);
-
-    // the lanes' shares of each body, in a fixed order, then its pair sums
+            // sparse items as pairs
+#pragma unroll 1
+            for (int i0 = 0; i0 < np; i0 += 64) {
+                const int i = i0 + lane;
+                const bool on = i < np;
+                const uint32_t r = rec[on ? i : i0];
+                const int k = (int)(r >> 6), b = (int)(r & 63u);
+                const double bx = __shfl(me.x, b), by = __shfl(me.y, b), bz = __shfl(me.z, b);
+                const double eb = PEPS && !F32 ? __shfl(eb2, b) : 0.0;
+                const float ebh = PEPS && F32 ? __shfl(ebhf, b) : 0.f;
+                const VT ux = __shfl(lxv, b), uy = __shfl(lyv, b), uz = __shfl(lzv, b);
+                const ItemV it = items[k];
+                VT o[5];
+                term(all_finite, it, bx, by, bz, eb, ebh, ux, uy, uz, on, o);
+                if (on) {
 #pragma unroll
-    for (int o = GB; o < 64; o <<= 1) {
-        gx += __shfl_xor(gx, o);
-        gy += __shfl_xor(gy, o);
-        gz += __shfl_xor(gz, o);
-    }
-    if (sub == 0) {
-        tacc[3 * bq] += gx;
-        tacc[3 * bq + 1] += gy;
-        tacc[3 * bq + 2] += gz;
-    }
+                    for (int q = 0; q < 3; q++)
+                        __hip_atomic_fetch_add(&tacc[3 * b + q], -(double)o[q], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                    for (int q = 0; q < NC; q++)
+                        __hip_atomic_fetch_add(&sacc[5 * k + q], (double)o[q], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            walkx::wave_sync();
+            for (int i = lane; i < 4 * ns; i += 64) {
+                const int k = nd + (i >> 2);
+                unsafeAtomicAdd(adj(items[k].src, i & 3), sacc[5 * k + (i & 3)]);
+            }
+            if (PEPS && lane < ns) add_e2(items[nd + lane].src, sacc[5 * (nd + lane) + 4]);
+            walkx::wave_sync();
+        };
+
+        walkx::Batch bt;
+        bt.start = (uint32_t)(kBatch * (wave - 1));
+        if (F32 || finite)
+            while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::true_type{}, bt);
+        else if constexpr (!F32)
+            while (walkx::next_batch(L, wave - 1, bt)) evaluate(std::false_type{}, bt);
+
+        // the lanes' shares of each body, in a fixed order, then its pair sums
+#pragma unroll
+        for (int o = GB; o < 64; o <<= 1) {
+            gx += __shfl_xor(gx, o);
+            gy += __shfl_xor(gy, o);
+            gz += __shfl_xor(gz, o);
+        }
+        if (sub == 0) {
+            tacc[3 * bq] += gx;
+            tacc[3 * bq + 1] += gy;
+            tacc[3 * bq + 2] += gz;
+        }
     }
     __syncthreads();
     // the waves' sums in wave order
