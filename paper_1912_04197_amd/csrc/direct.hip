@@ -234,7 +234,7 @@ __device__ inline Target load_target(const double *__restrict__ pos,
 
 // Targets and sources whose groups may be plain. FP32C: the target's softening makes
 // every r^2 a positive normal FP32 number if the source's half is a number (not NaN).
-// FP64: lengths and masses keep every factor above 2^-910.
+// FP64: lengths and masses keep every factor but that of a massless source above 2^-910.
 template <int PREC, bool PEPS>
 __device__ inline bool plain_target(const Target &g, double eps0sq, float eps0f)
 {
@@ -248,7 +248,7 @@ __device__ inline bool plain_source(const Src<PREC, PEPS> &s)
 {
     if constexpr (PREC == BH_FP64) {
         bool ok = fabs(s.x) + fabs(s.y) + fabs(s.z) <= 0.5 * kMildLength &&
-                  fabs(s.m) >= kMildMassMin;
+                  (s.m == 0.0 || fabs(s.m) >= kMildMassMin);
         if constexpr (PEPS) ok = ok && s.eh <= kMildEps2;
         return ok;
     } else {
