@@ -381,7 +381,7 @@ struct WalkParams {
     int32_t *counts;  // caller order n x 2 or nullptr
     bool per_body_eps;
     int precision;
-    int group;  // target bodies per wavefront: 64, 32 or 16
+    int group;  // target bodies per block: 64, 32 or 16
     const double *nquad = nullptr;  // node quadrupoles: add their terms (or nullptr)
     // velocities (in the order of acc) that the walk kicks by kick_h times the
     // acceleration it writes, as launch_kick does (or nullptr)

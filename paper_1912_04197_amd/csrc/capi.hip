@@ -221,17 +221,24 @@ bh_status record(bh_ctx *c, int which)
     return BH_OK;
 }
 
-// Bodies per walk wavefront for a call on n bodies: the configured size, or
-// by default 64 for large calls and 16 below 2^17 bodies, where 64-body groups
-// leave too few wavefronts to fill the chip.
+// Bodies per walk block for a call on n bodies: the configured size, or by default
+// 64 for large calls and 16 below 2^17 bodies, where 64-body groups leave too few
+// blocks to fill the chip. The line was measured when a group was one wave; with
+// blocks of four waves the groups of 16, 32 and 64 take (us, ball, leaf 8, FP32C) 32,
+// 45, 67 at 4096 bodies, 182, 179, 183 at 65,536, 355, 331, 328 at 131,071, 577, 507,
+// 470 at 262,144; in FP64 229, 230, 224 and 436, 428, 428 at the middle two. An FP32C
+// sum's grouping follows the group, so the line also fixes the last bits of results.
 int walk_group(const bh_ctx *c, int64_t n)
 {
     if (c->cfg.walk_group) return c->cfg.walk_group;
     return n < bhx::kSmallWalk ? 16 : bhx::kDefaultWalkGroup;
 }
 
-// The same for the adjoint walk, whose per-item work is heavier: measured
-// best at 16 below 2^15 bodies, 32 up to 2^19, 64 above.
+// The same for the adjoint walk, whose per-item work is heavier: 16 below 2^15
+// bodies, 32 up to 2^19, 64 above, measured when a group was one wave. With blocks of
+// four a VJP takes with groups of 16, 32 and 64 (us, ball, leaf 4, FP32C) 244, 259, 333 at
+// 16,384 bodies, 340, 327, 398 at 32,768, 537, 498, 560 at 65,536 and 3239, 2789, 3021
+// at 524,288, where 32 would now be the better one.
 int vjp_group(const bh_ctx *c, int64_t n)
 {
     if (c->cfg.walk_group) return c->cfg.walk_group;

@@ -91,12 +91,12 @@ enum { kPlain = 0, kTest = 1, kSkip = 2 };
 //
 // Bound by VALU issue (a wave64 FP32 or FP64 operation takes about four cycles
 // of its SIMD). An FP32C pair takes 16 instructions softened and 18 unsoftened,
-// where testing every pair's index and r^2 took 19; an FP64 pair 18, where two
-// Newton steps, the cube and m d r^-3 per axis took 27. Two targets per lane
-// halve the LDS reads (two ds_read_b128 per source), which kept the LDS pipe
-// 62 % busy with one. 65536 bodies, one sum, before and after: FP32C 2.19 ->
+// where testing every pair's index and r^2 took 19; an FP64 pair 17 (18 with a test
+// of every pair), where two Newton steps, the cube and m d r^-3 per axis took 27. Two
+// targets per lane halve the LDS reads (two ds_read_b128 per source), which kept the
+// LDS pipe 62 % busy with one. 65536 bodies, one sum, before and after: FP32C 2.19 ->
 // 1.77 ms (per-body softening), 2.14 -> 1.68 ms (one softening), FP64 4.43 ->
-// 2.75 ms.
+// 2.59 ms (2.73 with the test).
 template <int PREC, bool PEPS, bool PHI, int T, int MODE, bool FULL>
 __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Target (&tg)[T],
                                           double eps0sq, float eps0f, const int (&skip)[T])
@@ -122,7 +122,7 @@ __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Tar
 #pragma unroll 2
             for (int jj = 0; jj < kGroup; jj++) {
                 const Src<PREC, PEPS> s = q[jj];
-                // normal numbers, and with a massless source zeros
+                // classes of a good factor: normal numbers, and with a massless source zeros
                 const int numbers = s.m == 0.0 ? 0x168 : 0x108;
 #pragma unroll
                 for (int t = 0; t < T; t++) {
@@ -447,7 +447,7 @@ hipError_t launch_t(hipStream_t s, const double *pos, const double *mass, const 
         // one sum of 2048 bodies 41 -> 12 us in FP64 (64 blocks of 256 targets
         // and the row sums' launch before), 21 -> 11 us in FP32C; 4096 bodies
         // 43 -> 21 and 23 -> 16 us. Above, k_direct's rows fill the GPU and its
-        // two targets per lane win (6000 bodies in FP64: 37 us against 50 here
+        // two targets per lane win (6000 bodies in FP64: 36 us against 50 here
         // with 32 targets per block)
         if (n <= 2048)
             k_direct_small<PREC, PEPS, PHI, 8><<<(unsigned)((n + 7) / 8), kSmallThreads, 0, s>>>(
@@ -458,8 +458,9 @@ hipError_t launch_t(hipStream_t s, const double *pos, const double *mass, const 
                                                                      eps0sq, G, acc, phi);
         return hipGetLastError();
     }
-    // rows of source ranges (whole tiles): as many as the partial buffer
-    // holds, which makes 2048 blocks (eight a CU) for any smaller n
+    // rows of source ranges (whole tiles): as many as the partial buffer holds and at
+    // least a tile each, which makes at most about 2048 blocks (eight a CU): 561 at 4097
+    // bodies, 2048 at 8192, 1564 at 100,000 (two whole rows), 1025 (one) above 131,072
     const int64_t tb = (n + kBlockTargets - 1) / kBlockTargets;
     const int64_t all = (n + kTile - 1) / kTile;
     int64_t rows = part ? kDirectPart / (4 * n) : 1;

@@ -417,7 +417,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const uint64_t *__re
     counts[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of one digit's row of tile counts; one block per digit.
 // k_box_final and k_keys for one scene, with the tile layout of k_sort_hist,
 // and that kernel's digit counts of the first pass (bits shift..shift+7) of
 // the same tile.
@@ -461,6 +460,7 @@ __global__ __launch_bounds__(kSortThreads) void k_keys_hist(const double *__rest
     counts[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
 }
 
+// Exclusive scan of one digit's row of tile counts; one block per digit.
 __global__ __launch_bounds__(256) void k_sort_scan(uint32_t *__restrict__ counts,
                                                    uint32_t *__restrict__ totals, int nblk)
 {
@@ -1552,7 +1552,7 @@ __device__ inline void raise_max(int32_t *p, int32_t v)
 // take one launch whatever their depth instead of two each. Bound by latency (a
 // block's dependent loads, two barriers a step and the atomic on the node count
 // that all blocks share): at 2^20 bodies and leaf 4 it takes 66 us where the
-// launches of those levels and their moments took 130, at 50,000 (leaf 8) 11
+// launches of those levels and their moments took 130, at 50,000 (leaf 8) 10
 // instead of 24; steps of 40,000 to 2^20 bodies are 1 to 5 % shorter. 256 threads
 // a block are 1 % slower at 2^20 (more atomics), 1024 the same. The
 // launches above stop at the first level whose nodes held at most kSubBodies

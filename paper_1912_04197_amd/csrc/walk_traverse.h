@@ -14,7 +14,7 @@
 // with 16-body groups 38 %, the traversal's rounds and the batches taking turns.
 // Walk, one wave -> 1 + 3 waves: 2^20 bodies (leaf 4, FP32C) 2.37 -> 1.80 ms,
 // 131072 (Plummer, leaf 16) 1.20 -> 0.75 ms, 50,000 (FP64, leaf 8) 308 -> 163 us,
-// 1000 (leaf 16) 51 -> 20 us. Two evaluating waves: 4 % slower at 2^20, 15 %
+// 1000 (leaf 16) 51 -> 16 us. Two evaluating waves: 4 % slower at 2^20, 15 %
 // at 131072 and 8 % at 50,000; four: 25 % slower at 2^20 (fewer blocks fit a
 // CU's LDS), 5 % faster at 1000.
 #pragma once
