@@ -95,8 +95,8 @@ enum { kPlain = 0, kTest = 1, kSkip = 2 };
 // of every pair), where two Newton steps, the cube and m d r^-3 per axis took 27. Two
 // targets per lane halve the LDS reads (two ds_read_b128 per source), which kept the
 // LDS pipe 62 % busy with one. 65536 bodies, one sum, before and after: FP32C 2.19 ->
-// 1.77 ms (per-body softening), 2.14 -> 1.68 ms (one softening), FP64 4.43 ->
-// 2.59 ms (2.73 with the test).
+// 1.76 ms (per-body softening), 2.14 -> 1.65 ms (one softening), FP64 4.43 ->
+// 2.61 ms (2.73 with the test).
 template <int PREC, bool PEPS, bool PHI, int T, int MODE, bool FULL>
 __device__ __forceinline__ void sum_group(const Src<PREC, PEPS> *q, int cnt, Target (&tg)[T],
                                           double eps0sq, float eps0f, const int (&skip)[T])
@@ -267,6 +267,7 @@ __global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
 {
     using S = Src<PREC, PEPS>;
     __shared__ S src[kTile];
+    __shared__ bool group_ok[kTile / kGroup];  // the group's sources are plain
     __shared__ double red[3][4][kBlockTargets];  // the other waves' sums
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t b0 = (int64_t)blockIdx.x * kBlockTargets;
@@ -287,13 +288,14 @@ __global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
     const int64_t s_hi = s_lo + chunk < n ? s_lo + chunk : n;
     for (int64_t base = s_lo; base < s_hi; base += kTile) {
         const int64_t j = base + tid;
-        bool ok = true;  // the tile's sources are plain
         if (j < s_hi) {
             const S s = load_source<PREC, PEPS>(pos, mass, eps, j);
             src[tid] = s;
-            ok = plain_source<PREC, PEPS>(s);
+            // half a wave loads a group
+            const uint64_t odd = __ballot(!plain_source<PREC, PEPS>(s));
+            if (tid % kGroup == 0) group_ok[tid / kGroup] = (uint32_t)(odd >> (lane & 32)) == 0;
         }
-        const bool tile_ok = __syncthreads_and(ok);
+        __syncthreads();
         const int cnt = (int)((s_hi - base) < kTile ? (s_hi - base) : kTile);
         const bool own = base < b0 + kBlockTargets && base + cnt > b0;
 #pragma unroll 1
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(256) void k_direct(const double *__restrict__ pos,
                 skip[t] = own && at >= 0 && at < gc ? (int)at : -1;
             }
             add_group<PREC, PEPS, PHI, kTargets>(src + g * kGroup, gc, gc == kGroup, tg, eps0sq,
-                                                 eps0f, skip, own, plain && tile_ok);
+                                                 eps0f, skip, own, plain && group_ok[g]);
         }
         __syncthreads();
     }
@@ -387,6 +389,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_direct_small(
     static_assert((kGroup * sizeof(S)) % 256 == 0, "group stride");
     __shared__ alignas(16) char tile[kShares * kStride];
     __shared__ double red[W][4][TG];
+    __shared__ bool group_ok[kShares];  // the group's sources are plain
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tl = lane % TG, share = wave * kWaveShares + lane / TG;
     const int b0 = (int)blockIdx.x * TG, i = b0 + tl;
@@ -394,14 +397,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_direct_small(
     Target tg[1] = {load_target<PEPS>(pos, eps, i < n ? i : n - 1)};
     const bool plain = __ballot(!plain_target<PREC, PEPS>(tg[0], eps0sq, eps0f)) == 0;
     for (int base = 0; base < n; base += kShares * kGroup) {
-        bool ok = true;
         const int in = n - base < kShares * kGroup ? n - base : kShares * kGroup;
         for (int k = tid; k < in; k += kSmallThreads) {
             const S s = load_source<PREC, PEPS>(pos, mass, eps, base + k);
             *(S *)(tile + (k / kGroup) * kStride + (k % kGroup) * (int)sizeof(S)) = s;
-            ok = ok && plain_source<PREC, PEPS>(s);
+            // half a wave loads a group
+            const uint64_t odd = __ballot(!plain_source<PREC, PEPS>(s));
+            if (k % kGroup == 0) group_ok[k / kGroup] = (uint32_t)(odd >> (lane & 32)) == 0;
         }
-        const bool tile_ok = __syncthreads_and(ok);
+        __syncthreads();
         const int left = in - share * kGroup;
         const int cnt = left < 0 ? 0 : left < kGroup ? left : kGroup;
         const int at = i - base - share * kGroup;
@@ -411,6 +415,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_direct_small(
         const int g0 = base + share * kGroup;
         const bool own = __ballot(g0 < b0 + TG && g0 + cnt > b0) != 0;
         const bool full = __ballot(cnt != kGroup) == 0;
+        const bool tile_ok = __ballot(cnt > 0 && !group_ok[share]) == 0;
         if (__ballot(cnt > 0) != 0)
             add_group<PREC, PEPS, PHI, 1>((const S *)(tile + share * kStride), cnt, full, tg,
                                           eps0sq, eps0f, skip, own, plain && tile_ok);
