@@ -312,8 +312,10 @@ constexpr int kSortTile = kSortThreads * kSortItems;
 constexpr int kRedBlocks = 512;
 
 // What a new workspace holds before its first build: empty boxes, a zero header with
-// the status words' address, and no cell marks. On the null stream.
-hipError_t launch_init(const Workspace &w);
+// the status words' address, no cell marks, and no parents (an adjoint's table, or
+// nullptr: a node that an overflow leaves unlinked has the entry of an earlier build, so
+// that there has to be one). On the null stream.
+hipError_t launch_init(const Workspace &w, int32_t *nparent);
 
 // The sort that a build enqueued: what bucket_sort_hint gave (0 and false for a
 // one-block build).

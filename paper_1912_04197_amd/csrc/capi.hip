@@ -780,7 +780,7 @@ bh_status bh_create(const bh_config *cfg, void *hip_stream, bh_ctx **out)
         for (auto &ev : c->ev_pool)
             if (r == hipSuccess) r = hipEventCreate(&ev);
     }
-    if (r == hipSuccess) r = bhx::launch_init(w);
+    if (r == hipSuccess) r = bhx::launch_init(w, c->aw.nparent);
     if (r == hipSuccess) r = hipDeviceSynchronize();
     if (r != hipSuccess) {
         bh_status st = (r == hipErrorOutOfMemory) ? BH_E_OOM : BH_E_HIP;

@@ -2362,7 +2362,8 @@ __global__ __launch_bounds__(256) void k_scene_of(const int64_t *__restrict__ of
 // One launch for a new workspace (three fills and a copy took 10 us more).
 __global__ __launch_bounds__(256) void k_init(SceneBox *__restrict__ box, int scenes,
                                               uint32_t *__restrict__ hdr, uint32_t *status,
-                                              int32_t *__restrict__ mark)
+                                              int32_t *__restrict__ mark,
+                                              int32_t *__restrict__ nparent, int64_t nodes)
 {
     const int t = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
     for (int i = t; i < scenes; i += stride) reset_box(box + i);
@@ -2372,13 +2373,16 @@ __global__ __launch_bounds__(256) void k_init(SceneBox *__restrict__ box, int sc
                  : i == kAt + 1 ? (uint32_t)((uintptr_t)status >> 32)
                                 : 0u;
     for (int i = t; i < kPrefixCells; i += stride) mark[i] = INT32_MAX;
+    if (nparent)
+        for (int64_t i = t; i < nodes; i += stride) nparent[i] = -1;
 }
 
 }  // namespace
 
-hipError_t launch_init(const Workspace &w)
+hipError_t launch_init(const Workspace &w, int32_t *nparent)
 {
-    k_init<<<128, 256>>>(w.box, w.max_scenes, (uint32_t *)w.hdr, w.status_dev, w.prefix_mark);
+    k_init<<<nparent ? 1024 : 128, 256>>>(w.box, w.max_scenes, (uint32_t *)w.hdr, w.status_dev,
+                                          w.prefix_mark, nparent, w.node_cap);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """A build that runs out of its node table reports it and stays inside its arrays: the
 checked library, which can be given a smaller table, in a child process. Each scene is
-built (and walked) twice (the second build from the first one's hints), then the same library
-builds it with a whole table."""
+built, walked and differentiated twice (the second build from the first one's hints),
+down to a table of exactly its nodes, which does."""
 import os
 import subprocess
 import sys
@@ -34,6 +34,15 @@ for cap in sorted({1, 2, 9, nodes // 50 + 3, nodes // 3, nodes - 1, nodes}):
         try:
             acc = ctx.compute_accel(pos, mass, 0.5, softening=1e-2)
             assert cap == nodes and torch.equal(acc, ref)
+        except api.BHError as e:
+            assert cap < nodes and e.status == L.BH_E_CAPACITY, e
+    os.environ["BHX_CHECKED_NODE_CAP"] = str(cap)
+    ctx = api.Context(n, leaf_size=leaf, precision="fp64", adjoint=True)
+    del os.environ["BHX_CHECKED_NODE_CAP"]
+    for _ in range(2):
+        try:
+            ctx.accel_vjp(pos, mass, pos, theta=0.5, softening=1e-2)
+            assert cap == nodes
         except api.BHError as e:
             assert cap < nodes and e.status == L.BH_E_CAPACITY, e
 """
